@@ -105,6 +105,9 @@ hipError_t launch_backward_siddon(const Plan& p, const float* proj, float* vol, 
                                   float beta, hipStream_t s);
 hipError_t launch_backward_interp(const Plan& p, const float* proj, float* vol, int64_t view0, int64_t nviews,
                                   float beta, float* shell, hipStream_t s);
+// the interpolated adjoint's bricks for calls of few views (without the shells' sums)
+hipError_t launch_backward_interp_few_bricks(const Plan& p, const float* proj, float* vol, int64_t view0,
+                                             int64_t nviews, float beta, float* shell, hipStream_t s);
 hipError_t launch_backward_fdk(const Plan& p, const float* proj, float* vol, int64_t view0, int64_t nviews,
                                float beta, hipStream_t s);
 hipError_t launch_fdk_filter(const Plan& p, int wang, const float* proj, float* out, int64_t view0,
