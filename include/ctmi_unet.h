@@ -57,6 +57,19 @@ int ctmi_conv3d_bf16_fwd(int n, int d, int h, int w, const uint16_t* in0, int c0
 int ctmi_conv3d_bf16_dgrad(int n, int d, int h, int w, const uint16_t* dz, int cout, int ldz, const uint16_t* wd,
                            int cin, const uint16_t* mask, int ldm, uint16_t* dx, int ldx, void* stream);
 
+/* The network's first convolution straight from its FP32 input x (one value
+ * per voxel): ctmi_unet_pack_input followed by ctmi_conv3d_bf16_fwd with 16
+ * input and 16 output channels, bit for bit, without the 16-channel copy.
+ * wt: [16][27][16]. */
+int ctmi_unet_conv_first(int n, int d, int h, int w, const float* x, const uint16_t* wt, const float* bias, int relu,
+                         uint16_t* out, int ldo, void* stream);
+
+/* The last convolution (16 to 16 channels) and the residual head in one:
+ * ctmi_conv3d_bf16_fwd followed by ctmi_unet_head, bit for bit, without
+ * storing the activations between them. */
+int ctmi_unet_conv_head(int n, int d, int h, int w, const uint16_t* in, int ldi, const uint16_t* wt, const float* bias,
+                        int relu, const float* xin, const uint16_t* hw, const float* hb, float* out, void* stream);
+
 /* Device workspace (bytes) of ctmi_conv3d_bf16_wgrad for these sizes. */
 size_t ctmi_conv3d_wgrad_workspace_bytes(int n, int d, int h, int w, int cin, int cout);
 

@@ -119,6 +119,8 @@ _SIGS = {
     "ctmi_conv3d_bf16_fwd": (c_int, [c_int] * 4 + [c_p, c_int, c_int, c_p, c_int, c_int, c_p, c_p, c_int, c_int, c_p,
                                                    c_int, c_p]),
     "ctmi_conv3d_bf16_dgrad": (c_int, [c_int] * 4 + [c_p, c_int, c_int, c_p, c_int, c_p, c_int, c_p, c_int, c_p]),
+    "ctmi_unet_conv_first": (c_int, [c_int] * 4 + [c_p, c_p, c_p, c_int, c_p, c_int, c_p]),
+    "ctmi_unet_conv_head": (c_int, [c_int] * 4 + [c_p, c_int, c_p, c_p, c_int, c_p, c_p, c_p, c_p, c_p]),
     "ctmi_conv3d_wgrad_workspace_bytes": (ctypes.c_size_t, [c_int] * 6),
     "ctmi_conv3d_bf16_wgrad": (c_int, [c_int] * 4 + [c_p, c_int, c_int, c_p, c_int, c_int, c_p, c_int, c_int, c_p, c_p,
                                                      c_int, c_p, ctypes.c_size_t, c_p]),

@@ -148,6 +148,10 @@ struct UnetConv3 {
     int ldo;
     int cout, relu;
     int n, d, h, w;
+    const float* x32 = nullptr;  // FP32 network input (first convolution, head)
+    const uint16_t* hw = nullptr; // head weights [16] BF16 and bias
+    const float* hb = nullptr;
+    float* out32 = nullptr;      // FP32 network output (head)
 };
 
 struct UnetWgrad {
@@ -163,6 +167,10 @@ struct UnetWgrad {
 };
 
 hipError_t launch_unet_conv3(const UnetConv3& a, hipStream_t s);
+// 16-channel convolutions with the network's ends: FP32 input (x32), FP32
+// output through the residual head (x32, hw, hb -> out32)
+hipError_t launch_unet_conv3_first(const UnetConv3& a, hipStream_t s);
+hipError_t launch_unet_conv3_head(const UnetConv3& a, hipStream_t s);
 int unet_wgrad_splits(int n, int d, int h, int w, int cin, int cout);
 size_t unet_wgrad_ws_bytes(int n, int d, int h, int w, int cin, int cout);
 hipError_t launch_unet_conv3_wgrad(const UnetWgrad& a, float* dw, float* db, int accumulate, hipStream_t s);

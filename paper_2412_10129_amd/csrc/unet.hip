@@ -13,12 +13,12 @@
 //
 // The 3x3x3 convolution is an implicit GEMM on the gfx950 BF16 MFMA
 // (16x16x32, FP32 accumulators): D[co][voxel] = sum_k W[co][k] X[k][voxel]
-// with k = (tap, ci).  A workgroup owns 2 x 8 x 16 output voxels and every
-// output channel; input channels are staged 16 at a time as a halo brick in
-// LDS (48-byte voxel stride: the sixteen 16-byte lane reads of a row hit
-// disjoint banks), and one MFMA step covers two taps x 16 channels.  Weights
-// stream from L1/L2 (they are small and shared by every workgroup).  The
-// data gradient is the same kernel with flipped, transposed weights.
+// with k = (tap, ci), one MFMA step covering two taps x 16 channels.  Up to 32
+// input channels (the fine levels, bound by memory) a workgroup marches along z
+// (k_conv3z); above, it owns 2 x 8 x 16 output voxels and stages its input 16
+// channels at a time as a halo brick in LDS (48-byte voxel stride: the sixteen
+// 16-byte lane reads of a row hit disjoint banks; k_conv3).  The data gradient
+// is the same kernels with flipped, transposed weights.
 #include "ctmi_internal.h"
 
 namespace ctmi {
@@ -74,14 +74,43 @@ constexpr int HX = CX + 2, HY = CY + 2, HZ = CZ + 2;  // halo brick
 constexpr int HVOX = HX * HY * HZ;                    // 720
 constexpr int VS = 24;                                // LDS voxel stride (u16): 16 ch + 8 pad
 
+// bias, ReLU, ReLU mask (m: the layer input's values) and BF16 rounding of
+// four output channels
+__device__ __forceinline__ uint2 conv_epilogue(const f32x4& acc, const float* bias, int relu, bool mask, uint2 m)
+{
+    float v[4] = {acc[0], acc[1], acc[2], acc[3]};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] += bias[e];
+    if (relu) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e], 0.0f);
+    }
+    if (mask) {
+        if (!bf_pos((u16)(m.x & 0xFFFF))) v[0] = 0.0f;
+        if (!bf_pos((u16)(m.x >> 16))) v[1] = 0.0f;
+        if (!bf_pos((u16)(m.y & 0xFFFF))) v[2] = 0.0f;
+        if (!bf_pos((u16)(m.y >> 16))) v[3] = 0.0f;
+    }
+    uint2 o;
+    o.x = (uint32_t)f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16);
+    o.y = (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16);
+    return o;
+}
+
+// More than 32 input channels: a workgroup owns 2 x 8 x 16 output voxels and
+// NT tiles of 16 output channels.  The next 16 channels of the halo are loaded
+// into registers while the staged ones are worked on, and the next step's weights
+// (from L1/L2) and LDS reads are issued before this step's MFMAs: without that the
+// kernel waited for memory in each of its 14 steps per 16 channels.
 template <int NT>
 __global__ __launch_bounds__(256) void k_conv3(UnetConv3 a)
 {
     __shared__ __attribute__((aligned(16))) u16 xs[HVOX * VS];
 
-    const int tiles_x = (a.w + CX - 1) / CX;
+    const int tiles_x = (a.w + CX - 1) / CX, tiles_y = (a.h + CY - 1) / CY;
     const int x0 = (blockIdx.x % tiles_x) * CX;
-    const int y0 = (blockIdx.x / tiles_x) * CY;
+    const int y0 = (blockIdx.x / tiles_x % tiles_y) * CY;
+    const int co0 = (blockIdx.x / (tiles_x * tiles_y)) * 16 * NT;   // the workgroup's output channels
     const int z0 = blockIdx.y * CZ;
     const int nb = blockIdx.z;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -97,54 +126,100 @@ __global__ __launch_bounds__(256) void k_conv3(UnetConv3 a)
     const size_t plane = (size_t)a.h * a.w;
     const size_t vbase = (size_t)nb * a.d * plane;
 
+    // staged elements of this thread: item i = tid + 256 m is half i & 1 of
+    // halo voxel i >> 1
+    constexpr int LD = (2 * HVOX + 255) / 256;
+    uint32_t off[LD];   // voxel distance from the halo's corner
+    bool ok[LD];
+#pragma unroll
+    for (int m = 0; m < LD; ++m) {
+        const int i = tid + 256 * m, hv = i >> 1;
+        const int hx = hv % HX, hy = (hv / HX) % HY, hz = hv / (HX * HY);
+        const int gx = x0 + hx - 1, gy = y0 + hy - 1, gz = z0 + hz - 1;
+        ok[m] = hv < HVOX && gx >= 0 && gx < a.w && gy >= 0 && gy < a.h && gz >= 0 && gz < a.d;
+        off[m] = (uint32_t)((hz * a.h + hy) * a.w + hx);
+    }
+    const int64_t corner = (int64_t)vbase + (int64_t)(z0 - 1) * (int64_t)plane + (int64_t)(y0 - 1) * a.w + (x0 - 1);
+    // the next 16 channels' halo is loaded into registers while the current
+    // ones are computed, and the next step's weights while a step is
+    uint4 pf[LD];
+    auto fetch = [&](int cc) {
+        const bool second = cc >= a.c0;
+        const u16* src = second ? a.in1 + (cc - a.c0) : a.in0 + cc;
+        const int ld = second ? a.ld1 : a.ld0;
+        src += corner * ld + (tid & 1) * 8;
+#pragma unroll
+        for (int m = 0; m < LD; ++m) {
+            pf[m] = make_uint4(0, 0, 0, 0);
+            if (ok[m]) pf[m] = *reinterpret_cast<const uint4*>(src + (uint64_t)off[m] * (uint32_t)ld);
+        }
+    };
+    const int t1 = g >> 1, ch = (g & 1) * 8;
+    // lane offset (bytes) of tap t1 of the lane's output channel; the rest of a
+    // fragment's address is the same in every lane
+    const uint32_t wl = 2u * (((uint32_t)(co0 + li) * 27u + (uint32_t)t1) * (uint32_t)cin + (uint32_t)ch);
+    auto weights = [&](uint4 (&wf)[NT], uint32_t wc, int s) {
+#pragma unroll
+        for (int n = 0; n < NT; ++n) {
+            wf[n] = make_uint4(0, 0, 0, 0);
+            if (s < 13 || t1 == 0)
+                wf[n] = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(a.wt) +
+                                                        (size_t)(wc + (uint32_t)((n * 16 * 27 + 2 * s) * 2 * cin)) + wl);
+        }
+    };
+    const u16* xl = xs + li * VS + ch;
+    auto inputs = [&](uint4 (&xf)[4], int s) {
+        // halo voxel of tap 2s, and of tap 2s + 1 in lanes 32-63 (tap 27 does not exist)
+        const int ta = 2 * s, tb = s < 13 ? ta + 1 : ta;
+        const int va = (ta / 9 * HY + ta / 3 % 3) * HX + ta % 3, vb = (tb / 9 * HY + tb / 3 % 3) * HX + tb % 3;
+        const u16* xt = xl + (t1 ? vb : va) * VS;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int rr = wave * 4 + r;
+            xf[r] = *reinterpret_cast<const uint4*>(xt + ((rr >> 3) * HY + (rr & 7)) * HX * VS);
+            if (s == 13 && t1) xf[r] = make_uint4(0, 0, 0, 0);
+        }
+    };
+    auto mfmas = [&](const uint4 (&wf)[NT], const uint4 (&xf)[4]) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int n = 0; n < NT; ++n)
+                acc[r][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wf[n]), as_bf16x8(xf[r]), acc[r][n], 0, 0, 0);
+    };
+    fetch(0);
     for (int cc = 0; cc < cin; cc += 16) {
-        const u16* src;
-        int ld;
-        if (cc < a.c0) {
-            src = a.in0 + cc;
-            ld = a.ld0;
-        } else {
-            src = a.in1 + (cc - a.c0);
-            ld = a.ld1;
+        // (an opaque scalar: otherwise every fragment's address becomes a
+        // 64-bit loop variable in vector registers)
+        uint32_t wc = 2 * cc;
+        asm volatile("" : "+s"(wc));
+        uint4 wa[NT], wb[NT];
+        weights(wa, wc, 0);
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < LD; ++m) {
+            const int i = tid + 256 * m;
+            if (i < 2 * HVOX) *reinterpret_cast<uint4*>(&xs[(i >> 1) * VS + (tid & 1) * 8]) = pf[m];
         }
         __syncthreads();
-        for (int i = tid; i < 2 * HVOX; i += 256) {
-            const int hv = i >> 1, half = i & 1;
-            const int hx = hv % HX, hy = (hv / HX) % HY, hz = hv / (HX * HY);
-            const int gx = x0 + hx - 1, gy = y0 + hy - 1, gz = z0 + hz - 1;
-            uint4 q = make_uint4(0, 0, 0, 0);
-            if (gx >= 0 && gx < a.w && gy >= 0 && gy < a.h && gz >= 0 && gz < a.d)
-                q = *reinterpret_cast<const uint4*>(src + (vbase + (size_t)gz * plane + (size_t)gy * a.w + gx) * ld +
-                                                     half * 8);
-            *reinterpret_cast<uint4*>(&xs[hv * VS + half * 8]) = q;
-        }
-        __syncthreads();
-
-#pragma unroll 2
-        for (int s = 0; s < 14; ++s) {
-            const int tap = 2 * s + (g >> 1);
-            const int ch = (g & 1) * 8;
-            const bool valid = tap < 27;
-            const int tz = tap / 9, ty = (tap / 3) % 3, tx = tap % 3;
-            uint4 wf[NT];
+        if (cc + 16 < cin) fetch(cc + 16);
+        uint4 xa[4], xb[4];
+        inputs(xa, 0);
+        // (the scheduling barriers keep the compiler from loading every step's
+        // weights at once, which spills, and each step's reads ahead of the
+        // MFMAs they follow)
 #pragma unroll
-            for (int n = 0; n < NT; ++n) {
-                wf[n] = make_uint4(0, 0, 0, 0);
-                if (valid)
-                    wf[n] = *reinterpret_cast<const uint4*>(a.wt + ((size_t)(n * 16 + li) * 27 + tap) * cin + cc + ch);
+        for (int s = 0; s < 14; s += 2) {
+            weights(wb, wc, s + 1);
+            inputs(xb, s + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            mfmas(wa, xa);
+            if (s + 2 < 14) {
+                weights(wa, wc, s + 2);
+                inputs(xa, s + 2);
             }
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int rr = wave * 4 + r;
-                const int zl = rr >> 3, yl = rr & 7;
-                const int hv = ((zl + tz) * HY + (yl + ty)) * HX + li + tx;
-                uint4 xf = make_uint4(0, 0, 0, 0);
-                if (valid) xf = *reinterpret_cast<const uint4*>(&xs[hv * VS + ch]);
-                const bf16x8 xb = as_bf16x8(xf);
-#pragma unroll
-                for (int n = 0; n < NT; ++n)
-                    acc[r][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wf[n]), xb, acc[r][n], 0, 0, 0);
-            }
+            __builtin_amdgcn_sched_barrier(0);
+            mfmas(wb, xb);
         }
     }
 
@@ -158,27 +233,241 @@ __global__ __launch_bounds__(256) void k_conv3(UnetConv3 a)
         const size_t vox = vbase + (size_t)z * plane + (size_t)y * a.w + x;
 #pragma unroll
         for (int n = 0; n < NT; ++n) {
-            const int co = n * 16 + 4 * g;
-            float v[4] = {acc[r][n][0], acc[r][n][1], acc[r][n][2], acc[r][n][3]};
-            if (a.bias) {
+            const int co = co0 + n * 16 + 4 * g;
+            float bias[4] = {0.f, 0.f, 0.f, 0.f};
+            if (a.bias)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] += a.bias[co + e];
-            }
-            if (a.relu) {
+                for (int e = 0; e < 4; ++e) bias[e] = a.bias[co + e];
+            uint2 m = make_uint2(0, 0);
+            if (a.mask) m = *reinterpret_cast<const uint2*>(a.mask + vox * a.ldm + co);
+            *reinterpret_cast<uint2*>(a.out + vox * a.ldo + co) = conv_epilogue(acc[r][n], bias, a.relu, a.mask != nullptr, m);
+        }
+    }
+}
+
+// Values of another row of 16 lanes: MOVE 0: rows 1 and 3 take rows 0 and 2;
+// 1: rows 2 and 3 take rows 0 and 1; 2: rows 0 and 2 take rows 1 and 3 (the
+// other rows get values that are not used).
+template <int MOVE>
+__device__ __forceinline__ float from_row(float q)
+{
+    const uint32_t u = __float_as_uint(q);
+    if (MOVE == 1) return __uint_as_float(__builtin_amdgcn_permlane32_swap(u, u, false, false)[0]);
+    return __uint_as_float(__builtin_amdgcn_permlane16_swap(u, u, false, false)[MOVE == 0 ? 0 : 1]);
+}
+
+// The same convolution for up to 32 input channels, marching along z: a
+// workgroup owns a 16 x YT column of output voxels over zc planes and keeps the
+// four input planes it works on in an LDS ring (planes z - 1, z, z + 1 of the
+// current output plane, and plane z + 2, loaded into registers while plane z
+// is computed), so an input plane is staged once per workgroup (1.27 to 1.4
+// voxels read per output voxel, against 2.8 of the 2 x 8 x 16 tiles) and a plane
+// costs one barrier.  A wave works on one tile of 16 output channels, whose
+// weights (14 fragments of 16 bytes per lane and 16 input channels) stay in
+// registers for the whole march; NTW = 2 gives the workgroup's waves two
+// channel tiles.  Every output is formed by the same MFMAs on the same operands
+// in the same order as in k_conv3, so the bits are the same.
+//
+// LDS reads and memory bound it about equally: 256^3, 16 -> 16 channels 301 us
+// (1.07 GB: 3.6 TB/s, of 4.7 that a copy reaches); the four layers at 256^3 with
+// the input's packing and the head 4040 us as 2 x 8 x 16 tiles and 1650 us so.
+//
+// LDS layout: per plane and 16 input channels two halves of 8 channels, voxels
+// 16 bytes apart within a half, so 16 lanes read 256 consecutive bytes and every
+// tap is an immediate offset from a few base addresses.  A step's two taps sit
+// in lanes 0-31 and 32-63: next to each other in x (base A), or at the ends of
+// two rows (base B), or, once, of two planes (base C).
+//
+// An output plane is written after the barrier that ends its phase, and what
+// its epilogue reads (mask, network input) is loaded a phase ahead: loads and
+// stores complete in order, so a store before the staged plane's arrival would
+// be waited for.
+//
+// FIRST reads the FP32 network input instead of 16-channel rows (channel 0 =
+// bf16(x), the others 0).  HEAD also applies the residual 1x1x1 head and writes
+// the FP32 network output instead of the activations.
+template <int NCH>
+constexpr int march_rows() { return NCH == 1 ? 16 : 8; }
+
+template <int NCH, int NTW, bool FIRST, bool HEAD, bool MASK>
+__global__ __launch_bounds__(256) void k_conv3z(UnetConv3 a, int zc)
+{
+    constexpr int YT = march_rows<NCH>(), RW = YT * NTW / 4;   // tile rows, rows per wave
+    constexpr int PX = CX + 2, PV = PX * (YT + 2);             // staged voxels per plane
+    constexpr int HP = PV * 8, PC = 2 * HP, PL = NCH * PC;     // u16 per half, per 16 channels, per plane
+    constexpr int LD = FIRST ? (PV + 255) / 256 : (2 * PV + 255) / 256;   // loads per thread, plane and 16 channels
+    __shared__ __attribute__((aligned(16))) u16 xs[4 * PL];
+
+    const int tiles_x = (a.w + CX - 1) / CX, tiles_y = (a.h + YT - 1) / YT;
+    const int x0 = (blockIdx.x % tiles_x) * CX;
+    const int y0 = (blockIdx.x / tiles_x % tiles_y) * YT;
+    const int cot = (blockIdx.x / (tiles_x * tiles_y)) * NTW;
+    const int z0 = blockIdx.y * zc, z1 = min(z0 + zc, a.d);
+    const int nb = blockIdx.z;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int g = lane >> 4, li = lane & 15;
+    const int cin = a.c0 + a.c1;
+    const int co0 = (cot + wave % NTW) * 16, row0 = (wave / NTW) * RW;
+    const int64_t plane = (int64_t)a.h * a.w;
+    const int64_t vbase = (int64_t)nb * a.d * plane;
+
+    // output channels of this lane's accumulator: 4 gc .. 4 gc + 3.  For the
+    // head lane groups 2 and 3 trade places (through the weights' rows), so
+    // that the channel order runs over the groups as 0, 1, 3, 2 and a sum can be
+    // handed on with v_permlane16_swap and v_permlane32_swap.
+    const int gc = HEAD ? g ^ (g >> 1) : g;
+    const int wrow = HEAD ? li ^ ((li & 8) >> 1) : li;
+    const int co = co0 + 4 * gc;
+
+    // weights of this wave's channel tile (step s: taps 2s and 2s + 1)
+    uint4 wf[NCH][14];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e], 0.0f);
+    for (int c = 0; c < NCH; ++c)
+#pragma unroll
+        for (int s = 0; s < 14; ++s) {
+            const int tap = 2 * s + (g >> 1);
+            wf[c][s] = make_uint4(0, 0, 0, 0);
+            if (tap < 27)
+                wf[c][s] = *reinterpret_cast<const uint4*>(a.wt + ((size_t)(co0 + wrow) * 27 + tap) * cin + c * 16 + (g & 1) * 8);
+        }
+
+    // this thread's staged elements: item i = tid + 256 m is half i & 1 of
+    // voxel i >> 1 (FIRST: voxel i); lane offsets below 2^31 bytes (the
+    // launcher checks)
+    int off[LD], dst[LD];
+    bool ok[LD];
+#pragma unroll
+    for (int m = 0; m < LD; ++m) {
+        const int i = tid + 256 * m;
+        const int hv = FIRST ? i : i >> 1, half = FIRST ? 0 : i & 1;
+        const int gx = x0 + hv % PX - 1, gy = y0 + hv / PX - 1;
+        ok[m] = hv < PV && gx >= 0 && gx < a.w && gy >= 0 && gy < a.h;
+        off[m] = ok[m] ? gy * a.w + gx : 0;
+        dst[m] = hv < PV ? half * HP + hv * 8 : -1;
+    }
+    uint4 pf[NCH][LD];
+    auto fetch = [&](int z) {
+        const bool zin = z >= 0 && z < a.d;
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            const bool second = 16 * c >= a.c0;
+            const u16* src = second ? a.in1 + (16 * c - a.c0) : a.in0 + 16 * c;
+            const int ld = second ? a.ld1 : a.ld0;
+#pragma unroll
+            for (int m = 0; m < LD; ++m) {
+                pf[c][m] = make_uint4(0, 0, 0, 0);
+                if (zin && ok[m]) {
+                    if (FIRST)
+                        pf[c][m].x = f2bf((a.x32 + (vbase + z * plane))[off[m]]);
+                    else
+                        pf[c][m] = *reinterpret_cast<const uint4*>(src + (vbase + z * plane) * ld +
+                                                                    (off[m] * ld + ((tid & 1) * 8)));
+                }
             }
-            if (a.mask) {
-                const uint2 m = *reinterpret_cast<const uint2*>(a.mask + vox * a.ldm + co);
-                if (!bf_pos((u16)(m.x & 0xFFFF))) v[0] = 0.0f;
-                if (!bf_pos((u16)(m.x >> 16))) v[1] = 0.0f;
-                if (!bf_pos((u16)(m.y & 0xFFFF))) v[2] = 0.0f;
-                if (!bf_pos((u16)(m.y >> 16))) v[3] = 0.0f;
+        }
+    };
+    auto put = [&](int slot) {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c)
+#pragma unroll
+            for (int m = 0; m < LD; ++m)
+                if (dst[m] >= 0) *reinterpret_cast<uint4*>(&xs[slot * PL + c * PC + dst[m]]) = pf[c][m];
+    };
+    if (FIRST)   // channels 8..15 stay zero
+        for (int i = tid; i < 4 * PV; i += 256)
+            *reinterpret_cast<uint4*>(&xs[(i / PV) * PL + HP + (i % PV) * 8]) = make_uint4(0, 0, 0, 0);
+    // plane z sits in slot (z - z0 + 1) & 3
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        fetch(z0 - 1 + i);
+        put(i);
+    }
+    __syncthreads();
+
+    const int x = x0 + li;
+    const int lb = (g & 1) * HP + (row0 * PX + li) * 8;   // this lane's voxel at tap (0, 0, 0), in u16
+    const int t1 = g >> 1;                                // second tap of a step
+    float bias[4] = {0.f, 0.f, 0.f, 0.f}, hwf[4] = {0.f, 0.f, 0.f, 0.f}, hb = 0.0f;
+    if (a.bias)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bias[e] = a.bias[co + e];
+    if (HEAD) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) hwf[e] = bf2f(a.hw[4 * gc + e]);
+        hb = a.hb[0];
+    }
+    bool in[RW];
+    int orow[RW];   // voxel of row r in a plane
+#pragma unroll
+    for (int r = 0; r < RW; ++r) {
+        const int y = y0 + row0 + r;
+        in[r] = x < a.w && y < a.h;
+        orow[r] = in[r] ? y * a.w + x : 0;
+    }
+    for (int z = z0; z < z1; ++z) {
+        const int q = z - z0;
+        const int64_t vz = vbase + z * plane;
+        if (z + 1 < z1) fetch(z + 2);
+        uint2 mk[MASK ? RW : 1];
+        float xi[HEAD ? RW : 1];
+#pragma unroll
+        for (int r = 0; r < RW; ++r) {
+            if (MASK) mk[r] = *reinterpret_cast<const uint2*>(a.mask + (vz + orow[r]) * a.ldm + co);
+            if (HEAD) xi[r] = a.x32[vz + orow[r]];
+        }
+        const u16* bA[3];
+        const u16* bB[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const u16* b = xs + ((q + k) & 3) * PL + lb;
+            bA[k] = b + t1 * 8;
+            bB[k] = b + t1 * (PX - 2) * 8;
+        }
+        // taps 8 (0, 2, 2) and 9 (1, 0, 0)
+        const u16* bC = xs + ((q + t1) & 3) * PL + lb + (t1 ? 0 : (2 * PX + 2) * 8);
+        f32x4 acc[RW];
+#pragma unroll
+        for (int r = 0; r < RW; ++r) acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < NCH; ++c)
+#pragma unroll
+            for (int s = 0; s < 14; ++s) {
+                const int tap = 2 * s, tz = tap / 9, ty = tap / 3 % 3, tx = tap % 3;
+                const u16* b = s == 4 ? bC : (tx == 2 ? bB[tz] : bA[tz]) + (ty * PX + tx) * 8;
+                if (s == 13) b = bA[2] - t1 * 8 + (2 * PX + 2) * 8;   // tap 26 (lanes 32-63 read it too and drop it)
+#pragma unroll
+                for (int r = 0; r < RW; ++r) {
+                    uint4 xf = *reinterpret_cast<const uint4*>(b + c * PC + r * PX * 8);
+                    if (s == 13 && t1) xf = make_uint4(0, 0, 0, 0);
+                    acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wf[c][s]), as_bf16x8(xf), acc[r], 0, 0, 0);
+                }
             }
-            uint2 o;
-            o.x = (uint32_t)f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16);
-            o.y = (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16);
-            *reinterpret_cast<uint2*>(a.out + vox * a.ldo + co) = o;
+        if (z + 1 < z1) {
+            // slot of plane z - 2, last read for output plane z - 1
+            put((q + 3) & 3);
+            __syncthreads();
+        }
+#pragma unroll
+        for (int r = 0; r < RW; ++r) {
+            const uint2 o = conv_epilogue(acc[r], bias, a.relu, MASK, MASK ? mk[r] : make_uint2(0, 0));
+            if (!HEAD) {
+                if (in[r]) *reinterpret_cast<uint2*>(a.out + (vz + orow[r]) * a.ldo + co) = o;
+                continue;
+            }
+            // head: sum over the 16 channels in order, 4 per lane group (the
+            // activations' BF16 values), added to the FP32 input
+            const float f[4] = {__uint_as_float(o.x << 16), __uint_as_float(o.x & 0xFFFF0000u),
+                                __uint_as_float(o.y << 16), __uint_as_float(o.y & 0xFFFF0000u)};
+            auto chain = [&](float t) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) t = fmaf(f[e], hwf[e], t);
+                return t;
+            };
+            float t = chain(0.0f);                 // lane group 0
+            t = chain(from_row<0>(t));             // group 1 continues group 0's sum
+            t = chain(from_row<1>(t));             // group 3, group 1's
+            t = chain(from_row<2>(t));             // group 2, group 3's
+            if (in[r] && g == 2) a.out32[vz + orow[r]] = xi[r] + (hb + t);
         }
     }
 }
@@ -971,19 +1260,54 @@ inline unsigned blocks_for(int64_t n, int bs) { return (unsigned)((n + bs - 1) /
 
 }  // namespace
 
+// k_conv3z marches over zc planes: 32 where the volume gives the 256 CUs a
+// few workgroups each that way, fewer where it does not (each march stages two
+// planes more than it computes)
+template <int NCH, int NTW, bool FIRST = false, bool HEAD = false>
+static hipError_t launch_conv3z(const UnetConv3& a, hipStream_t s)
+{
+    constexpr int YT = march_rows<NCH>();
+    const int64_t cols = (int64_t)((a.w + CX - 1) / CX) * ((a.h + YT - 1) / YT) * (a.cout / (16 * NTW));
+    int zc = 32;
+    while (zc > 2 && cols * a.n * ((a.d + zc - 1) / zc) < 1024) zc >>= 1;
+    const dim3 grid((unsigned)cols, (a.d + zc - 1) / zc, a.n);
+    if (!FIRST && !HEAD && a.mask)
+        k_conv3z<NCH, NTW, false, false, true><<<grid, 256, 0, s>>>(a, zc);
+    else
+        k_conv3z<NCH, NTW, FIRST, HEAD, false><<<grid, 256, 0, s>>>(a, zc);
+    return hipGetLastError();
+}
+
 hipError_t launch_unet_conv3(const UnetConv3& a, hipStream_t s)
 {
-    const int tiles_x = (a.w + CX - 1) / CX, tiles_y = (a.h + CY - 1) / CY, tiles_z = (a.d + CZ - 1) / CZ;
-    dim3 grid(tiles_x * tiles_y, tiles_z, a.n);
-    switch (a.cout) {
-    case 16: k_conv3<1><<<grid, 256, 0, s>>>(a); break;
-    case 32: k_conv3<2><<<grid, 256, 0, s>>>(a); break;
-    case 64: k_conv3<4><<<grid, 256, 0, s>>>(a); break;
-    case 128: k_conv3<8><<<grid, 256, 0, s>>>(a); break;
+    const int cin = a.c0 + a.c1;
+    const int64_t plane = (int64_t)a.h * a.w;
+    // up to 32 input channels: the z march (its lane offsets are 32-bit, and
+    // a chunk of 16 channels comes from one tensor)
+    if (cin <= 32 && a.c0 % 16 == 0 && plane * std::max(a.ld0, a.ld1) < (int64_t)1 << 30 && a.d <= 65535 * 2) {
+        if (cin == 16) return a.cout == 16 ? launch_conv3z<1, 1>(a, s) : launch_conv3z<1, 2>(a, s);
+        return a.cout == 16 ? launch_conv3z<2, 1>(a, s) : launch_conv3z<2, 2>(a, s);
+    }
+    const int tiles = ((a.w + CX - 1) / CX) * ((a.h + CY - 1) / CY), tiles_z = (a.d + CZ - 1) / CZ;
+    // output channels per workgroup: all of them (the halo is then read once), or
+    // fewer (down to 16) where the tiles alone leave most of the 256 CUs idle (the
+    // deep levels of four 64^3 crops: 38 to 101 us per layer with all, 19 us with 16)
+    int nt = a.cout / 16;
+    while (nt > 1 && (int64_t)tiles * tiles_z * a.n * (a.cout / (16 * nt)) < 512) nt >>= 1;
+    const dim3 grid(tiles * (a.cout / (16 * nt)), tiles_z, a.n);
+    switch (nt) {
+    case 1: k_conv3<1><<<grid, 256, 0, s>>>(a); break;
+    case 2: k_conv3<2><<<grid, 256, 0, s>>>(a); break;
+    case 4: k_conv3<4><<<grid, 256, 0, s>>>(a); break;
+    case 8: k_conv3<8><<<grid, 256, 0, s>>>(a); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
+
+hipError_t launch_unet_conv3_first(const UnetConv3& a, hipStream_t s) { return launch_conv3z<1, 1, true>(a, s); }
+
+hipError_t launch_unet_conv3_head(const UnetConv3& a, hipStream_t s) { return launch_conv3z<1, 1, false, true>(a, s); }
 
 int unet_wgrad_splits(int n, int d, int h, int w, int cin, int cout)
 {

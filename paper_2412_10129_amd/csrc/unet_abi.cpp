@@ -94,6 +94,40 @@ int ctmi_conv3d_bf16_dgrad(int n, int d, int h, int w, const uint16_t* dz, int c
     return ok_or(ctmi::launch_unet_conv3(a, S(stream)), "conv3d_bf16_dgrad");
 }
 
+int ctmi_unet_conv_first(int n, int d, int h, int w, const float* x, const uint16_t* wt, const float* bias, int relu,
+                         uint16_t* out, int ldo, void* stream)
+{
+    int rc;
+    if ((rc = check_dims(n, d, h, w)) || (rc = check_ptr4(x, "x")) || (rc = check_tensor(out, 16, ldo, 16, "out"))) return rc;
+    if ((int64_t)h * w >= (int64_t)1 << 28) return api_fail(CTMI_EOVERFLOW, "planes of 2^28 voxels or more");
+    if (!wt || reinterpret_cast<uintptr_t>(wt) % 16 != 0) return api_fail(CTMI_EINVAL, "weights NULL or not 16-byte aligned");
+    if (bias && (rc = check_ptr4(bias, "bias"))) return rc;
+    if (empty(n, d, h, w)) return CTMI_OK;
+    ctmi::UnetConv3 a{nullptr, 16, 16, nullptr, 0, 8, wt, bias, nullptr, 0, out, ldo, 16, relu ? 1 : 0, n, d, h, w};
+    a.x32 = x;
+    return ok_or(ctmi::launch_unet_conv3_first(a, S(stream)), "unet_conv_first");
+}
+
+int ctmi_unet_conv_head(int n, int d, int h, int w, const uint16_t* in, int ldi, const uint16_t* wt, const float* bias,
+                        int relu, const float* xin, const uint16_t* hw, const float* hb, float* out, void* stream)
+{
+    int rc;
+    if ((rc = check_dims(n, d, h, w)) || (rc = check_tensor(in, 16, ldi, 16, "in")) || (rc = check_ptr4(xin, "xin")) ||
+        (rc = check_ptr4(hb, "head bias")) || (rc = check_ptr4(out, "out")))
+        return rc;
+    if ((int64_t)h * w * ldi >= (int64_t)1 << 30) return api_fail(CTMI_EOVERFLOW, "planes of 2^30 activations or more");
+    if (!wt || reinterpret_cast<uintptr_t>(wt) % 16 != 0) return api_fail(CTMI_EINVAL, "weights NULL or not 16-byte aligned");
+    if (!hw || reinterpret_cast<uintptr_t>(hw) % 2 != 0) return api_fail(CTMI_EINVAL, "head weights NULL or misaligned");
+    if (bias && (rc = check_ptr4(bias, "bias"))) return rc;
+    if (empty(n, d, h, w)) return CTMI_OK;
+    ctmi::UnetConv3 a{in, 16, ldi, nullptr, 0, 8, wt, bias, nullptr, 0, nullptr, 0, 16, relu ? 1 : 0, n, d, h, w};
+    a.x32 = xin;
+    a.hw = hw;
+    a.hb = hb;
+    a.out32 = out;
+    return ok_or(ctmi::launch_unet_conv3_head(a, S(stream)), "unet_conv_head");
+}
+
 size_t ctmi_conv3d_wgrad_workspace_bytes(int n, int d, int h, int w, int cin, int cout)
 {
     if (n <= 0 || d <= 0 || h <= 0 || w <= 0 || cin <= 0 || cout <= 0) return 0;

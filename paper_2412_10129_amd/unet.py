@@ -177,12 +177,22 @@ class UNet:
             raise ValueError("volume sizes must be multiples of 8 (three 2x poolings)")
         nl = len(self.ch)
         c = {}
-        x0 = self._empty(n, d, h, w, 16)
-        L.check(L.lib().ctmi_unet_pack_input(_p(x), x.numel(), _p(x0), _stream(stream)))
-        c["x0"] = x0
-        hcur, skips = x0, []
+        # without the cache the first convolution reads x itself and the last
+        # one writes the network's output: neither the 16-channel copy of the
+        # input nor the last activations are stored
+        ends = not keep and nl > 1 and h * w < 1 << 26
+        hcur, skips = None, []
+        if not ends:
+            hcur = self._empty(n, d, h, w, 16)
+            L.check(L.lib().ctmi_unet_pack_input(_p(x), x.numel(), _p(hcur), _stream(stream)))
+            c["x0"] = hcur
         for lvl in range(nl):
-            a = self._conv(f"enc{lvl}a", hcur, stream=stream)
+            if lvl == 0 and ends:
+                a = self._empty(n, d, h, w, 16)
+                L.check(L.lib().ctmi_unet_conv_first(n, d, h, w, _p(x), _p(self.wf["enc0a"]), _p(self.b("enc0a")), 1,
+                                                     _p(a), 16, _stream(stream)))
+            else:
+                a = self._conv(f"enc{lvl}a", hcur, stream=stream)
             hcur = self._conv(f"enc{lvl}b", a, stream=stream)
             c[f"enc{lvl}a"], c[f"enc{lvl}b"] = a, hcur
             if lvl < nl - 1:
@@ -192,9 +202,16 @@ class UNet:
         for lvl in range(nl - 2, -1, -1):
             u = self._up(f"up{lvl}", hcur, stream)
             a = self._conv(f"dec{lvl}a", u, skips[lvl], stream=stream)
+            if lvl == 0 and ends:
+                break
             hcur = self._conv(f"dec{lvl}b", a, stream=stream)
             c[f"up{lvl}"], c[f"dec{lvl}a"], c[f"dec{lvl}b"] = u, a, hcur
         out = torch.empty_like(x)
+        if ends:
+            L.check(L.lib().ctmi_unet_conv_head(n, d, h, w, _p(a), 16, _p(self.wf["dec0b"]), _p(self.b("dec0b")), 1,
+                                                _p(x), _p(self.wf["head"]), _p(self.b("head")), _p(out),
+                                                _stream(stream)))
+            return out[0] if squeeze else out
         L.check(L.lib().ctmi_unet_head(x.numel(), _p(x), _p(hcur), 16, 16, _p(self.wf["head"]), _p(self.b("head")),
                                        _p(out), _stream(stream)))
         c["x_in"] = x

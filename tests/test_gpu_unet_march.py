@@ -1,0 +1,95 @@
+"""The 3x3x3 convolution at the edges of its work split: the z march of up to
+32 input channels (columns of 16 x 16 or 16 x 8 voxels, marches of 2 to 32
+planes) and the output-channel split of the others, against the FP64 oracle;
+the fused ends of the network against the calls that they stand for, bit for
+bit."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import synth
+from oracle import unet as U
+from test_gpu_unet import P, _bf, _bf16_close, _lib, _np, _p, _s  # noqa: F401 (P: fixture)
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+def _conv(L, n, d, h, w, x0, c0, x1, c1, wt, b, cout):
+    out = torch.full((n, d, h, w, cout), float("nan"), dtype=torch.bfloat16, device="cuda")
+    L.check(L.lib().ctmi_conv3d_bf16_fwd(n, d, h, w, _p(x0), c0, x0.shape[-1], _p(x1), c1, x1.shape[-1] if c1 else 8,
+                                         _p(wt), _p(b), cout, 1, _p(out), cout, _s()))
+    return out
+
+
+# one voxel, one march and one more plane, columns cut in x and y, both tensors of
+# a concatenation, rows wider than their channels; from 48 channels on the tiles
+@pytest.mark.parametrize("n,d,h,w,c0,ld0,c1,cout", [
+    (1, 1, 1, 1, 16, 16, 0, 16),
+    (2, 3, 16, 16, 16, 16, 0, 32),
+    (1, 5, 17, 15, 16, 40, 0, 16),
+    (1, 2, 9, 17, 16, 24, 16, 16),
+    (1, 4, 8, 33, 32, 32, 0, 64),
+    (3, 1, 7, 16, 32, 48, 0, 128),
+    (1, 3, 9, 17, 48, 48, 0, 32),
+    (2, 2, 8, 16, 32, 32, 32, 64),
+])
+def test_conv3_split_edges(P, n, d, h, w, c0, ld0, c1, cout):  # noqa: F811
+    L = _lib()
+    x0 = synth.bf16_values((n, d, h, w, c0), 11)
+    x1 = synth.bf16_values((n, d, h, w, c1), 12) if c1 else None
+    wt = synth.bf16_values((cout, 27, c0 + c1), 13, -0.2, 0.2)
+    b = synth.bf16_values((cout,), 14, -0.5, 0.5)
+    wide = np.full((n, d, h, w, ld0), 1e30, np.float32)
+    wide[..., :c0] = x0
+    got = _conv(L, n, d, h, w, _bf(wide), c0, _bf(x1) if c1 else None, c1, _bf(wt), torch.from_numpy(b).cuda(), cout)
+    want = np.maximum(U.conv3(np.concatenate([x0, x1], -1) if c1 else x0, wt, b), 0.0)
+    assert not np.isnan(_np(got)).any()
+    _bf16_close(_np(got), want)
+
+
+@pytest.mark.parametrize("cin,cout", [(16, 16), (16, 32), (32, 16), (32, 32)])
+def test_march_length_does_not_matter(P, cin, cout):  # noqa: F811
+    """A volume that is marched in the longest pieces and thin slabs of it give
+    the same bits (every output is the same sum, whatever the split)."""
+    L = _lib()
+    d, h, w = 67, 264, 528
+    g = torch.Generator(device="cuda").manual_seed(15)
+    x = torch.randn((1, d, h, w, cin), generator=g, device="cuda").to(torch.bfloat16)
+    wt = (0.1 * torch.randn((cout, 27, cin), generator=g, device="cuda")).to(torch.bfloat16)
+    b = torch.randn(cout, generator=g, device="cuda")
+    full = _conv(L, 1, d, h, w, x, cin, None, 0, wt, b, cout)
+    for z0, z1 in ((0, 5), (29, 36), (61, d)):
+        slab = _conv(L, 1, z1 - z0, h, w, x[:, z0:z1].contiguous(), cin, None, 0, wt, b, cout)
+        lo, hi = (0 if z0 == 0 else 1), (z1 - z0 if z1 == d else z1 - z0 - 1)
+        assert torch.equal(slab[:, lo:hi].view(torch.int16), full[:, z0 + lo:z0 + hi].view(torch.int16))
+
+
+@pytest.mark.parametrize("n,d,h,w", [(1, 1, 1, 1), (1, 3, 5, 7), (2, 33, 18, 50), (1, 34, 16, 16), (4, 64, 64, 64)])
+def test_fused_ends_are_the_separate_calls(P, n, d, h, w):  # noqa: F811
+    L = _lib()
+    g = torch.Generator(device="cuda").manual_seed(16)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda")  # noqa: E731
+    x, b, hb = rnd(n, d, h, w), rnd(16), rnd(1)
+    w1, w2, hw = (0.2 * rnd(16, 27, 16)).to(torch.bfloat16), (0.1 * rnd(16, 27, 16)).to(torch.bfloat16), rnd(16).to(torch.bfloat16)
+    x16 = torch.empty((n, d, h, w, 16), dtype=torch.bfloat16, device="cuda")
+    L.check(L.lib().ctmi_unet_pack_input(_p(x), x.numel(), _p(x16), _s()))
+    a = _conv(L, n, d, h, w, x16, 16, None, 0, w1, b, 16)
+    a2 = torch.full_like(a, float("nan"))
+    L.check(L.lib().ctmi_unet_conv_first(n, d, h, w, _p(x), _p(w1), _p(b), 1, _p(a2), 16, _s()))
+    assert torch.equal(a.view(torch.int16), a2.view(torch.int16))
+    last = _conv(L, n, d, h, w, a, 16, None, 0, w2, b, 16)
+    want, got = torch.empty_like(x), torch.full_like(x, float("nan"))
+    L.check(L.lib().ctmi_unet_head(x.numel(), _p(x), _p(last), 16, 16, _p(hw), _p(hb), _p(want), _s()))
+    L.check(L.lib().ctmi_unet_conv_head(n, d, h, w, _p(a), 16, _p(w2), _p(b), 1, _p(x), _p(hw), _p(hb), _p(got), _s()))
+    assert torch.equal(got, want)
+
+
+def test_forward_with_and_without_the_cache(P):  # noqa: F811
+    """The inference path (fused ends) and the training forward give the same bits."""
+    net = P.UNet(seed=3)
+    x = torch.randn((2, 16, 24, 32), device="cuda", generator=torch.Generator(device="cuda").manual_seed(17))
+    out = net.forward(x)
+    kept = net.forward(x, keep=True)
+    assert torch.equal(out, kept[0] if isinstance(kept, tuple) else kept)
