@@ -475,29 +475,90 @@ __global__ __launch_bounds__(256) void k_conv3z(UnetConv3 a, int zc)
 // ------------------------------------------------------------ conv3 wgrad
 // dW[co][t][ci] = sum_v dz[v][co] x[v + t][ci]: an MFMA GEMM with M = 16
 // output channels, N = 16 input channels, K = voxels.  Both operands need 8
-// consecutive voxels per lane, so the workgroup stages its 2 x 8 x 16 voxel
-// tile transposed in LDS: dz as [co][voxel] and the input halo as three
-// x-shifted copies [shift][ci][z][y][16] (one per kx, so every 8-voxel read
-// is 16-byte aligned).  Wave w owns taps w, w + 4, ...; a workgroup owns
-// one (co tile, ci tile) pair and a strided share of the voxel tiles, and
-// writes its FP32 partial sums; a second kernel adds the partials in a
-// fixed order.
-constexpr int WG_DZS = 256 + 8;        // dz row stride (u16)
-constexpr int WG_XROW = HZ * HY * 16;  // 640
-constexpr int WG_XS = WG_XROW + 8;     // x ci-row stride (u16)
+// consecutive voxels of one channel per lane: the workgroup stages its 2 x 8 x
+// 16 voxel tile as it lies in memory ([voxel][16 channels], dz and the input
+// halo) and reads the fragments transposed (ds_read_b64_tr_b16: four voxels of
+// one channel per lane; lane group g takes row g / 2 and x half g % 2 of a row
+// pair).  Waves 0 to 2 own the nine taps kx = wave; a row pair of the halo
+// that the next step's ky = 0 shares with this one's ky = 2 stays in registers.
+// The next tile is loaded into registers while one is computed.  A workgroup
+// owns one (co tile, ci tile) pair and a strided share of the voxel tiles, and
+// writes its FP32 partial sums; the blocks past them sum dz alone, for the bias
+// gradient (channel_sums); a second kernel adds both in a fixed order.
+// Against fragments transposed through 16-bit LDS writes and three x-shifted
+// copies of the halo, and bias sums in launches of their own: the 17
+// weight gradients of a training step on four 64^3 crops with their bias sums and
+// the adding up 1414 us, now 608 us (382 of them here).
+constexpr int WG_T = 256;
+constexpr int WG_ITEMS = 2 * 256 + 2 * HVOX;           // 16-byte items: dz tile, then input halo
+constexpr int WG_LD = (WG_ITEMS + WG_T - 1) / WG_T;
 
-__global__ __launch_bounds__(256) void k_conv3_wgrad(UnetWgrad a)
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ s16x4 read_tr(const u16* p)
 {
-    __shared__ __attribute__((aligned(16))) u16 dzs[16 * WG_DZS];
-    __shared__ __attribute__((aligned(16))) u16 xsh[3 * 16 * WG_XS];
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p);
+}
 
-    const int ci_tiles = (a.c0 + a.c1) / 16;
-    const int pair = blockIdx.x;
-    const int cot = pair / ci_tiles, cit = pair % ci_tiles;
-    const int split = blockIdx.y, nsplit = gridDim.y;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int g = lane >> 4, li = lane & 15;
+__device__ __forceinline__ bf16x8 join(s16x4 a, s16x4 b)
+{
+    bf16x8 r;
+    __builtin_memcpy(&r, &a, 8);
+    __builtin_memcpy(reinterpret_cast<char*>(&r) + 8, &b, 8);
+    return r;
+}
+
+// Fragment of 8 voxels x 1 channel per lane (two reads of four voxels; rows of
+// 16 channels)
+__device__ __forceinline__ bf16x8 read_tr8(const u16* p) { return join(read_tr(p), read_tr(p + 4 * 16)); }
+
+// Channel sums of a BF16 tensor of c channels, block blk of nblk of 256 threads:
+// partial[blk][c] (FP32).  Thread = (voxel lane, group of 8 channels); the voxel
+// lanes' sums go through LDS (red: 2048 floats), where a thread adds those of
+// one channel in order.
+__device__ __forceinline__ void channel_sums(const u16* __restrict__ t, int ld, int c, int64_t nvox, int blk, int nblk,
+                                             float* red, float* __restrict__ partial)
+{
+    const int groups = c / 8, lanes = 256 / groups;
+    const int tid = threadIdx.x, cg = tid % groups, vl = tid / groups;
+    float s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (vl < lanes) {
+#pragma unroll 4
+        for (int64_t v = (int64_t)blk * lanes + vl; v < nvox; v += (int64_t)nblk * lanes) {
+            float f[8];
+            unpack8(*reinterpret_cast<const uint4*>(t + v * ld + cg * 8), f);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) s[i] += f[i];
+        }
+        *reinterpret_cast<float4*>(&red[vl * c + cg * 8]) = make_float4(s[0], s[1], s[2], s[3]);
+        *reinterpret_cast<float4*>(&red[vl * c + cg * 8 + 4]) = make_float4(s[4], s[5], s[6], s[7]);
+    }
+    __syncthreads();
+    for (int i = tid; i < c; i += 256) {
+        float tot = 0.0f;
+#pragma unroll 16
+        for (int l = 0; l < lanes; ++l) tot += red[l * c + i];
+        partial[(size_t)blk * c + i] = tot;
+    }
+}
+
+__global__ __launch_bounds__(WG_T) void k_conv3_wgrad(UnetWgrad a, int nsplit, int nbias, float* __restrict__ bias)
+{
+    __shared__ __attribute__((aligned(16))) u16 ls[WG_ITEMS * 8];
+    u16* const dzs = ls;
+    u16* const xs = ls + 512 * 8;
+
     const int cin = a.c0 + a.c1;
+    const int ci_tiles = cin / 16, pairs = ci_tiles * (a.cout / 16);
+    const int pair = blockIdx.x % pairs, split = blockIdx.x / pairs;
+    if (split >= nsplit) {
+        channel_sums(a.dz, a.ldz, a.cout, (int64_t)a.n * a.d * a.h * a.w, blockIdx.x - pairs * nsplit, nbias,
+                     reinterpret_cast<float*>(ls), bias);
+        return;
+    }
+    const int cot = pair / ci_tiles, cit = pair % ci_tiles;
+    const int tid = threadIdx.x, lane = tid & 63, kx = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 4, li = lane & 15;
 
     const u16* xsrc;
     int xld;
@@ -514,120 +575,141 @@ __global__ __launch_bounds__(256) void k_conv3_wgrad(UnetWgrad a)
     const int ntiles = tiles_x * tiles_y * tiles_z * a.n;
     const size_t plane = (size_t)a.h * a.w;
 
-    f32x4 acc[7];
+    // this thread's items tid + 256 m: tile-relative voxel (x, y, z), the halo's from -1
+    int lx[WG_LD], ly[WG_LD], lz[WG_LD];
 #pragma unroll
-    for (int j = 0; j < 7; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    for (int t = split; t < ntiles; t += nsplit) {
+    for (int m = 0; m < WG_LD; ++m) {
+        const int i = tid + WG_T * m;
+        if (i < 512) {
+            const int v = i >> 1;
+            lx[m] = v & 15;
+            ly[m] = (v >> 4) & 7;
+            lz[m] = v >> 7;
+        } else {
+            const int v = (i - 512) >> 1;
+            lx[m] = v % HX - 1;
+            ly[m] = (v / HX) % HY - 1;
+            lz[m] = v / (HX * HY) - 1;
+        }
+    }
+    uint4 pf[WG_LD];
+    auto fetch = [&](int t) {
         int rem = t;
-        const int tx_ = rem % tiles_x;
+        const int x0 = (rem % tiles_x) * CX;
         rem /= tiles_x;
-        const int ty_ = rem % tiles_y;
+        const int y0 = (rem % tiles_y) * CY;
         rem /= tiles_y;
-        const int tz_ = rem % tiles_z;
-        const int nb = rem / tiles_z;
-        const int x0 = tx_ * CX, y0 = ty_ * CY, z0 = tz_ * CZ;
-        const size_t vbase = (size_t)nb * a.d * plane;
-
-        __syncthreads();
-        // dz tile: 256 voxels x 16 channels -> dzs[co][voxel]
-        {
-            const int v = tid;  // one voxel per thread
-            const int xl = v & 15, yl = (v >> 4) & 7, zl = v >> 7;
-            const int gx = x0 + xl, gy = y0 + yl, gz = z0 + zl;
-            if (gx < a.w && gy < a.h && gz < a.d) {
-                const u16* p = dsrc + (vbase + (size_t)gz * plane + (size_t)gy * a.w + gx) * a.ldz;
-                const uint4 q0 = *reinterpret_cast<const uint4*>(p);
-                const uint4 q1 = *reinterpret_cast<const uint4*>(p + 8);
-                const uint32_t wd[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
+        const int z0 = (rem % tiles_z) * CZ;
+        const size_t vbase = (size_t)(rem / tiles_z) * a.d * plane;
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    dzs[(2 * i) * WG_DZS + v] = (u16)(wd[i] & 0xFFFF);
-                    dzs[(2 * i + 1) * WG_DZS + v] = (u16)(wd[i] >> 16);
-                }
-            } else {
-#pragma unroll
-                for (int i = 0; i < 16; ++i) dzs[i * WG_DZS + v] = 0;
+        for (int m = 0; m < WG_LD; ++m) {
+            const int i = tid + WG_T * m;
+            const int gx = x0 + lx[m], gy = y0 + ly[m], gz = z0 + lz[m];
+            pf[m] = make_uint4(0, 0, 0, 0);
+            if (i < WG_ITEMS && gx >= 0 && gx < a.w && gy >= 0 && gy < a.h && gz >= 0 && gz < a.d) {
+                const size_t v = vbase + (size_t)gz * plane + (size_t)gy * a.w + gx;
+                pf[m] = *reinterpret_cast<const uint4*>((i < 512 ? dsrc + v * a.ldz : xsrc + v * xld) + (tid & 1) * 8);
             }
         }
-        // input halo: 4 x 10 x 18 voxels x 16 channels -> three shifted copies
-        for (int hv = tid; hv < HVOX; hv += 256) {
-            const int hx = hv % HX, hy = (hv / HX) % HY, hz = hv / (HX * HY);
-            const int gx = x0 + hx - 1, gy = y0 + hy - 1, gz = z0 + hz - 1;
-            uint32_t wd[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-            if (gx >= 0 && gx < a.w && gy >= 0 && gy < a.h && gz >= 0 && gz < a.d) {
-                const u16* p = xsrc + (vbase + (size_t)gz * plane + (size_t)gy * a.w + gx) * xld;
-                const uint4 q0 = *reinterpret_cast<const uint4*>(p);
-                const uint4 q1 = *reinterpret_cast<const uint4*>(p + 8);
-                wd[0] = q0.x; wd[1] = q0.y; wd[2] = q0.z; wd[3] = q0.w;
-                wd[4] = q1.x; wd[5] = q1.y; wd[6] = q1.z; wd[7] = q1.w;
-            }
-            const int rowoff = (hz * HY + hy) * 16;
+    };
+
+    f32x4 acc[3][3];   // [kz][ky]
 #pragma unroll
-            for (int s = 0; s < 3; ++s) {
-                const int j = hx - s;
-                if (j < 0 || j >= 16) continue;
+    for (int j = 0; j < 9; ++j) acc[j / 3][j % 3] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // this lane's read addresses within a row pair
+    const int la = ((g >> 1) * CX + 8 * (g & 1) + (li >> 2)) * 16 + (li & 3) * 4;
+    const int lb = ((g >> 1) * HX + 8 * (g & 1) + (li >> 2) + kx) * 16 + (li & 3) * 4;
+
+    fetch(split);
+    for (int t = split; t < ntiles; t += nsplit) {
+        __syncthreads();   // the previous tile's fragments have been read
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    xsh[(s * 16 + 2 * i) * WG_XS + rowoff + j] = (u16)(wd[i] & 0xFFFF);
-                    xsh[(s * 16 + 2 * i + 1) * WG_XS + rowoff + j] = (u16)(wd[i] >> 16);
-                }
-            }
+        for (int m = 0; m < WG_LD; ++m) {
+            const int i = tid + WG_T * m;
+            if (i < WG_ITEMS) *reinterpret_cast<uint4*>(&ls[i * 8]) = pf[m];
         }
         __syncthreads();
-
-        // K = 256 voxels in 8 steps of 32: lane group g takes row 2k + (g >> 1),
-        // x-half (g & 1)
-#pragma unroll 2
-        for (int k = 0; k < 8; ++k) {
-            const int rr = 2 * k + (g >> 1);
-            const int xh = (g & 1) * 8;
-            const int zl = rr >> 3, yl = rr & 7;
-            const bf16x8 af = as_bf16x8(*reinterpret_cast<const uint4*>(&dzs[li * WG_DZS + rr * 16 + xh]));
+        if (t + nsplit < ntiles) fetch(t + nsplit);
+        if (kx == 3) continue;   // the fourth wave only loads
 #pragma unroll
-            for (int j = 0; j < 7; ++j) {
-                const int tap = wave + 4 * j;
-                if (tap < 27) {
-                    const int kz = tap / 9, ky = (tap / 3) % 3, kx = tap % 3;
-                    const uint4 bq = *reinterpret_cast<const uint4*>(
-                        &xsh[(kx * 16 + li) * WG_XS + ((zl + kz) * HY + (yl + ky)) * 16 + xh]);
-                    acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, as_bf16x8(bq), acc[j], 0, 0, 0);
+        for (int zl = 0; zl < CZ; ++zl) {
+            bf16x8 first[3];
+#pragma unroll
+            for (int kz = 0; kz < 3; ++kz) first[kz] = read_tr8(xs + lb + (zl + kz) * HY * HX * 16);
+#pragma unroll
+            for (int y = 0; y < CY; y += 2) {
+                const bf16x8 af = read_tr8(dzs + la + (zl * CY + y) * CX * 16);
+#pragma unroll
+                for (int kz = 0; kz < 3; ++kz) {
+                    const u16* row = xs + lb + ((zl + kz) * HY + y) * HX * 16;
+                    const bf16x8 b1 = read_tr8(row + HX * 16), b2 = read_tr8(row + 2 * HX * 16);
+                    acc[kz][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, first[kz], acc[kz][0], 0, 0, 0);
+                    acc[kz][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, b1, acc[kz][1], 0, 0, 0);
+                    acc[kz][2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, b2, acc[kz][2], 0, 0, 0);
+                    first[kz] = b2;
                 }
             }
         }
     }
+    if (kx == 3) return;
 
     // partial[split][co][t][ci]: lane holds rows co = 4g + e, column ci = li
     float* part = a.partial + (size_t)split * a.cout * 27 * cin;
 #pragma unroll
-    for (int j = 0; j < 7; ++j) {
-        const int tap = wave + 4 * j;
-        if (tap >= 27) continue;
+    for (int j = 0; j < 9; ++j) {
+        const int tap = 3 * j + kx;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int co = cot * 16 + 4 * g + e;
-            part[((size_t)co * 27 + tap) * cin + cit * 16 + li] = acc[j][e];
+            part[((size_t)co * 27 + tap) * cin + cit * 16 + li] = acc[j / 3][j % 3][e];
         }
     }
 }
 
-// out[i] = sum_s partial[s][i] (fixed order), FP32
-// out[i] (+)= sum over k of partial[k][i]: a 256-thread block takes 32
-// consecutive i and 8 lanes of splits (lane l sums the splits k = l mod 8 in
-// order), then lane 0 adds the 8 lane sums in order: a fixed summation
-// order, so the result is reproducible, with 8x the parallelism of one
-// thread per i (the small layers have a few thousand weights over up to
-// 1024 splits).
-constexpr int SUM_E = 32, SUM_L = 8;
-__global__ __launch_bounds__(256) void k_sum_partials(const float* __restrict__ partial, int nsplit, int64_t n,
-                                                      float* __restrict__ out, int accumulate)
+// dw[i] (+)= sum over k of partial[k][i], k < nsplit, i < nw, and db[i] (+)= the
+// sum over k of bias[k][i], k < nbias, i < nb: a 256-thread block takes 32
+// consecutive i and 8 lanes of k (lane l sums k = l mod 8 in order), then one
+// thread adds the 8 lane sums in order: a fixed summation order, so the result
+// is reproducible.  Latency bounds it (each sum is a chain of up to 128 adds):
+// SUM_F loads are in flight per thread, and dw and db share a launch.
+constexpr int SUM_E = 32, SUM_L = 8, SUM_F = 32;
+__global__ __launch_bounds__(256) void k_sum_partials(const float* __restrict__ partial, int nsplit, int64_t nw,
+                                                      const float* __restrict__ bias, int nbias, int nb,
+                                                      float* __restrict__ dw, float* __restrict__ db, int accumulate)
 {
     __shared__ float red[SUM_L][SUM_E];
+    const int64_t dwb = (nw + SUM_E - 1) / SUM_E;
+    int64_t i0 = (int64_t)blockIdx.x * SUM_E, n = nw;
+    const float* p = partial;
+    float* out = dw;
+    if (blockIdx.x >= dwb) {
+        i0 -= dwb * SUM_E;
+        n = nb;
+        p = bias;
+        out = db;
+        nsplit = nbias;
+    }
     const int e = threadIdx.x % SUM_E, l = threadIdx.x / SUM_E;
-    const int64_t i = (int64_t)blockIdx.x * SUM_E + e;
+    const int64_t i = i0 + e;
     float s = 0.0f;
-    if (i < n)
-        for (int k = l; k < nsplit; k += SUM_L) s += partial[(size_t)k * n + i];
+    if (i < n) {
+        const float* q = p + i + l * n;
+        int k = l;
+        for (; k + (SUM_F - 1) * SUM_L < nsplit; k += SUM_F * SUM_L, q += SUM_F * SUM_L * n) {
+            float v[SUM_F];
+#pragma unroll
+            for (int j = 0; j < SUM_F; ++j) v[j] = q[j * SUM_L * n];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < SUM_F; ++j) s += v[j];
+        }
+        float v[SUM_F];
+#pragma unroll
+        for (int j = 0; j < SUM_F; ++j) v[j] = k + j * SUM_L < nsplit ? q[j * SUM_L * n] : 0.0f;
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < SUM_F; ++j) s = k + j * SUM_L < nsplit ? s + v[j] : s;
+    }
     red[l][e] = s;
     __syncthreads();
     if (l == 0 && i < n) {
@@ -635,37 +717,6 @@ __global__ __launch_bounds__(256) void k_sum_partials(const float* __restrict__ 
 #pragma unroll
         for (int m = 1; m < SUM_L; ++m) t += red[m][e];
         out[i] = accumulate ? out[i] + t : t;
-    }
-}
-
-// per-block channel sums of a BF16 tensor: partial[block][c] (FP32)
-__global__ __launch_bounds__(256) void k_channel_sums(const u16* __restrict__ t, int ld, int c, int64_t nvox,
-                                                      float* __restrict__ partial)
-{
-    __shared__ float red[256];
-    // thread = (voxel lane vl, channel group of 8 cg); 256 / (c / 8) voxel lanes
-    const int groups = c / 8;
-    const int lanes = 256 / groups;
-    const int tid = threadIdx.x;
-    const int cg = tid % groups, vl = tid / groups;
-    float s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (vl < lanes) {
-        for (int64_t v = (int64_t)blockIdx.x * lanes + vl; v < nvox; v += (int64_t)gridDim.x * lanes) {
-            float f[8];
-            unpack8(*reinterpret_cast<const uint4*>(t + v * ld + cg * 8), f);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) s[i] += f[i];
-        }
-    }
-    for (int i = 0; i < 8; ++i) {
-        red[tid] = (vl < lanes) ? s[i] : 0.0f;
-        __syncthreads();
-        if (tid < groups) {
-            float tot = 0.0f;
-            for (int l = 0; l < lanes; ++l) tot += red[l * groups + tid];
-            partial[(size_t)blockIdx.x * c + tid * 8 + i] = tot;
-        }
-        __syncthreads();
     }
 }
 
@@ -999,89 +1050,34 @@ __global__ __launch_bounds__(256) void k_up2_dgrad_mfma(const u16* __restrict__ 
     }
 }
 
-// weight gradient of up2: dw[co][s][ci] = sum_v g[2v + s][co] x[v][ci].
-// Block = (s, co tile of 16, ci tile of 16) x voxel split; thread = one
-// (co, ci) output; 64 coarse voxels per LDS round.
-__global__ __launch_bounds__(256) void k_up2_wgrad(const u16* __restrict__ x, int ldx, int cin,
-                                                   const u16* __restrict__ gr, int ldg, int cout, int n, int d, int h,
-                                                   int w, float* __restrict__ partial)
-{
-    __shared__ float gs[64][17];
-    __shared__ float xs_[64][17];
-    const int ci_tiles = cin / 16, co_tiles = cout / 16;
-    int b = blockIdx.x;
-    const int cit = b % ci_tiles;
-    b /= ci_tiles;
-    const int cot = b % co_tiles;
-    const int s = b / co_tiles;
-    const int split = blockIdx.y, nsplit = gridDim.y;
-    const int tid = threadIdx.x;
-    const int co_l = tid >> 4, ci_l = tid & 15;
-    const int64_t nvox = (int64_t)n * d * h * w;
-    const int64_t nchunks = (nvox + 63) / 64;
-    float acc = 0.0f;
-    for (int64_t ch = split; ch < nchunks; ch += nsplit) {
-        __syncthreads();
-        {
-            const int vl = tid >> 2, part = tid & 3;  // 64 voxels x 4 groups of 4 channels
-            const int64_t v = ch * 64 + vl;
-            float fg[4] = {0, 0, 0, 0}, fx[4] = {0, 0, 0, 0};
-            if (v < nvox) {
-                int64_t r = v;
-                const int xx = (int)(r % w);
-                r /= w;
-                const int yy = (int)(r % h);
-                r /= h;
-                const int zz = (int)(r % d);
-                const int nb = (int)(r / d);
-                const int Z = 2 * zz + (s >> 2), Y = 2 * yy + ((s >> 1) & 1), X = 2 * xx + (s & 1);
-                const size_t fv = (((size_t)nb * 2 * d + Z) * 2 * h + Y) * 2 * w + X;
-                const uint2 qg = *reinterpret_cast<const uint2*>(gr + fv * ldg + cot * 16 + part * 4);
-                const uint2 qx = *reinterpret_cast<const uint2*>(x + (size_t)v * ldx + cit * 16 + part * 4);
-                fg[0] = __uint_as_float(qg.x << 16); fg[1] = __uint_as_float(qg.x & 0xFFFF0000u);
-                fg[2] = __uint_as_float(qg.y << 16); fg[3] = __uint_as_float(qg.y & 0xFFFF0000u);
-                fx[0] = __uint_as_float(qx.x << 16); fx[1] = __uint_as_float(qx.x & 0xFFFF0000u);
-                fx[2] = __uint_as_float(qx.y << 16); fx[3] = __uint_as_float(qx.y & 0xFFFF0000u);
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                gs[vl][part * 4 + e] = fg[e];
-                xs_[vl][part * 4 + e] = fx[e];
-            }
-        }
-        __syncthreads();
-#pragma unroll 8
-        for (int k = 0; k < 64; ++k) acc = fmaf(gs[k][co_l], xs_[k][ci_l], acc);
-    }
-    float* part = partial + (size_t)split * cout * 8 * cin;
-    part[((size_t)(cot * 16 + co_l) * 8 + s) * cin + cit * 16 + ci_l] = acc;
-}
-
-// The same weight gradient on the MFMA: per (s, co tile, ci tile) block a
-// 16 x 16 GEMM with K = coarse voxels.  Both operands need 8 consecutive
-// voxels per lane, so each wave stages its 64-voxel chunk transposed in
-// LDS (g rows as [co][voxel], x rows as [ci][voxel]) and issues two MFMAs;
-// the block's four waves take interleaved chunks of its voxel share and add
-// their 16 x 16 sums in a fixed order at the end (deterministic partials, the
-// same layout as k_up2_wgrad's).
-#ifndef CTMI_UP2_WGRAD_MFMA
-#define CTMI_UP2_WGRAD_MFMA 1
-#endif
-constexpr int UPW_S = 72;   // LDS row stride (u16) of a transposed chunk
+// Weight gradient of up2 on the MFMA: dw[co][s][ci] = sum_v g[2v + s][co]
+// x[v][ci], per (s, co tile, ci tile) block a 16 x 16 GEMM with K = coarse
+// voxels.  Each wave stages its 64-voxel chunk in LDS as it lies in memory
+// ([voxel][16 channels]), the next chunk being loaded meanwhile, and reads both
+// operands transposed (as in k_conv3_wgrad).  The block's four waves take
+// interleaved chunks of its voxel share and add their sums in a fixed order at
+// the end (partial[split][co][s][ci]); the blocks past them sum g alone, for the
+// bias gradient.
 __global__ __launch_bounds__(256) void k_up2_wgrad_mfma(const u16* __restrict__ x, int ldx, int cin,
                                                         const u16* __restrict__ gr, int ldg, int cout, int n, int d,
-                                                        int h, int w, float* __restrict__ partial)
+                                                        int h, int w, float* __restrict__ partial, int nsplit,
+                                                        int nbias, float* __restrict__ bias)
 {
-    __shared__ __attribute__((aligned(16))) u16 gt[4][16 * UPW_S];
-    __shared__ __attribute__((aligned(16))) u16 xt[4][16 * UPW_S];
-    __shared__ float red[4][256];
+    __shared__ __attribute__((aligned(16))) u16 gt[4][64 * 16];
+    __shared__ __attribute__((aligned(16))) u16 xt[4][64 * 16];
+    __shared__ __attribute__((aligned(16))) float red[4][512];
     const int ci_tiles = cin / 16, co_tiles = cout / 16;
-    int b = blockIdx.x;
+    const int blocks = 8 * ci_tiles * co_tiles;
+    int b = blockIdx.x % blocks;
     const int cit = b % ci_tiles;
     b /= ci_tiles;
     const int cot = b % co_tiles;
     const int s = b / co_tiles;
-    const int split = blockIdx.y, nsplit = gridDim.y;
+    const int split = blockIdx.x / blocks;
+    if (split >= nsplit) {
+        channel_sums(gr, ldg, cout, (int64_t)n * 8 * d * h * w, blockIdx.x - blocks * nsplit, nbias, red[0], bias);
+        return;
+    }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4, li = lane & 15;
     const int64_t nvox = (int64_t)n * d * h * w;
     const int64_t nchunks = (nvox + 63) / 64;
@@ -1089,10 +1085,12 @@ __global__ __launch_bounds__(256) void k_up2_wgrad_mfma(const u16* __restrict__ 
     const int64_t rounds = (mine + 3) / 4;
     const int D2 = 2 * d, H2 = 2 * h, W2 = 2 * w;
     f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int64_t it = 0; it < rounds; ++it) {
+    const int lv = (8 * g + (li >> 2)) * 16 + (li & 3) * 4;
+    uint4 g0, g1, x0, x1;
+    auto fetch = [&](int64_t it) {
         const int64_t j = 4 * it + wave;               // this wave's chunk in the split's list
         const int64_t v = (split + j * nsplit) * 64 + lane;
-        uint4 g0 = make_uint4(0, 0, 0, 0), g1 = g0, x0 = g0, x1 = g0;
+        g0 = g1 = x0 = x1 = make_uint4(0, 0, 0, 0);
         if (j < mine && v < nvox) {
             int64_t r = v;
             const int cx = (int)(r % w);
@@ -1110,24 +1108,21 @@ __global__ __launch_bounds__(256) void k_up2_wgrad_mfma(const u16* __restrict__ 
             x0 = *reinterpret_cast<const uint4*>(xp);
             x1 = *reinterpret_cast<const uint4*>(xp + 8);
         }
+    };
+    fetch(0);
+    for (int64_t it = 0; it < rounds; ++it) {
         __syncthreads();   // every wave has read the previous chunk's fragments
-        {
-            const uint32_t gw[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
-            const uint32_t xw[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
-#pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                gt[wave][(2 * c) * UPW_S + lane] = (u16)(gw[c] & 0xFFFFu);
-                gt[wave][(2 * c + 1) * UPW_S + lane] = (u16)(gw[c] >> 16);
-                xt[wave][(2 * c) * UPW_S + lane] = (u16)(xw[c] & 0xFFFFu);
-                xt[wave][(2 * c + 1) * UPW_S + lane] = (u16)(xw[c] >> 16);
-            }
-        }
+        *reinterpret_cast<uint4*>(&gt[wave][lane * 16]) = g0;
+        *reinterpret_cast<uint4*>(&gt[wave][lane * 16 + 8]) = g1;
+        *reinterpret_cast<uint4*>(&xt[wave][lane * 16]) = x0;
+        *reinterpret_cast<uint4*>(&xt[wave][lane * 16 + 8]) = x1;
         __syncthreads();
+        if (it + 1 < rounds) fetch(it + 1);
 #pragma unroll
         for (int kk = 0; kk < 64; kk += 32) {
-            const uint4 af = *reinterpret_cast<const uint4*>(&gt[wave][li * UPW_S + kk + 8 * g]);
-            const uint4 bf = *reinterpret_cast<const uint4*>(&xt[wave][li * UPW_S + kk + 8 * g]);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(af), as_bf16x8(bf), acc, 0, 0, 0);
+            const bf16x8 af = read_tr8(&gt[wave][kk * 16 + lv]);
+            const bf16x8 bf = read_tr8(&xt[wave][kk * 16 + lv]);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bf, acc, 0, 0, 0);
         }
     }
     asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" : "+a"(acc));
@@ -1205,17 +1200,26 @@ __global__ __launch_bounds__(256) void k_head_loss_bwd(const float* __restrict__
     }
 }
 
-// out[i] = sum_s partial[s][i] in FP64 (fixed order); the first nf sums
-// also go to outf as FP32 when outf is given
-__global__ void k_sum_partials64(const double* __restrict__ partial, int nsplit, int n, double* __restrict__ out,
-                                 float* __restrict__ outf, int nf)
+// out[i] = sum_k partial[k][i] in FP64, one block per column i (lane l sums the
+// terms l mod 256 in order, then a tree: a fixed order); the first nf sums also
+// go to outf as FP32 when outf is given
+__global__ __launch_bounds__(256) void k_sum_partials64(const double* __restrict__ partial, int nsplit, int n,
+                                                        double* __restrict__ out, float* __restrict__ outf, int nf)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+    __shared__ double red[256];
+    const int i = blockIdx.x, tid = threadIdx.x;
     double s = 0.0;
-    for (int k = 0; k < nsplit; ++k) s += partial[(size_t)k * n + i];
-    out[i] = s;
-    if (outf && i < nf) outf[i] = (float)s;
+    for (int k = tid; k < nsplit; k += 256) s += partial[(size_t)k * n + i];
+    red[tid] = s;
+    __syncthreads();
+    for (int st = 128; st > 0; st >>= 1) {
+        if (tid < st) red[tid] += red[tid + st];
+        __syncthreads();
+    }
+    if (tid == 0) {
+        out[i] = red[0];
+        if (outf && i < nf) outf[i] = (float)red[0];
+    }
 }
 
 // Adam on FP32 master weights (bias-corrected step sizes from the host):
@@ -1319,32 +1323,35 @@ int unet_wgrad_splits(int n, int d, int h, int w, int cin, int cout)
     return (int)sp;
 }
 
+// Blocks of a bias gradient's channel sums over nvox voxels
+static int bias_blocks(int64_t nvox) { return (int)std::min<int64_t>(1024, std::max<int64_t>(1, nvox / 1024)); }
+
 size_t unet_wgrad_ws_bytes(int n, int d, int h, int w, int cin, int cout)
 {
-    const size_t a = (size_t)unet_wgrad_splits(n, d, h, w, cin, cout) * cout * 27 * cin * sizeof(float);
-    const size_t b = (size_t)1024 * cout * sizeof(float);  // channel-sum partials
-    return a > b ? a : b;
+    return ((size_t)unet_wgrad_splits(n, d, h, w, cin, cout) * cout * 27 * cin +
+            (size_t)bias_blocks((int64_t)n * d * h * w) * cout) *
+           sizeof(float);
+}
+
+static hipError_t launch_sum_partials(const float* partial, int nsplit, int64_t nw, const float* bias, int nbias, int nb,
+                                      float* dw, float* db, int accumulate, hipStream_t s)
+{
+    const unsigned blocks = blocks_for(nw, SUM_E) + (db ? blocks_for(nb, SUM_E) : 0);
+    k_sum_partials<<<blocks, 256, 0, s>>>(partial, nsplit, nw, bias, nbias, nb, dw, db, accumulate);
+    return hipGetLastError();
 }
 
 hipError_t launch_unet_conv3_wgrad(const UnetWgrad& a, float* dw, float* db, int accumulate, hipStream_t s)
 {
     const int cin = a.c0 + a.c1;
     const int nsplit = unet_wgrad_splits(a.n, a.d, a.h, a.w, cin, a.cout);
-    dim3 grid((cin / 16) * (a.cout / 16), nsplit);
-    k_conv3_wgrad<<<grid, 256, 0, s>>>(a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
     const int64_t nw = (int64_t)a.cout * 27 * cin;
-    k_sum_partials<<<blocks_for(nw, SUM_E), 256, 0, s>>>(a.partial, nsplit, nw, dw, accumulate);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (db) {
-        const int64_t nvox = (int64_t)a.n * a.d * a.h * a.w;
-        int nb = (int)std::min<int64_t>(1024, std::max<int64_t>(1, nvox / 1024));
-        k_channel_sums<<<nb, 256, 0, s>>>(a.dz, a.ldz, a.cout, nvox, a.partial);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        k_sum_partials<<<blocks_for(a.cout, SUM_E), 256, 0, s>>>(a.partial, nb, a.cout, db, accumulate);
-    }
-    return hipGetLastError();
+    const int nbias = db ? bias_blocks((int64_t)a.n * a.d * a.h * a.w) : 0;
+    float* bias = a.partial + nsplit * nw;
+    k_conv3_wgrad<<<(cin / 16) * (a.cout / 16) * nsplit + nbias, WG_T, 0, s>>>(a, nsplit, nbias, bias);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return launch_sum_partials(a.partial, nsplit, nw, bias, nbias, a.cout, dw, db, accumulate, s);
 }
 
 hipError_t launch_unet_pack_input(const float* x, int64_t nvox, uint16_t* out, hipStream_t s)
@@ -1418,33 +1425,23 @@ int unet_up2_wgrad_splits(int n, int d, int h, int w, int cin, int cout)
 
 size_t unet_up2_wgrad_ws_bytes(int n, int d, int h, int w, int cin, int cout)
 {
-    const size_t a = (size_t)unet_up2_wgrad_splits(n, d, h, w, cin, cout) * cout * 8 * cin * sizeof(float);
-    const size_t b = (size_t)1024 * cout * sizeof(float);
-    return a > b ? a : b;
+    return ((size_t)unet_up2_wgrad_splits(n, d, h, w, cin, cout) * cout * 8 * cin +
+            (size_t)bias_blocks((int64_t)n * 8 * d * h * w) * cout) *
+           sizeof(float);
 }
 
 hipError_t launch_unet_up2_wgrad(const uint16_t* x, int ldx, int cin, const uint16_t* g, int ldg, int cout, int n,
                                  int d, int h, int w, float* ws, float* dw, float* db, int accumulate, hipStream_t s)
 {
     const int nsplit = unet_up2_wgrad_splits(n, d, h, w, cin, cout);
-    dim3 grid(8 * (cin / 16) * (cout / 16), nsplit);
-    if (CTMI_UP2_WGRAD_MFMA)
-        k_up2_wgrad_mfma<<<grid, 256, 0, s>>>(x, ldx, cin, g, ldg, cout, n, d, h, w, ws);
-    else
-        k_up2_wgrad<<<grid, 256, 0, s>>>(x, ldx, cin, g, ldg, cout, n, d, h, w, ws);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
     const int64_t nw = (int64_t)cout * 8 * cin;
-    k_sum_partials<<<blocks_for(nw, SUM_E), 256, 0, s>>>(ws, nsplit, nw, dw, accumulate);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (db) {
-        const int64_t nvox = (int64_t)n * 8 * d * h * w;
-        int nb = (int)std::min<int64_t>(1024, std::max<int64_t>(1, nvox / 1024));
-        k_channel_sums<<<nb, 256, 0, s>>>(g, ldg, cout, nvox, ws);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        k_sum_partials<<<blocks_for(cout, SUM_E), 256, 0, s>>>(ws, nb, cout, db, accumulate);
-    }
-    return hipGetLastError();
+    const int nbias = db ? bias_blocks((int64_t)n * 8 * d * h * w) : 0;
+    float* bias = ws + nsplit * nw;
+    k_up2_wgrad_mfma<<<8 * (cin / 16) * (cout / 16) * nsplit + nbias, 256, 0, s>>>(x, ldx, cin, g, ldg, cout, n, d, h, w,
+                                                                                   ws, nsplit, nbias, bias);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return launch_sum_partials(ws, nsplit, nw, bias, nbias, cout, dw, db, accumulate, s);
 }
 
 hipError_t launch_unet_head(const float* xin, const uint16_t* act, int lda, int c, const uint16_t* hw,
@@ -1464,7 +1461,7 @@ hipError_t launch_unet_head_loss_bwd(const float* out, const float* tgt, const u
     k_head_loss_bwd<<<nb, 256, 0, s>>>(out, tgt, act, lda, hw, nvox, 1.0 / (double)nvox, dz, ldz, ws);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    k_sum_partials64<<<1, 64, 0, s>>>(ws, nb, HEAD_C + 2, sums, dhead, HEAD_C + 1);
+    k_sum_partials64<<<HEAD_C + 2, 256, 0, s>>>(ws, nb, HEAD_C + 2, sums, dhead, HEAD_C + 1);
     return hipGetLastError();
 }
 

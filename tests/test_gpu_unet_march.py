@@ -10,7 +10,7 @@ import pytest
 
 import synth
 from oracle import unet as U
-from test_gpu_unet import P, _bf, _bf16_close, _lib, _np, _p, _s  # noqa: F401 (P: fixture)
+from test_gpu_unet import P, _bf, _bf16_close, _lib, _np, _p, _rel, _s  # noqa: F401 (P: fixture)
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -93,3 +93,65 @@ def test_forward_with_and_without_the_cache(P):  # noqa: F811
     out = net.forward(x)
     kept = net.forward(x, keep=True)
     assert torch.equal(out, kept[0] if isinstance(kept, tuple) else kept)
+
+
+# one voxel; one tile; a few tiles per split with every axis cut; fewer tiles than
+# splits over many channel pairs; rows wider than their channels
+@pytest.mark.parametrize("n,d,h,w,cin,ld,cout", [
+    (1, 1, 1, 1, 16, 16, 16),
+    (1, 2, 8, 16, 16, 24, 32),
+    (2, 63, 65, 41, 16, 16, 16),
+    (4, 8, 8, 8, 64, 80, 128),
+])
+def test_conv3_wgrad_split_edges(P, n, d, h, w, cin, ld, cout):  # noqa: F811
+    L = _lib()
+    x = synth.bf16_values((n, d, h, w, cin), 21)
+    dz = synth.bf16_values((n, d, h, w, cout), 22)
+    wide = np.full((n, d, h, w, ld), 1e30, np.float32)
+    wide[..., :cin] = x
+    ws = torch.full((L.lib().ctmi_conv3d_wgrad_workspace_bytes(n, d, h, w, cin, cout) // 4,), float("nan"), device="cuda")
+    dw, db = torch.ones((cout, 27, cin), device="cuda"), torch.ones(cout, device="cuda")
+    tx, tdz = _bf(wide), _bf(dz)
+    wdw, wdb = U.conv3_wgrad(x, dz)
+    for acc in (1, 0):
+        L.check(L.lib().ctmi_conv3d_bf16_wgrad(n, d, h, w, _p(tx), cin, ld, None, 0, 8, _p(tdz), cout, cout, _p(dw),
+                                               _p(db), acc, _p(ws), ws.numel() * 4, _s()))
+        assert _rel(dw.cpu().numpy().astype(np.float64) - acc, wdw) < 1e-5
+        assert _rel(db.cpu().numpy().astype(np.float64) - acc, wdb) < 1e-5
+
+
+# one voxel; several rounds of chunks per workgroup with the last one cut; one
+# chunk of many channels
+@pytest.mark.parametrize("n,d,h,w,cin,cout", [(1, 1, 1, 1, 32, 16), (1, 32, 33, 35, 32, 16), (1, 4, 4, 4, 128, 64)])
+def test_up2_wgrad_with_bias(P, n, d, h, w, cin, cout):  # noqa: F811
+    L = _lib()
+    x = synth.bf16_values((n, d, h, w, cin), 23)
+    g = synth.bf16_values((n, 2 * d, 2 * h, 2 * w, cout), 24)
+    ws = torch.full((L.lib().ctmi_upsample2_wgrad_workspace_bytes(n, d, h, w, cin, cout) // 4,), float("nan"), device="cuda")
+    dw, db = torch.ones((cout, 8, cin), device="cuda"), torch.ones(cout, device="cuda")
+    tx, tg = _bf(x), _bf(g)
+    wdw, wdb = U.up2_wgrad(x, g)
+    for acc in (1, 0):
+        L.check(L.lib().ctmi_upsample2_wgrad(n, d, h, w, _p(tx), cin, cin, _p(tg), cout, cout, _p(dw), _p(db), acc,
+                                             _p(ws), ws.numel() * 4, _s()))
+        assert _rel(dw.cpu().numpy().astype(np.float64) - acc, wdw) < 1e-5
+        assert _rel(db.cpu().numpy().astype(np.float64) - acc, wdb) < 1e-5
+
+
+@pytest.mark.parametrize("nv", [1, 257, 140001])   # 1, 2 and 512 blocks of partial sums
+def test_head_loss_sums(P, nv):  # noqa: F811
+    L = _lib()
+    rng = np.random.Generator(np.random.PCG64(25))
+    out, tgt = rng.random(nv).astype(np.float32), rng.random(nv).astype(np.float32)
+    act, hw = synth.bf16_values((nv, 16), 26), synth.bf16_values((16,), 27, -0.5, 0.5)
+    ws = torch.empty(L.lib().ctmi_unet_head_workspace_bytes() // 8 + 2, dtype=torch.float64, device="cuda")
+    sums, dhead = torch.empty(18, dtype=torch.float64, device="cuda"), torch.empty(17, device="cuda")
+    dz = torch.empty((nv, 16), dtype=torch.bfloat16, device="cuda")
+    tout, ttgt, tact, thw = torch.from_numpy(out).cuda(), torch.from_numpy(tgt).cuda(), _bf(act), _bf(hw)
+    L.check(L.lib().ctmi_unet_head_mse_bwd(nv, _p(tout), _p(ttgt), _p(tact), 16, _p(thw), _p(dz), 16, _p(sums),
+                                           _p(dhead), _p(ws), ws.numel() * 8, _s()))
+    loss, g = U.mse_loss(out.astype(np.float64), tgt)
+    s = sums.cpu().numpy()
+    assert abs(s[17] / nv - loss) < 1e-6 * loss
+    assert _rel(s[:16], g @ act) < 1e-5 and abs(s[16] - g.sum()) < 1e-5 * np.abs(g).sum()
+    assert _rel(dhead.cpu().numpy(), s[:17]) < 1e-6
