@@ -328,6 +328,28 @@ int bitrev(int x, int bits)
     return r;
 }
 
+// Cells of one plane that a 16 x 16 pixel tile of rays at 45 degrees and the
+// slab around it cover, by the pixels' footprint at the volume's centre (largest
+// over the views): sizes the forward kernels' LDS boxes.
+float tile_area(const ctmi::VolDims& v, const ctmi::DetDims& d, const std::vector<ViewGeo>& t)
+{
+    const double C[3] = {0.5 * v.nx, 0.5 * v.ny, 0.5 * v.nz};
+    double most = 0.0;
+    for (const ViewGeo& g : t) {
+        double cr = 0.0, rr = 0.0, u2 = 0.0, v2 = 0.0;
+        for (int i = 0; i < 3; ++i) {
+            const double r = g.P00[i] + 0.5 * d.nu * g.DU[i] + 0.5 * d.nv * g.DV[i] - g.S[i];   // source to detector centre
+            cr += (C[i] - g.S[i]) * r;
+            rr += r * r;
+            u2 += (double)g.DU[i] * g.DU[i];
+            v2 += (double)g.DV[i] * g.DV[i];
+        }
+        const double m = rr > 0.0 ? std::fmin(std::fmax(cr / rr, 0.0), 1.0) : 1.0;
+        most = std::fmax(most, (22.6 * m * std::sqrt(u2) + 14.0) * (16.0 * m * std::sqrt(v2) + 4.0));
+    }
+    return (float)most;
+}
+
 // Frequency response of the zero-padded Ram-Lak kernel on the iso grid
 // tau = du DSO / DSD: H[k] = tau (h[0] + 2 sum_{n odd < nu} h[n] cos(2 pi k n / L)),
 // times 1/L for the inverse transform, stored in bit-reversed order.
@@ -468,6 +490,7 @@ static int create_plan(const ctmi_geometry* geo, const double* angles, const ctm
         view_table_general(geo, views, nviews, t.data(), t64.data());
     else
         view_table(geo, angles, nviews, t.data(), t64.data());
+    p->tile_area = tile_area(p->vol, p->det, t);
     std::vector<float> Hbr, tw;
     ramp_tables(geo, L, logL, Hbr, tw);
 

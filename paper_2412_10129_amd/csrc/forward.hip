@@ -3,7 +3,7 @@
 //
 // A workgroup of 256 threads owns a 16x16 pixel tile of one view.  The tile's
 // rays run mostly along one axis (the dominant axis of the tile's central
-// ray); the volume is cut into slabs of SLAB cells across that axis and the
+// ray); the volume is cut into slabs of a few cells across that axis and the
 // workgroup visits the slabs in the direction of travel.  For each slab it
 // stages in LDS the box of voxels the tile's rays can touch there (bounded by
 // the four corner rays of the tile, which enclose the whole ray bundle), then
@@ -20,11 +20,17 @@
 // views under one L2.
 //
 // The interpolated projector stages its boxes one slab ahead: the next
-// slab's first 2048 box elements are loaded into registers while the
-// current slab is sampled (7% faster at 512^3 x 720; the register budget is
-// held at six waves per SIMD, the LDS limit).  The Siddon walk keeps more
-// state per ray and runs slower with the extra registers, so it stages each
-// box when it needs it.
+// slab's first 4096 box elements are loaded into registers while the
+// current slab is sampled (the register budget is held at six waves per SIMD,
+// the LDS limit).  The Siddon walk keeps more state per ray, so it stages each
+// box when it needs it, at five waves per SIMD (six spill: 4163 against 4084 us
+// for 256^3 x 90 on 512^2).
+//
+// Both are bound by VALU and LDS about equally: 512^3 x 120 on 1024 x 768
+// interpolated 80.8 -> 61.2 ms (1.40 VALU instructions and 0.83 LDS steps per CU
+// and clock), 256^3 x 90 on 512^2 Siddon 5.87 -> 4.08 ms, with staging in quads,
+// pitches without bank conflicts, slabs fitted to each tile and LDS addresses formed
+// in FP32.
 #include "ctmi_internal.h"
 
 namespace ctmi {
@@ -37,34 +43,59 @@ namespace {
 #ifndef CTMI_FWD_TV
 #define CTMI_FWD_TV 16
 #endif
-#ifndef CTMI_FWD_SLAB
-#define CTMI_FWD_SLAB 10
-#endif
-#ifndef CTMI_FWD_BOXCAP
-#define CTMI_FWD_BOXCAP 6144
-#endif
-// interpolated forward: box elements per thread fetched ahead into
-// registers, and the waves per SIMD the register budget is sized for
+// interpolated forward: groups of four box elements per thread fetched ahead
+// into registers, and the waves per SIMD the register budget is sized for
 #ifndef CTMI_FWD_PF
-#define CTMI_FWD_PF 8
+#define CTMI_FWD_PF 4
 #endif
 #ifndef CTMI_FWD_WAVES
 #define CTMI_FWD_WAVES 6
 #endif
 // Siddon forward: waves per SIMD the register budget is sized for
 #ifndef CTMI_FWD_SID_WAVES
-#define CTMI_FWD_SID_WAVES 6
+#define CTMI_FWD_SID_WAVES 5
 #endif
 constexpr int TU = CTMI_FWD_TU, TV = CTMI_FWD_TV;   // ray tile (pixels), TU * TV = 256
-#ifndef CTMI_FWD_SID_SLAB
-#define CTMI_FWD_SID_SLAB 12
+#ifndef CTMI_FWD_SID_PF
+#define CTMI_FWD_SID_PF 4
 #endif
-constexpr int SLAB = CTMI_FWD_SLAB;                 // slab thickness along the dominant axis (interpolated)
-constexpr int SID_SLAB = CTMI_FWD_SID_SLAB;         // the same for the Siddon layer walk
-constexpr int BOXCAP = CTMI_FWD_BOXCAP;             // LDS floats for the staged box
+// Slab thickness along the dominant axis: the thickest of these of which every
+// slab's box fits the LDS capacity (a clipped box sends its slab's samples through
+// the checked path), the last if none does.  Thin slabs pay more for their
+// barriers, setup and, in the interpolated projector, three planes of overlap, but
+// boxes of rays at 45 degrees and of pixels of a voxel or more are wide: 24 views of
+// 256 x 256 x 128 on 256 x 200 pixels of a voxel, one thickness (10; Siddon 12)
+// 1532 us, Siddon 785, so 993 and 490.  Along x the planes are the box's rows: 4 n +
+// 1 and the overlap make rows of 4 n + 4 words.
+#ifndef CTMI_FWD_THICK
+#define CTMI_FWD_THICK {16, 13, 10, 8, 6, 4, 4}
+#endif
+#ifndef CTMI_FWD_THICK_X
+#define CTMI_FWD_THICK_X {17, 13, 9, 9, 5, 5, 5}
+#endif
+#ifndef CTMI_FWD_SID_THICK
+#define CTMI_FWD_SID_THICK {24, 20, 16, 12, 8, 4, 8}
+#endif
+constexpr int NTHICK = 7;
+__device__ __forceinline__ int interp_thickness(int a, int c)
+{
+    constexpr int t[NTHICK] = CTMI_FWD_THICK, tx[NTHICK] = CTMI_FWD_THICK_X;
+    int r = 0;
+#pragma unroll
+    for (int i = 0; i < NTHICK; ++i) r = i == c ? (a == 0 ? tx[i] : t[i]) : r;
+    return r;
+}
+__device__ __forceinline__ int siddon_thickness(int c)
+{
+    constexpr int t[NTHICK] = CTMI_FWD_SID_THICK;
+    int r = 0;
+#pragma unroll
+    for (int i = 0; i < NTHICK; ++i) r = i == c ? t[i] : r;
+    return r;
+}
 constexpr int SLABTAB = 64;                         // slab boxes formed up front per block
+constexpr int BOXCAP_MAX = 15360;                   // most LDS floats for the staged box
 static_assert(TU * TV == 256, "one ray per thread");
-static_assert(BOXCAP < 65536, "box index must stay below 2^16");
 
 struct TileMap {
     int tiles_u, tiles_v;
@@ -72,11 +103,29 @@ struct TileMap {
 };
 
 // Staged box: voxel index origin and extent per axis (x, y, z); LDS layout
-// [z][y][x] with x fastest (coalesced global loads).
+// [z][y][x] with x fastest (coalesced global loads), the x extent a multiple of 4.
 struct Box {
     int o[3];
     int e[3];
+    int w, wz;   // pitch of rows and planes in LDS
 };
+
+// Pitches of a box of e0 x e1 cells per plane.  A read takes 32 lanes (two
+// detector rows of 16 rays) a clock from 32 banks.  Where the dominant axis is y or
+// z, rays side by side read along x, so the two rows' banks are disjoint if the
+// planes lie 16 banks apart; rows and planes stay on 16 bytes, and the box is
+// written four words at a time.  Along x, rays side by side read rows side by side
+// (and cells of two columns): even pitches of 2 mod 4 with odd planes.  A model of
+// the tile's reads gives 1.33 and 1.36 clocks per 32 lanes for these, 1.72 for
+// unpadded planes and 1.86, 2.3 and 3 for row pitches of 13, 12 and 16 along x;
+// interpolated A, 512^3 x 120: 89 ms at
+// 12 words and unpadded planes, 195 at 16, 68.4 at 13, 61.2 so.
+__device__ __forceinline__ int row_pad(int a) { return a == 0 ? 2 : 0; }
+__device__ __forceinline__ int plane_pitch(int a, int w, int e1)
+{
+    const int n = w * e1;
+    return a == 0 ? n | 1 : ((n + 15) & ~31) + 16;
+}
 
 #ifndef CTMI_FWD_XCD
 #define CTMI_FWD_XCD 1
@@ -169,103 +218,184 @@ __device__ __forceinline__ void bundle_bounds(const ViewGeo& g, const DetDims& d
 }
 
 // Box covering index range [lo_i, hi_i] per axis, clipped to [clo_i, chi_i]
-// and to the LDS capacity (the non-dominant axes shrink first).  Returns
-// false if empty.
-__device__ __forceinline__ bool make_box(const int lo[3], const int hi[3], const int clo[3], const int chi[3], int a,
+// and to the LDS capacity (the non-dominant axes shrink first).  Returns 0 if
+// it is empty, BOX_SOME, or BOX_SOME | BOX_CLIPPED where the capacity cut it.
+constexpr int BOX_SOME = 1, BOX_CLIPPED = 2;
+__device__ __forceinline__ int make_box(const int lo[3], const int hi[3], const int clo[3], const int chi[3], int a, int cap,
                                          Box& b)
 {
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
         const int l = max(lo[i], clo[i]), h = min(hi[i], chi[i]);
-        if (h < l) return false;
+        if (h < l) return 0;
         b.o[i] = l;
         b.e[i] = h - l + 1;
     }
+    b.e[0] = (b.e[0] + 3) & ~3;
     // capacity: shrink the larger non-dominant extent until the box fits
-    // (every index below is a compile-time constant, so the box stays in
-    // registers)
-    for (int it = 0; it < 4 && b.e[0] * b.e[1] * b.e[2] > BOXCAP; ++it) {
+    const int pad = row_pad(a);
+    auto size = [&]() { return plane_pitch(a, b.e[0] + pad, b.e[1]) * b.e[2]; };
+    const bool clipped = size() > cap;
+    for (int it = 0; it < 4 && size() > cap; ++it) {
         const int e1 = a == 0 ? b.e[1] : b.e[0];      // first non-dominant extent
         const int e2 = a == 2 ? b.e[1] : b.e[2];      // second non-dominant extent
         const bool first = e1 >= e2;
-        const int keep = first ? e2 : e1;             // the other non-dominant extent
-        const int ea = a == 0 ? b.e[0] : (a == 1 ? b.e[1] : b.e[2]);
-        const int ne = max(1, BOXCAP / (keep * ea));
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            const bool is1 = i == (a == 0 ? 1 : 0), is2 = i == (a == 2 ? 1 : 2);
-            if ((first && is1) || (!first && is2)) b.e[i] = ne;
-        }
+        const int cut = first ? (a == 0 ? 1 : 0) : (a == 2 ? 1 : 2);
+        const int room = max(cap / b.e[2] - 31, 0);   // for a plane without its padding
+        if (cut == 0)
+            b.e[0] = max((room / b.e[1] - pad) & ~3, 4);
+        else if (cut == 1)
+            b.e[1] = max(room / (b.e[0] + pad), 1);
+        else
+            b.e[2] = max(cap / plane_pitch(a, b.e[0] + pad, b.e[1]), 1);
     }
-    return b.e[0] * b.e[1] * b.e[2] <= BOXCAP;
+    if (size() > cap) {   // (at most the thickest slab's planes of one row: always fits)
+        b.e[0] = a == 0 ? b.e[0] : 4;
+        b.e[1] = a == 1 ? b.e[1] : 1;
+        b.e[2] = a == 2 ? b.e[2] : 1;
+    }
+    b.w = b.e[0] + pad;
+    b.wz = plane_pitch(a, b.w, b.e[1]);
+    return clipped ? BOX_SOME | BOX_CLIPPED : BOX_SOME;
 }
 
-// Box staging by rows.  A row is the box's x extent W = e[0] at one (y, z);
-// thread t takes column t mod W of rows t div W + m RG (pass m), RG =
-// floor(256 / W) whole rows per pass, so consecutive threads load
-// consecutive x (coalesced global reads, consecutive LDS words) and a
-// thread's column and its x bounds check stay fixed.  From one pass to the
-// next a thread's row advances by RG = RGz e[1] + RGy, so its (y, z) and its
-// global index advance by constants, with one carry from y into z.  Initial
-// quotients use float reciprocals: floor((i + 1/2) r), r = fl(1/e), equals
-// i div e for every i < 2^22, because (i + 1/2)/e is at least 1/(2e) away
-// from an integer while the FP32 error is below (i + 1/2) 2^-23 / e.  The
-// global index is kept modulo 2^32 (a cell inside the volume has an index
-// below 2^31, checked at plan creation).  A box wider than 256 along x (not
-// produced by tile-sized bundles) is staged element by element.
-struct Stage {
-    int ly, lz;        // this thread's current row as box (y, z); lz >= e[2] once past the last row
-    unsigned gi;       // global index of the current element (mod 2^32)
-    int li;            // its LDS index
-    int rgy, rgz;      // pass advance
-    unsigned d1, d2;   // global index advance, and the extra on a carry into z
-    int lstep;         // LDS index advance
-    bool xok;          // this thread holds a column, inside the volume along x
+// Box staging by rows, four consecutive x at a time.  A row is the box's x
+// extent at one (y, z), W = e[0] / 4 quads; thread t takes quad t mod W of rows
+// t div W + m RG (pass m), RG = floor(256 / W) whole rows per pass, so a thread's
+// column and its x bounds check stay fixed.  From one pass to the next a
+// thread's row advances by RG = RGz e[1] + RGy, so its (y, z), its global index
+// and its LDS index advance by constants, with one carry from y into z.  (Element by
+// element, and with the quotients formed by every thread for every slab, staging
+// took 360 of the interpolated projector's 1160 VALU instructions per slab and
+// wave; global loads of four words need only their word's alignment.)  Initial
+// quotients use float reciprocals: floor((i + 1/2) r), r = fl(1/e), equals i div
+// e for every i < 2^22, because (i + 1/2)/e is at least 1/(2e) away from an
+// integer while the FP32 error is below (i + 1/2) 2^-23 / e.  The global index is
+// kept modulo 2^32 (a cell inside the volume has an index below 2^31, checked at
+// plan creation).  A box wider than 1024 along x (not produced by tile-sized
+// bundles) is staged element by element.
+typedef float quad __attribute__((ext_vector_type(4), aligned(4)));
+typedef float pair __attribute__((ext_vector_type(2), aligned(4)));
+typedef float quad16 __attribute__((ext_vector_type(4)));
+
+// What staging a slab's box needs, the same for the whole block: one row of the
+// block's slab table.
+struct Slab {
+    Box b;
+    int flags;
+    float r0, r1;        // 1 / W, 1 / e[1]
+    int rg, rgy, rgz;    // rows per pass (0: box wider than 1024) and the pass advance
 };
 
-__device__ __forceinline__ Stage stage_of(const Box& b, const VolDims& v)
+__device__ __forceinline__ Slab slab_of_box(const Box& b, int flags)
 {
-    Stage s;
-    const float r0 = 1.0f / (float)b.e[0], r1 = 1.0f / (float)b.e[1];
-    const int rg = (int)__builtin_floorf(256.5f * r0);
-    const int t = (int)threadIdx.x;
-    const int tr = (int)__builtin_floorf(((float)t + 0.5f) * r0);
-    const int tx = t - tr * b.e[0];
-    s.lz = (int)__builtin_floorf(((float)tr + 0.5f) * r1);
-    s.ly = tr - s.lz * b.e[1];
-    if (tr >= rg) s.lz = b.e[2];   // no column for this thread
-    s.rgz = (int)__builtin_floorf(((float)rg + 0.5f) * r1);
-    s.rgy = rg - s.rgz * b.e[1];
-    const unsigned nx = (unsigned)v.nx, nxy = (unsigned)v.nx * (unsigned)v.ny;
-    const int gx = b.o[0] + tx;
-    s.xok = (unsigned)gx < nx;
-    s.gi = (unsigned)(b.o[2] + s.lz) * nxy + (unsigned)(b.o[1] + s.ly) * nx + (unsigned)gx;
-    s.d1 = (unsigned)s.rgz * nxy + (unsigned)s.rgy * nx;
-    s.d2 = nxy - (unsigned)b.e[1] * nx;
-    s.li = tr * b.e[0] + tx;
-    s.lstep = rg * b.e[0];
+    Slab s;
+    s.b = b;
+    s.flags = flags;
+    const int w = b.e[0] >> 2;
+    s.r0 = 1.0f / (float)w;
+    s.r1 = 1.0f / (float)b.e[1];
+    s.rg = w <= 256 ? (int)__builtin_floorf(256.5f * s.r0) : 0;
+    s.rgz = (int)__builtin_floorf(((float)s.rg + 0.5f) * s.r1);
+    s.rgy = s.rg - s.rgz * b.e[1];
     return s;
 }
 
-// value of the current element (0 outside the volume), then advance a pass
-template <bool CHECK>
-__device__ __forceinline__ float stage_next(Stage& s, const float* __restrict__ vol, const VolDims& v, const Box& b)
+// A table row is eight words: origin, e0 | e1 << 16, e2 | flags << 16, the two
+// reciprocals (the pitches follow from the extents), rg | rgz << 9 | rgy << 18 (rg and rgz at most 256, rgy below e1 <= the capacity)
+static_assert(BOXCAP_MAX < 1 << 14, "rgy in 14 bits");
+__device__ __forceinline__ void put_slab(int4* row, const Slab& s)
 {
-    float val = 0.0f;
-    // (CHECK false: the caller knows the box lies inside the volume)
-    if (!CHECK || (s.xok && (unsigned)(b.o[1] + s.ly) < (unsigned)v.ny && (unsigned)(b.o[2] + s.lz) < (unsigned)v.nz))
-        val = vol[s.gi];
-    s.ly += s.rgy;
-    const bool c = s.ly >= b.e[1];
-    s.ly -= c ? b.e[1] : 0;
-    s.lz += s.rgz + (c ? 1 : 0);
-    s.gi += s.d1 + (c ? s.d2 : 0u);
-    s.li += s.lstep;
-    return val;
+    row[0] = make_int4(s.b.o[0], s.b.o[1], s.b.o[2], s.b.e[0] | s.b.e[1] << 16);
+    row[1] = make_int4(s.b.e[2] | s.flags << 16, __float_as_int(s.r0), __float_as_int(s.r1),
+                       s.rg | s.rgz << 9 | (int)((unsigned)s.rgy << 18));
 }
 
-// element i of a box wider than 256 along x
-__device__ __forceinline__ float element_value(const float* __restrict__ vol, const VolDims& v, const Box& b, int i)
+__device__ __forceinline__ Slab get_slab(const int4* row, int a)
+{
+    const int4 p = row[0], q = row[1];
+    Slab s;
+    s.b.o[0] = __builtin_amdgcn_readfirstlane(p.x);
+    s.b.o[1] = __builtin_amdgcn_readfirstlane(p.y);
+    s.b.o[2] = __builtin_amdgcn_readfirstlane(p.z);
+    const int e01 = __builtin_amdgcn_readfirstlane(p.w), e2f = __builtin_amdgcn_readfirstlane(q.x);
+    const int adv = __builtin_amdgcn_readfirstlane(q.w);
+    s.b.e[0] = e01 & 0xffff;
+    s.b.e[1] = (int)((unsigned)e01 >> 16);
+    s.b.e[2] = e2f & 0xffff;
+    s.flags = (int)((unsigned)e2f >> 16);
+    s.b.w = s.b.e[0] + row_pad(a);
+    s.b.wz = plane_pitch(a, s.b.w, s.b.e[1]);
+    s.r0 = __int_as_float(q.y);
+    s.r1 = __int_as_float(q.z);
+    s.rg = adv & 511;
+    s.rgz = (adv >> 9) & 511;
+    s.rgy = (int)((unsigned)adv >> 18);
+    return s;
+}
+
+struct Stage {
+    int gx;            // this thread's volume x
+    int ly, lz;        // its current row as box (y, z); lz past the box when the thread is done (or holds no column)
+    unsigned gi;       // global index of its current quad (mod 2^32)
+    int li;            // its LDS index
+};
+
+// this thread's position at pass m0
+__device__ __forceinline__ Stage stage_of(const Slab& sl, const VolDims& v, int m0)
+{
+    Stage s;
+    const Box& b = sl.b;
+    const int w = b.e[0] >> 2, t = (int)threadIdx.x;
+    const int tr = (int)__builtin_floorf(((float)t + 0.5f) * sl.r0);
+    const int row = tr + m0 * sl.rg;
+    s.lz = (int)__builtin_floorf(((float)row + 0.5f) * sl.r1);
+    s.ly = row - (int)__umul24(s.lz, b.e[1]);
+    const int tx = 4 * (t - (int)__umul24(tr, w));
+    s.gx = b.o[0] + tx;
+    const unsigned nx = (unsigned)v.nx, nxy = (unsigned)v.nx * (unsigned)v.ny;
+    s.gi = ((unsigned)b.o[2] * nxy + (unsigned)b.o[1] * nx) + ((unsigned)s.lz * nxy + (unsigned)s.ly * nx) + (unsigned)s.gx;
+    s.li = (int)__umul24(s.lz, b.wz) + (int)__umul24(s.ly, b.w) + tx;
+    if (t >= sl.rg * w) s.lz = 1 << 20;
+    return s;
+}
+
+__device__ __forceinline__ void stage_step(Stage& s, const Slab& sl, const VolDims& v)
+{
+    const unsigned nx = (unsigned)v.nx, nxy = (unsigned)v.nx * (unsigned)v.ny;
+    const unsigned d1 = (unsigned)sl.rgz * nxy + (unsigned)sl.rgy * nx;   // and on a carry into z:
+    const unsigned d2 = d1 + nxy - (unsigned)sl.b.e[1] * nx;
+    const int l1 = sl.rgz * sl.b.wz + sl.rgy * sl.b.w, l2 = l1 + sl.b.wz - sl.b.e[1] * sl.b.w;
+    s.ly += sl.rgy;
+    const bool c = s.ly >= sl.b.e[1];
+    s.ly -= c ? sl.b.e[1] : 0;
+    s.lz += sl.rgz + (c ? 1 : 0);
+    s.gi += c ? d2 : d1;
+    s.li += c ? l2 : l1;
+}
+
+// values of the current quad (0 outside the volume)
+template <bool CHECK>
+__device__ __forceinline__ quad stage_value(const Stage& s, const Slab& sl, const float* __restrict__ vol, const VolDims& v)
+{
+    // (CHECK false: the caller knows the box lies inside the volume)
+    if (!CHECK) return *reinterpret_cast<const quad*>(vol + s.gi);
+    quad r = {0.0f, 0.0f, 0.0f, 0.0f};
+    if ((unsigned)(sl.b.o[1] + s.ly) < (unsigned)v.ny && (unsigned)(sl.b.o[2] + s.lz) < (unsigned)v.nz) {
+        if (s.gx >= 0 && s.gx + 3 < v.nx) {
+            r = *reinterpret_cast<const quad*>(vol + s.gi);
+        } else {
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if ((unsigned)(s.gx + c) < (unsigned)v.nx) r[c] = vol[s.gi + (unsigned)c];
+        }
+    }
+    return r;
+}
+
+// element i of a box wider than 1024 along x
+__device__ __forceinline__ float element_value(const float* __restrict__ vol, const VolDims& v, const Box& b, int i,
+                                               int& li)
 {
     const float r0 = 1.0f / (float)b.e[0], r1 = 1.0f / (float)b.e[1];
     const int q = (int)__builtin_floorf(((float)i + 0.5f) * r0);
@@ -273,26 +403,11 @@ __device__ __forceinline__ float element_value(const float* __restrict__ vol, co
     const int lz = (int)__builtin_floorf(((float)q + 0.5f) * r1);
     const int ly = q - (int)__umul24(lz, b.e[1]);
     const int gx = b.o[0] + lx, gy = b.o[1] + ly, gz = b.o[2] + lz;
+    li = lz * b.wz + ly * b.w + lx;
     float val = 0.0f;
     if ((unsigned)gx < (unsigned)v.nx && (unsigned)gy < (unsigned)v.ny && (unsigned)gz < (unsigned)v.nz)
         val = vol[(__umul24((unsigned)gz, (unsigned)v.ny) + (unsigned)gy) * (unsigned)v.nx + (unsigned)gx];
     return val;
-}
-
-template <bool CHECK = true>
-__device__ __forceinline__ void load_box(float* box, const float* __restrict__ vol, const VolDims& v, const Box& b)
-{
-    if (b.e[0] > 256) {
-        const int n = b.e[0] * b.e[1] * b.e[2];
-        for (int i = threadIdx.x; i < n; i += blockDim.x) box[i] = element_value(vol, v, b, i);
-        return;
-    }
-    Stage s = stage_of(b, v);
-    if (!CHECK) s.xok = true;
-    while (s.lz < b.e[2]) {
-        const int li = s.li;
-        box[li] = stage_next<CHECK>(s, vol, v, b);
-    }
 }
 
 // the box lies inside the volume (no staged cell needs a bounds check)
@@ -302,68 +417,81 @@ __device__ __forceinline__ bool box_inside(const Box& b, const VolDims& v)
            b.o[2] + b.e[2] <= v.nz;
 }
 
-// Software-pipelined staging: the first PF passes of the next slab's box
-// are loaded into registers while the current slab is sampled, then written
-// to LDS; any further passes are read directly when the box is written.
+// The first PF passes of a box go through registers: the loads are issued
+// together (by the interpolated projector a slab ahead, while the current slab
+// is sampled), then written to LDS; any further passes are loaded when the box
+// is written.
 template <int PF>
-__device__ __forceinline__ void fetch_box(float (&r)[PF], const float* __restrict__ vol, const VolDims& v,
-                                          const Box& b, bool on)
+struct Fetched {
+    quad v[PF];
+    int li[PF];   // LDS index, negative where there is nothing to write
+};
+
+template <int PF, bool CHECK>
+__device__ __forceinline__ void fetch_passes(Fetched<PF>& r, Stage s, const Slab& sl, const float* __restrict__ vol,
+                                             const VolDims& v)
 {
-    if (on && b.e[0] <= 256) {
-        Stage s = stage_of(b, v);
-        if (box_inside(b, v)) {
 #pragma unroll
-            for (int m = 0; m < PF; ++m) {
-                const bool row = s.lz < b.e[2];
-                const float val = row ? stage_next<false>(s, vol, v, b) : 0.0f;
-                r[m] = val;
-            }
-        } else {
-#pragma unroll
-            for (int m = 0; m < PF; ++m) {
-                const bool row = s.lz < b.e[2];
-                const float val = stage_next<true>(s, vol, v, b);
-                r[m] = row ? val : 0.0f;
-            }
+    for (int m = 0; m < PF; ++m) {
+        r.v[m] = quad{0.0f, 0.0f, 0.0f, 0.0f};
+        r.li[m] = -1;
+        if (s.lz < sl.b.e[2]) {
+            r.v[m] = stage_value<CHECK>(s, sl, vol, v);
+            r.li[m] = s.li;
         }
-    } else {
-#pragma unroll
-        for (int m = 0; m < PF; ++m) r[m] = 0.0f;
+        if (m + 1 < PF) stage_step(s, sl, v);
     }
 }
 
 template <int PF>
-__device__ __forceinline__ void put_box(float* box, const float (&r)[PF], const float* __restrict__ vol,
-                                        const VolDims& v, const Box& b, bool on)
+__device__ __forceinline__ void fetch_box(Fetched<PF>& r, const float* __restrict__ vol, const VolDims& v, const Slab& sl)
 {
-    if (!on) return;
-    if (b.e[0] > 256) {
-        load_box(box, vol, v, b);
+    if (!sl.rg) return;
+    const Stage s = stage_of(sl, v, 0);
+    if (box_inside(sl.b, v))
+        fetch_passes<PF, false>(r, s, sl, vol, v);
+    else
+        fetch_passes<PF, true>(r, s, sl, vol, v);
+}
+
+template <int PF>
+__device__ __forceinline__ void put_box(float* box, const Fetched<PF>& r, const float* __restrict__ vol, const VolDims& v,
+                                        const Slab& sl, int a)
+{
+    if (!sl.rg) {
+        const int n = sl.b.e[0] * sl.b.e[1] * sl.b.e[2];
+        for (int i = threadIdx.x; i < n; i += blockDim.x) {
+            int li;
+            const float val = element_value(vol, v, sl.b, i, li);
+            box[li] = val;
+        }
         return;
     }
-    Stage s = stage_of(b, v);
+    if (a == 0) {
 #pragma unroll
-    for (int m = 0; m < PF; ++m) {
-        if (s.lz < b.e[2]) box[s.li] = r[m];
-        s.ly += s.rgy;
-        const bool c = s.ly >= b.e[1];
-        s.ly -= c ? b.e[1] : 0;
-        s.lz += s.rgz + (c ? 1 : 0);
-        s.gi += s.d1 + (c ? s.d2 : 0u);
-        s.li += s.lstep;
-    }
-    if (box_inside(b, v)) {
-        while (s.lz < b.e[2]) {
-            const int li = s.li;
-            box[li] = stage_next<false>(s, vol, v, b);
-        }
+        for (int m = 0; m < PF; ++m)
+            if (r.li[m] >= 0) *reinterpret_cast<quad*>(box + r.li[m]) = r.v[m];
     } else {
-        while (s.lz < b.e[2]) {
-            const int li = s.li;
-            box[li] = stage_next<true>(s, vol, v, b);
-        }
+#pragma unroll
+        for (int m = 0; m < PF; ++m)
+            if (r.li[m] >= 0) *reinterpret_cast<quad16*>(box + r.li[m]) = r.v[m];
+    }
+    if (PF * sl.rg < sl.b.e[1] * sl.b.e[2]) {
+        const bool in = box_inside(sl.b, v);
+        for (Stage s = stage_of(sl, v, PF); s.lz < sl.b.e[2]; stage_step(s, sl, v))
+            *reinterpret_cast<quad*>(box + s.li) = in ? stage_value<false>(s, sl, vol, v) : stage_value<true>(s, sl, vol, v);
     }
 }
+
+// LDS addresses kept in FP32: the float n 2^-149 (a denormal, at full rate here)
+// has the integer n as its bits, so an address formed by exact fused multiply-adds
+// on such floats is read without a conversion.
+typedef const __attribute__((address_space(3))) float lds_float;
+__device__ __forceinline__ unsigned lds_address(const float* p)
+{
+    return (unsigned)(uintptr_t)(__attribute__((address_space(3))) const char*)p;
+}
+__device__ __forceinline__ lds_float* lds_at(unsigned address) { return (lds_float*)(uintptr_t)address; }
 
 // ------------------------------------------------------------------ Siddon
 // The Siddon sum is taken one layer at a time along the tile's dominant
@@ -388,7 +516,7 @@ __device__ __forceinline__ float sid_cell(const float* box, const float* __restr
 {
     const int lx = x - bx.o[0], ly = y - bx.o[1], lz = z - bx.o[2];
     if ((unsigned)lx < (unsigned)bx.e[0] && (unsigned)ly < (unsigned)bx.e[1] && (unsigned)lz < (unsigned)bx.e[2])
-        return box[(lz * bx.e[1] + ly) * bx.e[0] + lx];
+        return box[lz * bx.wz + ly * bx.w + lx];
     if ((unsigned)x < (unsigned)v.nx && (unsigned)y < (unsigned)v.ny && (unsigned)z < (unsigned)v.nz)
         return vol[(__umul24((unsigned)z, (unsigned)v.ny) + (unsigned)y) * (unsigned)v.nx + (unsigned)x];
     return 0.0f;
@@ -445,10 +573,11 @@ __device__ __forceinline__ void walk_layer(LayerRay& r, float ae, int k, int a, 
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CTMI_FWD_SID_WAVES, 8))) k_forward_siddon(const float* __restrict__ vol, float* __restrict__ proj,
                                                         const ViewGeo* __restrict__ tab,
                                                         const ViewGeo64* __restrict__ tab64, int view0, TileMap m,
-                                                        VolDims v, DetDims det)
+                                                        VolDims v, DetDims det, int cap)
 {
-    __shared__ float box[BOXCAP];
-    __shared__ int sbox[SLABTAB][7];   // the first SLABTAB slabs' boxes (origin, extent, non-empty)
+    extern __shared__ __attribute__((aligned(16))) float box[];   // cap floats
+    __shared__ int4 sbox[SLABTAB][2];   // the first SLABTAB slabs
+    __shared__ int thick;               // planes per slab
     int view, tu0, tv0;
     tile_of_block(m, blockIdx.x, view, tu0, tv0);
     const int iu = tu0 + (int)(threadIdx.x % TU), iv = tv0 + (int)(threadIdx.x / TU);
@@ -512,15 +641,15 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CTMI_F
     khi = __builtin_amdgcn_readfirstlane(khi);
     const bool wave_steep = __any(steep);
 
-    const int nslab = (na + SID_SLAB - 1) / SID_SLAB;
+    int slab = 0, nslab = 0;
     const int clo[3] = {0, 0, 0}, chi[3] = {v.nx - 1, v.ny - 1, v.nz - 1};
     // the staged box of slab si (in the direction of travel): the cells
     // under the bundle, no margin (a ray whose walk rounds into a cell
     // outside, a corner ray within ulps of a plane, finds out below and
     // reads that slab plane by plane)
-    auto slab_box = [&](int si, Box& bx) -> bool {
+    auto slab_box = [&](int si) -> Slab {
         const int s = dir > 0 ? si : nslab - 1 - si;
-        const int c0 = s * SID_SLAB, c1 = min(c0 + SID_SLAB, na);   // cells [c0, c1) along a
+        const int c0 = s * slab, c1 = min(c0 + slab, na);   // cells [c0, c1) along a
         float blo[3], bhi[3];
         bundle_bounds(g, det, tu0, tv0, a, (float)c0, (float)c1, 0.0f, blo, bhi);
         int lo[3], hi[3];
@@ -534,54 +663,59 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CTMI_F
             lo[i] = i == a ? c0 : lo[i];
             hi[i] = i == a ? c1 - 1 : hi[i];
         }
-        return make_box(lo, hi, clo, chi, a, bx);
-    };
-    // the first SLABTAB boxes are formed once, one slab per thread, instead
-    // of by every wave at every slab
-    if ((int)threadIdx.x < min(nslab, SLABTAB)) {
         Box bx;
-        const bool ok = slab_box((int)threadIdx.x, bx);
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            sbox[threadIdx.x][i] = bx.o[i];
-            sbox[threadIdx.x][3 + i] = bx.e[i];
+        const int f = make_box(lo, hi, clo, chi, a, cap, bx);
+        if (!f) return slab_of_box(Box{{0, 0, 0}, {4, 1, 1}, 4, 4}, 0);
+        // (a row rounded up past the volume starts earlier instead)
+        bx.o[0] = max(min(bx.o[0], v.nx - bx.e[0]), 0);
+        return slab_of_box(bx, f);
+    };
+    // the first wave picks the slab thickness and forms the boxes, one per lane
+    // (not every wave at every slab)
+    if (threadIdx.x < 64) {
+        Slab mine;
+        for (int c = 0; c < NTHICK; ++c) {
+            slab = siddon_thickness(c);
+            nslab = (na + slab - 1) / slab;
+            mine = slab_box((int)threadIdx.x);
+            bool cut = (int)threadIdx.x < nslab && (mine.flags & BOX_CLIPPED);
+            for (int si = (int)threadIdx.x + 64; si < nslab; si += 64) cut |= (slab_box(si).flags & BOX_CLIPPED) != 0;
+            if (!__any(cut)) break;
         }
-        sbox[threadIdx.x][6] = ok ? 1 : 0;
+        if ((int)threadIdx.x < min(nslab, SLABTAB)) put_slab(sbox[threadIdx.x], mine);
+        if (threadIdx.x == 0) thick = slab;
     }
     __syncthreads();
+    slab = __builtin_amdgcn_readfirstlane(thick);
+    nslab = (na + slab - 1) / slab;
 
     for (int si = 0; si < nslab; ++si) {
         const int s = dir > 0 ? si : nslab - 1 - si;
-        const int c0 = s * SID_SLAB, c1 = min(c0 + SID_SLAB, na);   // cells [c0, c1) along a
-        Box bx;
-        bool ok;
+        const int c0 = s * slab, c1 = min(c0 + slab, na);   // cells [c0, c1) along a
+        Slab sl;
         if (si < SLABTAB) {
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                bx.o[i] = sbox[si][i];
-                bx.e[i] = sbox[si][3 + i];
-            }
-            ok = sbox[si][6] != 0;
+            sl = get_slab(sbox[si], a);
         } else {
-            ok = slab_box(si, bx);
+            int4 row[2];
+            put_slab(row, slab_box(si));
+            sl = get_slab(row, a);   // (the same in every lane: scalar registers)
         }
-        if (!ok) continue;
-        // the box is the same in every lane: scalar registers
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            bx.o[i] = __builtin_amdgcn_readfirstlane(bx.o[i]);
-            bx.e[i] = __builtin_amdgcn_readfirstlane(bx.e[i]);
-        }
+        if (!sl.flags) continue;
+        const Box& bx = sl.b;
         __syncthreads();
-        load_box<false>(box, vol, v, bx);   // (clipped to the volume by make_box)
+        {
+            Fetched<CTMI_FWD_SID_PF> q;
+            fetch_box<CTMI_FWD_SID_PF>(q, vol, v, sl);
+            put_box<CTMI_FWD_SID_PF>(box, q, vol, v, sl, a);
+        }
         __syncthreads();
         const int k0 = max(c0, klo), k1 = min(c1 - 1, khi);
         if (k0 > k1) continue;   // no ray of this wave reaches these layers
 
         // box strides (elements) and origins of the three axes
-        const int st_a = pick3(a, 1, bx.e[0], bx.e[0] * bx.e[1]);
-        const int st_b = pick3(b, 1, bx.e[0], bx.e[0] * bx.e[1]);
-        const int st_c = pick3(c, 1, bx.e[0], bx.e[0] * bx.e[1]);
+        const int st_a = pick3(a, 1, bx.w, bx.wz);
+        const int st_b = pick3(b, 1, bx.w, bx.wz);
+        const int st_c = pick3(c, 1, bx.w, bx.wz);
         const int oa = pick3(a, bx.o[0], bx.o[1], bx.o[2]);
         const int ob = pick3(b, bx.o[0], bx.o[1], bx.o[2]), eb = pick3(b, bx.e[0], bx.e[1], bx.e[2]);
         const int oc = pick3(c, bx.o[0], bx.o[1], bx.o[2]), ec = pick3(c, bx.e[0], bx.e[1], bx.e[2]);
@@ -603,36 +737,42 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CTMI_F
                 roff = inbox ? 4 * ((ib - ob) * st_b + (ic - oc) * st_c) : 0;
             }
         }
-        const int DB = 4 * B.step * st_b, DC = 4 * C.step * st_c;
-        const char* boxb = (const char*)box;
-        for (int kk = 0; kk <= k1 - k0; ++kk) {
-            const int k = dir > 0 ? k0 + kk : k1 - kk;
-            const float aa = __builtin_fmaf((float)(k + (dir > 0)), A.inv, A.c);   // exit plane of layer k
-            const float ae = __builtin_amdgcn_fmed3f(aa, r.acur, r.aend);
-            const int loff = 4 * (k - oa) * st_a;
-            if (idle) {
-            } else if (inbox && !wave_steep) {
-                const bool cb = r.anb < ae, cc = r.anc < ae, bfirst = r.anb <= r.anc;
-                const float t1 = __builtin_amdgcn_fmed3f(bfirst ? r.anb : r.anc, r.acur, ae);
-                const float t2 = __builtin_amdgcn_fmed3f(bfirst ? r.anc : r.anb, r.acur, ae);
-                const int db = cb ? DB : 0, dc = cc ? DC : 0;
-                const int o0 = roff + loff;
-                const float v0 = *(const float*)(boxb + o0);
-                const float v1 = *(const float*)(boxb + o0 + (bfirst ? db : dc));
-                const float v2 = *(const float*)(boxb + o0 + db + dc);
+        const int n = idle ? 0 : k1 - k0 + 1, kf = dir > 0 ? k0 : k1;   // layers, and the first in the direction of travel
+        if (inbox && !wave_steep) {
+            // The three-cell form, 27 VALU per layer.  o is the LDS address of the
+            // ray's cell in FP32 (lds_at); plane numbers and steps are exact too.
+            const float DB = __int_as_float(4 * st_b), DC = __int_as_float(4 * st_c);
+            const float DA = dir > 0 ? __int_as_float(4 * st_a) : -__int_as_float(4 * st_a);
+            const float fdir = (float)dir, sb = (float)B.step, sc = (float)C.step;
+            float o = __int_as_float((int)lds_address(box) + roff + 4 * (kf - oa) * st_a);
+            float q = (float)(kf + (dir > 0));
+#pragma unroll 4
+            for (int i = 0; i < n; ++i) {
+                const float ae = __builtin_amdgcn_fmed3f(__builtin_fmaf(q, A.inv, A.c), r.acur, r.aend);   // exit plane
+                const bool bfirst = r.anb <= r.anc;
+                const float t1 = fminf(fminf(r.anb, r.anc), ae), t2 = fminf(fmaxf(r.anb, r.anc), ae);
+                const float fb = r.anb < ae ? sb : 0.0f, fc = r.anc < ae ? sc : 0.0f;
+                const float ob1 = __builtin_fmaf(fb, DB, o), oc1 = __builtin_fmaf(fc, DC, o);
+                const float o2 = __builtin_fmaf(fc, DC, ob1);
+                const float v0 = *lds_at(__float_as_uint(o));
+                const float v1 = *lds_at(__float_as_uint(bfirst ? ob1 : oc1));
+                const float v2 = *lds_at(__float_as_uint(o2));
                 r.acc = __builtin_fmaf(t1 - r.acur, v0, r.acc);
                 r.acc = __builtin_fmaf(t2 - t1, v1, r.acc);
                 r.acc = __builtin_fmaf(ae - t2, v2, r.acc);
                 r.acur = ae;
-                roff += db + dc;
-                r.qb = cb ? r.qb + (float)B.step : r.qb;
-                r.qc = cc ? r.qc + (float)C.step : r.qc;
+                o = o2 + DA;
+                q += fdir;
+                r.qb += fb;
+                r.qc += fc;
                 r.anb = __builtin_fmaf(r.qb, B.inv, B.c);
                 r.anc = __builtin_fmaf(r.qc, C.inv, C.c);
-            } else {
-                walk_layer(r, ae, k, a, B, C, box, vol, v, bx);
-                const int ib = (int)r.qb - (B.step > 0), ic = (int)r.qc - (C.step > 0);
-                roff = 4 * ((ib - ob) * st_b + (ic - oc) * st_c);
+            }
+        } else {
+            for (int i = 0; i < n; ++i) {
+                const int k = kf + i * dir;
+                const float aa = __builtin_fmaf((float)(k + (dir > 0)), A.inv, A.c);   // exit plane of layer k
+                walk_layer(r, __builtin_amdgcn_fmed3f(aa, r.acur, r.aend), k, a, B, C, box, vol, v, bx);
             }
         }
     }
@@ -686,6 +826,13 @@ __device__ __forceinline__ float trilinear_global(const float* __restrict__ vol,
     const int ix = (int)fx, iy = (int)fy, iz = (int)fz;
     const float ax = p[0] - fx, ay = p[1] - fy, az = p[2] - fz;
     float r[8];
+    if ((unsigned)ix < (unsigned)(v.nx - 1) && (unsigned)iy < (unsigned)(v.ny - 1) && (unsigned)iz < (unsigned)(v.nz - 1)) {
+        const float* q = vol + (((int64_t)iz * v.ny + iy) * v.nx + ix);
+        const int64_t nxy = (int64_t)v.nx * v.ny;
+        const pair p0 = *reinterpret_cast<const pair*>(q), p1 = *reinterpret_cast<const pair*>(q + v.nx);
+        const pair p2 = *reinterpret_cast<const pair*>(q + nxy), p3 = *reinterpret_cast<const pair*>(q + nxy + v.nx);
+        r[0] = p0.x, r[1] = p0.y, r[2] = p1.x, r[3] = p1.y, r[4] = p2.x, r[5] = p2.y, r[6] = p3.x, r[7] = p3.y;
+    } else
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
         const int jx = ix + (c & 1), jy = iy + ((c >> 1) & 1), jz = iz + (c >> 2);
@@ -708,11 +855,12 @@ struct Bundle {
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CTMI_FWD_WAVES, 8))) k_forward_interp(const float* __restrict__ vol, float* __restrict__ proj,
                                                         const ViewGeo* __restrict__ tab,
                                                         const ViewGeo64* __restrict__ tab64, int view0, TileMap m,
-                                                        VolDims v, DetDims det, float ds)
+                                                        VolDims v, DetDims det, float ds, int cap)
 {
-    __shared__ float box[BOXCAP];
+    extern __shared__ __attribute__((aligned(16))) float box[];   // cap floats
     __shared__ Bundle bun;
-    __shared__ int sbox[SLABTAB][7];   // the first SLABTAB slabs' boxes (origin, extent, fits | clipped << 1)
+    __shared__ int4 sbox[SLABTAB][2];   // the first SLABTAB slabs
+    __shared__ int thick;               // planes per slab
     int view, tu0, tv0;
     tile_of_block(m, blockIdx.x, view, tu0, tv0);
     const int iu = tu0 + (int)(threadIdx.x % TU), iv = tv0 + (int)(threadIdx.x / TU);
@@ -755,20 +903,19 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CTMI_F
     // a sample's lower corner A = floor(pos_a) lies in [-2, n] (the sample
     // range reaches one step beyond the interpolant's support, and FP32
     // positions may round across its edge); slab s takes the samples before
-    // the plane s SLAB + SLAB - 1 (direction +) or from the plane s SLAB - 1
-    // on (direction -), and stages planes [s SLAB - 2, s SLAB + SLAB] so a
+    // the plane s slab + slab - 1 (direction +) or from the plane s slab - 1
+    // on (direction -), and stages planes [s slab - 2, s slab + slab] so a
     // sample assigned one step early or late by rounding still finds its
     // corners in the box.  Boxes may reach one plane of zeros beyond each
     // halo plane, so every corner of such a sample is staged.
-    const int nslab = (na + SLAB) / SLAB;
+    int slab = 0, nslab = 0;
     const int clo[3] = {-2, -2, -2}, chi[3] = {v.nx + 1, v.ny + 1, v.nz + 1};
 
     // slab si's plane range [A0, A1], its staged box and whether the box
     // holds the whole bundle range (uniform over the block)
-    auto slab_box = [&](int si, int& A0, int& A1, Box& b, bool& fits, bool& clipped) {
+    auto slab_box = [&](int si) -> Slab {
         const int s = dir > 0 ? si : nslab - 1 - si;
-        A0 = s * SLAB - 1;
-        A1 = A0 + SLAB;
+        const int A0 = s * slab - 1, A1 = A0 + slab;
         // bundle bounds over the staged plane range [A0 - 1, A1 + 1]
         float blo[3] = {CTMI_INF, CTMI_INF, CTMI_INF}, bhi[3] = {-CTMI_INF, -CTMI_INF, -CTMI_INF};
 #pragma unroll
@@ -791,58 +938,45 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CTMI_F
             lo[i] = i == a ? A0 - 1 : lo[i];
             hi[i] = i == a ? A1 + 1 : hi[i];
         }
-        fits = make_box(lo, hi, clo, chi, a, b);
-        clipped = false;
-        if (fits) {
-#pragma unroll
-            for (int i = 0; i < 3; ++i) clipped |= b.o[i] > max(lo[i], clo[i]) || b.o[i] + b.e[i] - 1 < min(hi[i], chi[i]);
-        }
+        Box b;
+        const int f = make_box(lo, hi, clo, chi, a, cap, b);
+        return f ? slab_of_box(b, f) : slab_of_box(Box{{0, 0, 0}, {4, 1, 1}, 4, 4}, 0);
     };
-    // the first SLABTAB boxes are formed once, one slab per thread, instead
-    // of by every wave at every slab
-    if ((int)threadIdx.x < min(nslab, SLABTAB)) {
-        int A0, A1;
-        Box bx;
-        bool fits, clipped;
-        slab_box((int)threadIdx.x, A0, A1, bx, fits, clipped);
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            sbox[threadIdx.x][i] = bx.o[i];
-            sbox[threadIdx.x][3 + i] = bx.e[i];
+    // the first wave picks the slab thickness and forms the boxes, one per lane
+    // (not every wave at every slab)
+    if (threadIdx.x < 64) {
+        Slab mine;
+        for (int c = 0; c < NTHICK; ++c) {
+            slab = interp_thickness(a, c);
+            nslab = (na + slab) / slab;
+            mine = slab_box((int)threadIdx.x);
+            bool cut = (int)threadIdx.x < nslab && (mine.flags & BOX_CLIPPED);
+            for (int si = (int)threadIdx.x + 64; si < nslab; si += 64) cut |= (slab_box(si).flags & BOX_CLIPPED) != 0;
+            if (!__any(cut)) break;
         }
-        sbox[threadIdx.x][6] = (fits ? 1 : 0) | (clipped ? 2 : 0);
+        if ((int)threadIdx.x < min(nslab, SLABTAB)) put_slab(sbox[threadIdx.x], mine);
+        if (threadIdx.x == 0) thick = slab;
     }
     __syncthreads();
-    auto slab_of = [&](int si, int& A0, int& A1, Box& b, bool& fits, bool& clipped) {
-        if (si < SLABTAB) {
-            const int s = dir > 0 ? si : nslab - 1 - si;
-            A0 = s * SLAB - 1;
-            A1 = A0 + SLAB;
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                b.o[i] = __builtin_amdgcn_readfirstlane(sbox[si][i]);
-                b.e[i] = __builtin_amdgcn_readfirstlane(sbox[si][3 + i]);
-            }
-            const int f = __builtin_amdgcn_readfirstlane(sbox[si][6]);
-            fits = (f & 1) != 0;
-            clipped = (f & 2) != 0;
-        } else {
-            slab_box(si, A0, A1, b, fits, clipped);
-        }
+    slab = __builtin_amdgcn_readfirstlane(thick);
+    nslab = (na + slab) / slab;
+    auto slab_of = [&](int si) -> Slab {
+        if (si < SLABTAB) return get_slab(sbox[si], a);
+        int4 row[2];
+        put_slab(row, slab_box(si));
+        return get_slab(row, a);   // (the same in every lane: scalar registers)
     };
     // the next slab's box is fetched into registers while this one is sampled
     constexpr int PF = CTMI_FWD_PF;
-    float pf[PF];
-    int nA0, nA1;
-    Box nb;
-    bool nfits, nclipped;
-    slab_of(0, nA0, nA1, nb, nfits, nclipped);
-    fetch_box<PF>(pf, vol, v, nb, nfits);
+    Fetched<PF> pf;
+    Slab next = slab_of(0);
+    if (next.flags & BOX_SOME) fetch_box<PF>(pf, vol, v, next);
 
     for (int si = 0; si < nslab; ++si) {
-        const int A0 = nA0, A1 = nA1;
-        const Box b = nb;
-        const bool fits = nfits, clipped = nclipped;
+        const Slab sl = next;
+        const Box& b = sl.b;
+        const bool fits = (sl.flags & BOX_SOME) != 0, clipped = (sl.flags & BOX_CLIPPED) != 0;
+        const int A0 = (dir > 0 ? si : nslab - 1 - si) * slab - 1, A1 = A0 + slab;
         // this thread's last sample in the slab
         int kl;
         {
@@ -852,20 +986,21 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CTMI_F
             kl = (si == nslab - 1 || !mono) ? k1 : min(kl, k1);
         }
         __syncthreads();
-        put_box<PF>(box, pf, vol, v, b, fits);
+        if (fits) put_box<PF>(box, pf, vol, v, sl, a);
         __syncthreads();
         if (si + 1 < nslab) {
-            slab_of(si + 1, nA0, nA1, nb, nfits, nclipped);
-            fetch_box<PF>(pf, vol, v, nb, nfits);
+            next = slab_of(si + 1);
+            if (next.flags & BOX_SOME) fetch_box<PF>(pf, vol, v, next);
         }
-        if (fits && !clipped && mono) {
-            // fast path: every sample of the slab has its 2x2x2 corners in the
-            // box; the byte offset is formed in FP32 from box-relative
-            // coordinates, every intermediate an integer below 2^24
-            const float SY = (float)(4 * b.e[0]), SZ = (float)(4 * b.e[0] * b.e[1]);
-            const float ox = (float)b.o[0], oyf = (float)b.o[1], ozf = (float)b.o[2];
-            const int oy = 4 * b.e[0], oz = 4 * b.e[0] * b.e[1];
-            const char* base = reinterpret_cast<const char*>(box);
+        // byte offsets over the whole grid and its margins stay exact FP32 integers
+        const bool exact = (int64_t)b.wz * (v.nz + 4) + (int64_t)b.w * (v.ny + 4) + v.nx + 4 < 1 << 22;
+        if (fits && !clipped && mono && exact) {
+            // fast path: every sample of the slab has its 2x2x2 corners in the box.
+            // The LDS address is formed in FP32 as a multiple of 2^-149 (see
+            // lds_read): the box's origin is the first product's addend.
+            const float SX = __int_as_float(4), SY = __int_as_float(4 * b.w), SZ = __int_as_float(4 * b.wz);
+            const float C0 = (float)((int)lds_address(box) - 4 * (b.o[0] + b.w * b.o[1] + b.wz * b.o[2])) * 0x1p-149f;
+            const unsigned o01 = 4 * (unsigned)b.w, o10 = 4 * (unsigned)b.wz, o11 = o10 + o01;
             // samples k..kl by their offset j = k - kc from the ray's anchor, an
             // exact FP32 integer (interp_pos's position, without an int->float
             // conversion per sample).  Only a ray with samples here enters: its
@@ -877,11 +1012,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CTMI_F
 #pragma unroll
                 for (int i = 0; i < 3; ++i) p[i] = __builtin_fmaf(j, r.st[i], r.base[i]);
                 const float fx = __builtin_floorf(p[0]), fy = __builtin_floorf(p[1]), fz = __builtin_floorf(p[2]);
-                const int off = (int)__builtin_fmaf(fz - ozf, SZ, __builtin_fmaf(fy - oyf, SY, (fx - ox) * 4.0f));
-                const float* r0 = reinterpret_cast<const float*>(base + off);
-                const float* r1 = reinterpret_cast<const float*>(base + off + oy);
-                const float* r2 = reinterpret_cast<const float*>(base + off + oz);
-                const float* r3 = reinterpret_cast<const float*>(base + off + oz + oy);
+                const unsigned off =
+                    __float_as_uint(__builtin_fmaf(fz, SZ, __builtin_fmaf(fy, SY, __builtin_fmaf(fx, SX, C0))));
+                const lds_float *r0 = lds_at(off), *r1 = lds_at(off + o01), *r2 = lds_at(off + o10), *r3 = lds_at(off + o11);
                 const float ax = p[0] - fx, ay = p[1] - fy, az = p[2] - fz;
                 const float c00 = lerp1(ax, r0[0], r0[1]), c01 = lerp1(ax, r1[0], r1[1]);
                 const float c10 = lerp1(ax, r2[0], r2[1]), c11 = lerp1(ax, r3[0], r3[1]);
@@ -896,8 +1029,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CTMI_F
                 const int lx = (int)fx - b.o[0], ly = (int)fy - b.o[1], lz = (int)fz - b.o[2];
                 if (fits && (unsigned)lx < (unsigned)(b.e[0] - 1) && (unsigned)ly < (unsigned)(b.e[1] - 1) &&
                     (unsigned)lz < (unsigned)(b.e[2] - 1)) {
-                    const float* q = box + (lz * b.e[1] + ly) * b.e[0] + lx;
-                    const int sy = b.e[0], sz = b.e[0] * b.e[1];
+                    const float* q = box + lz * b.wz + ly * b.w + lx;
+                    const int sy = b.w, sz = b.wz;
                     const float ax = p[0] - fx, ay = p[1] - fy, az = p[2] - fz;
                     const float c00 = lerp1(ax, q[0], q[1]), c01 = lerp1(ax, q[sy], q[sy + 1]);
                     const float c10 = lerp1(ax, q[sz], q[sz + 1]), c11 = lerp1(ax, q[sz + sy], q[sz + sy + 1]);
@@ -927,13 +1060,29 @@ TileMap tile_map(const Plan& p, int64_t nviews)
 
 }  // namespace
 
+// LDS floats for a workgroup's box: six, five, four or two workgroups per CU (the
+// Siddon walk's registers allow five).  A wider box costs wavefronts in flight, a
+// narrower one thin slabs, and clipped boxes where pixels span several voxels.
+// The lines lie where neighbours measured equal on cubes of 256 voxels, 24 views, by
+// voxels per pixel (interpolated, us at 6144 / 7424 / 9472 / 15360 floats: 0.75:
+// 1617 1670 1777 2894; 0.98: 1287 1220 1298 1972; 1.17: 1640 1377 1207 1628; 1.69: 3083
+// 2500 1824 1637; Siddon 0.65: 1211 1185 1276 2124; 1.43: 809 668 649 835; 2.6 (128
+// planes): 473 487 475 662; 3.9 (24 x 256 x 48): 125 123 127 106).
+static int box_capacity(const Plan& p, bool siddon)
+{
+    if (p.tile_area <= (siddon ? 790.0f : 540.0f)) return siddon ? 7424 : 6144;
+    if (p.tile_area <= 790.0f) return 7424;
+    return p.tile_area <= (siddon ? 5000.0f : 1450.0f) ? 9472 : BOXCAP_MAX;
+}
+
 hipError_t launch_forward_siddon(const Plan& p, const float* vol, float* proj, int64_t view0, int64_t nviews,
                                  hipStream_t s)
 {
     const TileMap m = tile_map(p, nviews);
     const int64_t blocks = (int64_t)m.tiles_u * m.tiles_v * nviews;
-    hipLaunchKernelGGL(k_forward_siddon, dim3((unsigned)blocks), dim3(256), 0, s, vol, proj, p.d_views, p.d_views64,
-                       (int)view0, m, p.vol, p.det);
+    const int cap = box_capacity(p, true);
+    hipLaunchKernelGGL(k_forward_siddon, dim3((unsigned)blocks), dim3(256), cap * sizeof(float), s, vol, proj, p.d_views, p.d_views64,
+                       (int)view0, m, p.vol, p.det, cap);
     return hipGetLastError();
 }
 
@@ -942,8 +1091,9 @@ hipError_t launch_forward_interp(const Plan& p, const float* vol, float* proj, i
 {
     const TileMap m = tile_map(p, nviews);
     const int64_t blocks = (int64_t)m.tiles_u * m.tiles_v * nviews;
-    hipLaunchKernelGGL(k_forward_interp, dim3((unsigned)blocks), dim3(256), 0, s, vol, proj, p.d_views, p.d_views64,
-                       (int)view0, m, p.vol, p.det, p.ds);
+    const int cap = box_capacity(p, false);
+    hipLaunchKernelGGL(k_forward_interp, dim3((unsigned)blocks), dim3(256), cap * sizeof(float), s, vol, proj, p.d_views, p.d_views64,
+                       (int)view0, m, p.vol, p.det, p.ds, cap);
     return hipGetLastError();
 }
 
