@@ -9,232 +9,227 @@ namespace ctmi {
 namespace {
 
 // ------------------------------------------------------------ backprojector
-// One thread per (x, y) voxel column segment of ZC voxels; every view of the
-// call is accumulated in registers, so each output voxel is written once.
-// On a circular orbit W and fu do not depend on z, so per view a thread
-// computes one reciprocal and then walks its ZC voxels along v.
+// A workgroup owns 16 x 16 voxel columns of ZC voxels, one column per thread;
+// every view of the call is accumulated in registers, so each output voxel is
+// written once.  On a circular orbit W and fu do not depend on z, so per view a
+// thread computes one reciprocal and then walks its ZC voxels along v.
 //
-// Views are taken FDK_VB at a time: the detector footprint of the
-// workgroup's voxel block in each view (bounding box of its 8 projected
-// corners, one pixel of margin below and two above, clamped to the
-// detector) is staged in LDS with coalesced row reads, and the bilinear
-// taps read LDS.  A footprint larger than FDK_CAP pixels (or a block corner
-// not in front of the source) reads its view from global memory instead.
-// The values read are the same either way, so the result does not depend on
-// the path.
-#ifndef CTMI_FDK_TX
-#define CTMI_FDK_TX 32
-#endif
-#ifndef CTMI_FDK_ZC
-#define CTMI_FDK_ZC 16
-#endif
-constexpr int FDK_TX = CTMI_FDK_TX, FDK_TY = 256 / FDK_TX, FDK_ZC = CTMI_FDK_ZC;
-#ifndef CTMI_FDK_VB
-#define CTMI_FDK_VB 2
-#endif
-#ifndef CTMI_FDK_CAP
-#define CTMI_FDK_CAP 2560
-#endif
-#ifndef CTMI_FDK_P
-#define CTMI_FDK_P 64
-#endif
-constexpr int FDK_VB = CTMI_FDK_VB, FDK_CAP = CTMI_FDK_CAP;
-// Row pitch of a staged footprint up to FDK_P pixels wide: a compile-time
-// pitch puts a voxel's four taps at one address plus immediate offsets
-// (two paired LDS reads).
-constexpr int FDK_P = CTMI_FDK_P;
-static_assert(FDK_P + 1 <= 255, "paired-read offsets are 8-bit dword counts");
-#ifndef CTMI_FDK_XCD
-#define CTMI_FDK_XCD 0
-#endif
+// The detector footprint of the block in a view (bounding box of its 8
+// projected corners with a pixel of margin below and two above) is staged in LDS,
+// zero outside the detector, so that the taps need neither clamps nor zero
+// weights: rows of four pixels per thread, the next view's loaded into
+// registers while this one is summed, one barrier per view.  A footprint wider
+// than the row pitch (or 64 pixels) or higher than FDK_H rows, or a block with a
+// corner not in front of the source, reads its view from global memory instead.
+//
+// A read takes 32 lanes (8 x 4 columns: a wave is 8 x 8 columns) from 32 banks; row
+// pitches of 16 modulo 32 keep neighbours that share a column but not a row apart
+// (a model of the reads gives 1.02 clocks per 32 lanes; 16 x 2 columns 1.3, 32 x 1
+// 1.85; a pitch of 68 with 16 x 2 columns measured 19.6 ms against 18.2).  The narrow
+// pitch leaves LDS for eight workgroups per CU.  The tap's LDS address is formed in
+// FP32 as a multiple of 2^-149 (a denormal has its integer as bits): one fused
+// multiply-add per voxel.
+//
+// LDS reads bound it (77 % of the LDS cycles, 1.2 VALU instructions per CU and
+// clock): 512^3, 360 views on 1024 x 768 33.9 -> 17.7 ms against blocks of 32 x 8
+// columns staged pixel by pixel between barriers, with clamped taps at the edges.
+// ZC 8: 20.5 ms, 32: 17.5 (with five waves per SIMD; small volumes want the smaller).
+constexpr int FDK_T = 16;                       // voxel columns per side
+constexpr int FDK_H = 48;                       // most staged rows
+constexpr int FDK_M = FDK_H / 16;               // staging passes of 16 rows
+constexpr int FDK_NARROW = 48, FDK_WIDE = 80;   // LDS row pitches
+constexpr int FDK_TAB = 16;                     // views whose footprints are formed together
 
+typedef float fdk_quad __attribute__((ext_vector_type(4), aligned(4)));
+typedef float fdk_quad16 __attribute__((ext_vector_type(4)));
+
+// How a block reads a view
+enum { FDK_GLOBAL = 0, FDK_NONE = 1, FDK_EDGE = 2, FDK_INSIDE = 3 };
 struct FdkBox {
-    int u0, v0, w, h;   // staged pixels [u0, u0 + w) x [v0, v0 + h); w = 0: not staged
-    int pitch;          // LDS row pitch (floats): FDK_P when w <= FDK_P and it fits, else w
-    float rw;           // 1 / w
-    int inner;          // pitch FDK_P and no margin clipped by the detector (below)
+    int u0, v0;     // first staged pixel
+    int w, h;       // staged pixels and rows
+    int how;        // nothing to add (off the detector), staged with or without bounds checks, or not staged
 };
 
-#ifndef CTMI_FDK_WAVES
-#define CTMI_FDK_WAVES 6
-#endif
-__global__ void __launch_bounds__(FDK_TX* FDK_TY) __attribute__((amdgpu_waves_per_eu(CTMI_FDK_WAVES, 8))) k_backward_fdk(const float* __restrict__ proj,
-                                                                 float* __restrict__ vol,
-                                                                 const ViewGeo* __restrict__ tab, int view0,
-                                                                 int nviews, VolDims v, DetDims det, int nbx,
-                                                                 int nby, float beta)
+__device__ __forceinline__ FdkBox fdk_box(const ViewGeo& g, const float lo[3], const float hi[3], const DetDims& det,
+                                          int width)
 {
-    __shared__ float box[FDK_VB][FDK_CAP];
-    __shared__ FdkBox fb[FDK_VB];
-    const int b = CTMI_FDK_XCD ? (int)xcd_contiguous(blockIdx.x, gridDim.x) : (int)blockIdx.x;
-    const int bx = b % nbx, by = (b / nbx) % nby, bz = b / (nbx * nby);
-    const int ix = bx * FDK_TX + (int)(threadIdx.x % FDK_TX);
-    const int iy = by * FDK_TY + (int)(threadIdx.x / FDK_TX);
-    const int iz0 = bz * FDK_ZC;
-    const bool live = ix < v.nx && iy < v.ny;   // every thread takes part in staging
-    // the block's voxel centres (clamped to the volume)
-    const float lo[3] = {(float)(bx * FDK_TX), (float)(by * FDK_TY), (float)iz0};
-    const float hi[3] = {(float)(min((bx + 1) * FDK_TX, v.nx) - 1), (float)(min((by + 1) * FDK_TY, v.ny) - 1),
-                         (float)(min(iz0 + FDK_ZC, v.nz) - 1)};
-    const float fx = (float)ix, fy = (float)iy, fz0 = (float)iz0;
-    float acc[FDK_ZC];
+    float umin = CTMI_INF, umax = -CTMI_INF, vmin = CTMI_INF, vmax = -CTMI_INF, wmin = CTMI_INF;
 #pragma unroll
-    for (int z = 0; z < FDK_ZC; ++z) acc[z] = 0.0f;
+    for (int q = 0; q < 8; ++q) {
+        const float cx = (q & 1) ? hi[0] : lo[0], cy = (q & 2) ? hi[1] : lo[1], cz = (q & 4) ? hi[2] : lo[2];
+        const float W = __builtin_fmaf(g.MW[0], cx, __builtin_fmaf(g.MW[1], cy, __builtin_fmaf(g.MW[2], cz, g.MW[3])));
+        const float U = __builtin_fmaf(g.MU[0], cx, __builtin_fmaf(g.MU[1], cy, __builtin_fmaf(g.MU[2], cz, g.MU[3])));
+        const float V = __builtin_fmaf(g.MV[0], cx, __builtin_fmaf(g.MV[1], cy, __builtin_fmaf(g.MV[2], cz, g.MV[3])));
+        const float rw = 1.0f / W;
+        wmin = fminf(wmin, W);
+        umin = fminf(umin, U * rw);
+        umax = fmaxf(umax, U * rw);
+        vmin = fminf(vmin, V * rw);
+        vmax = fmaxf(vmax, V * rw);
+    }
+    FdkBox f = {0, 0, 0, 0, FDK_GLOBAL};
+    // (rows below 60000: the taps' offsets stay exact FP32 integers)
+    if (!(wmin > 0.0f) || det.nv >= 60000 || det.nu >= 1 << 22) return f;
+    // no tap of a voxel of the block is on the detector (two pixels to spare)
+    if (umax < -3.0f || vmax < -3.0f || umin > (float)det.nu + 2.0f || vmin > (float)det.nv + 2.0f) {
+        f.how = FDK_NONE;
+        return f;
+    }
+    // a voxel of the block projects inside the corners' bounding box, so its
+    // taps floor(u), floor(u) + 1 lie in [floor(umin) - 1, floor(umax) + 2] (a pixel
+    // to spare for rounding), and the same for v
+    if (umax - umin > (float)width || vmax - vmin > (float)FDK_H) return f;
+    f.u0 = (int)__builtin_floorf(umin) - 1;
+    f.v0 = (int)__builtin_floorf(vmin) - 1;
+    f.w = (int)__builtin_floorf(umax) + 3 - f.u0;
+    f.h = (int)__builtin_floorf(vmax) + 3 - f.v0;
+    if (f.w > width || f.h > FDK_H) return f;
+    // (loads come in whole quads and passes of 16 rows)
+    const bool inside = f.u0 >= 0 && f.v0 >= 0 && f.u0 + ((f.w + 3) & ~3) <= det.nu && f.v0 + ((f.h + 15) & ~15) <= det.nv;
+    f.how = inside ? FDK_INSIDE : FDK_EDGE;
+    return f;
+}
 
-    for (int k0 = 0; k0 < nviews; k0 += FDK_VB) {
-        const int nb = min(FDK_VB, nviews - k0);
-        __syncthreads();   // the previous chunk's reads of box and fb are done
-        if ((int)threadIdx.x < nb) {
-            const ViewGeo& g = tab[view0 + k0 + threadIdx.x];
-            float umin = CTMI_INF, umax = -CTMI_INF, vmin = CTMI_INF, vmax = -CTMI_INF, wmin = CTMI_INF;
+template <int ZC, int P>
+__global__ void __launch_bounds__(FDK_T* FDK_T) __attribute__((amdgpu_waves_per_eu(P == FDK_NARROW ? 7 : 5, 8)))
+k_backward_fdk(const float* __restrict__ proj, float* __restrict__ vol, const ViewGeo* __restrict__ tab, int view0,
+               int nviews, VolDims v, DetDims det, int nbx, int nby, float beta)
+{
+    __shared__ __attribute__((aligned(16))) float box[2][FDK_H * P];
+    __shared__ FdkBox fb[2 * FDK_TAB];   // ring: views k and on, a half formed at a time
+    constexpr int W_MAX = P < 64 ? P : 64;   // 16 threads stage a row
+    const int b = (int)blockIdx.x;
+    const int bx = b % nbx, by = (b / nbx) % nby, bz = b / (nbx * nby);
+    const int tid = (int)threadIdx.x;
+    const int ix = bx * FDK_T + (tid & 7) + (tid >> 3 & 8);   // a wave: 8 x 8 columns
+    const int iy = by * FDK_T + (tid >> 3 & 7) + (tid >> 4 & 8);
+    const int iz0 = bz * ZC;
+    const bool live = ix < v.nx && iy < v.ny;   // every thread takes part in staging
+    // the block's voxel centres (of live columns, all ZC voxels)
+    const float lo[3] = {(float)(bx * FDK_T), (float)(by * FDK_T), (float)iz0};
+    const float hi[3] = {(float)(min((bx + 1) * FDK_T, v.nx) - 1), (float)(min((by + 1) * FDK_T, v.ny) - 1),
+                         (float)(iz0 + ZC - 1)};
+    const float fx = (float)ix, fy = (float)iy, fz0 = (float)iz0;
+    float acc[ZC];
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const float cx = (q & 1) ? hi[0] : lo[0], cy = (q & 2) ? hi[1] : lo[1], cz = (q & 4) ? hi[2] : lo[2];
-                const float W = __builtin_fmaf(g.MW[0], cx, __builtin_fmaf(g.MW[1], cy, __builtin_fmaf(g.MW[2], cz, g.MW[3])));
-                const float U = __builtin_fmaf(g.MU[0], cx, __builtin_fmaf(g.MU[1], cy, __builtin_fmaf(g.MU[2], cz, g.MU[3])));
-                const float V = __builtin_fmaf(g.MV[0], cx, __builtin_fmaf(g.MV[1], cy, __builtin_fmaf(g.MV[2], cz, g.MV[3])));
-                const float rw = 1.0f / W;
-                wmin = fminf(wmin, W);
-                umin = fminf(umin, U * rw);
-                umax = fmaxf(umax, U * rw);
-                vmin = fminf(vmin, V * rw);
-                vmax = fmaxf(vmax, V * rw);
-            }
-            FdkBox f;
-            f.w = 0;
-            f.u0 = f.v0 = f.h = 0;
-            f.pitch = 0;
-            f.rw = 1.0f;
-            f.inner = 0;
-            // clamp in float first: corners may project far off the detector
-            umin = fminf(fmaxf(umin, -4.0f), (float)det.nu + 4.0f);
-            umax = fminf(fmaxf(umax, -4.0f), (float)det.nu + 4.0f);
-            vmin = fminf(fmaxf(vmin, -4.0f), (float)det.nv + 4.0f);
-            vmax = fminf(fmaxf(vmax, -4.0f), (float)det.nv + 4.0f);
-            const int u0 = max((int)__builtin_floorf(umin) - 1, 0), u1 = min((int)__builtin_floorf(umax) + 2, det.nu - 1);
-            const int v0 = max((int)__builtin_floorf(vmin) - 1, 0), v1 = min((int)__builtin_floorf(vmax) + 2, det.nv - 1);
-            // a voxel of the block projects inside the corners' bounding
-            // box (all in front of the source; on a circular orbit u does
-            // not depend on z), so its taps floor(u), floor(u) + 1 lie in
-            // [floor(umin) - 1, floor(umax) + 2], and the same for v, with a
-            // pixel to spare for rounding: when no end was clipped, every tap
-            // is on the detector and in the box.  (A block cut by the
-            // volume's last z plane still runs its threads past it, outside
-            // [lo, hi]: it keeps the clamped taps.)
-            const bool inner = (int)__builtin_floorf(vmin) - 1 >= 0 && (int)__builtin_floorf(vmax) + 2 <= det.nv - 1 &&
-                               (int)__builtin_floorf(umin) - 1 >= 0 && (int)__builtin_floorf(umax) + 2 <= det.nu - 1 &&
-                               iz0 + FDK_ZC <= v.nz;
-            // (each side is checked first, so the product cannot overflow)
-            if (wmin > 0.0f && u0 <= u1 && v0 <= v1 && u1 - u0 < FDK_CAP && v1 - v0 < FDK_CAP) {
-                const int w = u1 - u0 + 1, h = v1 - v0 + 1;
-                const int pitch = w <= FDK_P && h * FDK_P <= FDK_CAP ? FDK_P : w;
-                if (h * pitch <= FDK_CAP) {
-                    f.u0 = u0;
-                    f.v0 = v0;
-                    f.w = w;
-                    f.h = h;
-                    f.pitch = pitch;
-                    f.rw = 1.0f / (float)w;
-                    f.inner = inner && pitch == FDK_P ? 1 : 0;
+    for (int z = 0; z < ZC; ++z) acc[z] = 0.0f;
+
+    auto get = [&](int k) {
+        const FdkBox& m = fb[k & (2 * FDK_TAB - 1)];
+        FdkBox f;
+        f.u0 = __builtin_amdgcn_readfirstlane(m.u0);
+        f.v0 = __builtin_amdgcn_readfirstlane(m.v0);
+        f.w = __builtin_amdgcn_readfirstlane(m.w);
+        f.h = __builtin_amdgcn_readfirstlane(m.h);
+        f.how = __builtin_amdgcn_readfirstlane(m.how);
+        return f;
+    };
+    const int sr = tid >> 4, sc = (tid & 15) * 4;   // this thread's row (+ 16 m) and first column of a footprint
+    const unsigned soff = (unsigned)sr * (unsigned)det.nu + (unsigned)sc;
+    fdk_quad pf[FDK_M];
+    auto fetch = [&](int k, const FdkBox& f) {
+        if (f.how < FDK_EDGE || sc >= f.w) return;
+        const float* pk = proj + (int64_t)k * det.nv * det.nu;
+        if (f.how == FDK_INSIDE) {
+            const float* pq = pk + ((int64_t)f.v0 * det.nu + f.u0);
+#pragma unroll
+            for (int m = 0; m < FDK_M; ++m)
+                if (16 * m < f.h) pf[m] = *reinterpret_cast<const fdk_quad*>(pq + (int64_t)(16 * m) * det.nu + soff);
+            return;
+        }
+#pragma unroll
+        for (int m = 0; m < FDK_M; ++m) {
+            const int u = f.u0 + sc, vv = f.v0 + sr + 16 * m;
+            pf[m] = fdk_quad{0.0f, 0.0f, 0.0f, 0.0f};
+            if (16 * m < f.h && (unsigned)vv < (unsigned)det.nv) {
+                const float* row = pk + (int64_t)vv * det.nu;
+                if (u >= 0 && u + 3 < det.nu) {
+                    pf[m] = *reinterpret_cast<const fdk_quad*>(row + u);
+                } else {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        if ((unsigned)(u + c) < (unsigned)det.nu) pf[m][c] = row[u + c];
                 }
             }
-            fb[threadIdx.x] = f;
         }
-        __syncthreads();
-        for (int q = 0; q < nb; ++q) {
-            const FdkBox f = fb[q];
-            if (f.w == 0) continue;
-            const float* pk = proj + (int64_t)(k0 + q) * det.nv * det.nu;
-            const int n = f.w * f.h;
-            for (int i = threadIdx.x; i < n; i += blockDim.x) {
-                // row i / w from FP32 ((i + 1/2) / w is at least 1/(2w) from an integer)
-                const int r = (int)(((float)i + 0.5f) * f.rw);
-                box[q][r * f.pitch + (i - r * f.w)] = pk[(int64_t)(f.v0 + r) * det.nu + f.u0 + (i - r * f.w)];
+    };
+
+    if (tid < min(2 * FDK_TAB, nviews)) fb[tid] = fdk_box(tab[view0 + tid], lo, hi, det, W_MAX);
+    __syncthreads();
+    FdkBox next = get(0);
+    fetch(0, next);
+    for (int k = 0; k < nviews; ++k) {
+        const FdkBox f = next;
+        float* bq = box[k & 1];
+        // (the half that held the last FDK_TAB views; read again FDK_TAB - 1 barriers from here)
+        if (k > 0 && (k & (FDK_TAB - 1)) == 0 && tid < min(FDK_TAB, nviews - k - FDK_TAB))
+            fb[(k + FDK_TAB + tid) & (2 * FDK_TAB - 1)] = fdk_box(tab[view0 + k + FDK_TAB + tid], lo, hi, det, W_MAX);
+        if (f.how >= FDK_EDGE && sc < f.w) {
+#pragma unroll
+            for (int m = 0; m < FDK_M; ++m)
+                if (16 * m < f.h) *reinterpret_cast<fdk_quad16*>(&bq[(sr + 16 * m) * P + sc]) = pf[m];
+        }
+        __syncthreads();   // (also: the other buffer's reads are done)
+        if (k + 1 < nviews) {
+            next = get(k + 1);
+            fetch(k + 1, next);
+        }
+        if (!live || f.how == FDK_NONE) continue;
+        const ViewGeo& g = tab[view0 + k];
+        const float W = __builtin_fmaf(g.MW[0], fx, __builtin_fmaf(g.MW[1], fy, g.MW[3]));
+        const float r0 = __builtin_amdgcn_rcpf(W);
+        const float rw = __builtin_fmaf(__builtin_fmaf(-W, r0, 1.0f), r0, r0);   // 1 / W (one Newton step)
+        const float fu = __builtin_fmaf(g.MU[0], fx, __builtin_fmaf(g.MU[1], fy, g.MU[3])) * rw;
+        const float fv0 = __builtin_fmaf(g.MV[2], fz0, __builtin_fmaf(g.MV[0], fx, __builtin_fmaf(g.MV[1], fy, g.MV[3]))) * rw;
+        const float dfv = g.MV[2] * rw;
+        const float wt = rw * rw;
+        const float flu = __builtin_floorf(fu);
+        const int iu = (int)flu;
+        const float au = fu - flu;
+        if (f.how >= FDK_EDGE) {
+            // LDS address of (row floor(v), column iu) as the FP32 integer C + 4 P floor(v), times 2^-149
+            const int C = (int)(unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)bq +
+                          4 * (iu - f.u0 - f.v0 * P);
+            const float Cf = (float)C * 0x1p-149f, Pf = __int_as_float(4 * P);
+            const float wu0 = 1.0f - au;
+#pragma unroll
+            for (int z = 0; z < ZC; ++z) {
+                const float fv = __builtin_fmaf((float)z, dfv, fv0);
+                const float flv = __builtin_floorf(fv);
+                const float av = fv - flv;
+                const auto* t = (const __attribute__((address_space(3))) float*)(uintptr_t)__float_as_uint(
+                    __builtin_fmaf(flv, Pf, Cf));
+                const float s0 = __builtin_fmaf(wu0, t[0], au * t[1]);
+                const float s1 = __builtin_fmaf(wu0, t[P], au * t[P + 1]);
+                acc[z] = __builtin_fmaf(wt, __builtin_fmaf(av, s1 - s0, s0), acc[z]);
             }
-        }
-        __syncthreads();
-        if (!live) continue;
-        for (int q = 0; q < nb; ++q) {
-            const int k = k0 + q;
-            const ViewGeo& g = tab[view0 + k];
-            const float W = __builtin_fmaf(g.MW[0], fx, __builtin_fmaf(g.MW[1], fy, g.MW[3]));
-            const float rw = 1.0f / W;
-            const float fu = __builtin_fmaf(g.MU[0], fx, __builtin_fmaf(g.MU[1], fy, g.MU[3])) * rw;
-            const float fv0 = __builtin_fmaf(g.MV[2], fz0, __builtin_fmaf(g.MV[0], fx, __builtin_fmaf(g.MV[1], fy, g.MV[3]))) * rw;
-            const float dfv = g.MV[2] * rw;
-            const float wt = rw * rw;
-            const float flu = __builtin_floorf(fu);
-            const int iu = (int)flu;
-            const float au = fu - flu;
+        } else {
             const float wu0 = (unsigned)iu < (unsigned)det.nu ? 1.0f - au : 0.0f;
             const float wu1 = (unsigned)(iu + 1) < (unsigned)det.nu ? au : 0.0f;
             if (wu0 == 0.0f && wu1 == 0.0f) continue;
             const int u0 = min(max(iu, 0), det.nu - 1), u1 = min(max(iu + 1, 0), det.nu - 1);
-            const FdkBox f = fb[q];
-            if (f.w > 0) {
-                // staged: LDS offsets clamped into the box (a no-op when the
-                // footprint holds the taps, which its margins ensure); the
-                // columns once per view, the rows per voxel unless the box
-                // holds every row the block can tap
-                const int c0 = min(max(u0 - f.u0, 0), f.w - 1), c1 = min(max(u1 - f.u0, 0), f.w - 1);
-                const float* bq = box[q];
-                if (f.inner) {
-                    // every tap lies in the box and on the detector (above):
-                    // no clamps and no zero weights (wu0, wu1 are 1 - au, au);
-                    // the row offset is an exact FP32 integer (below 2^24)
-                    const float v0f = (float)f.v0;
-                    const float* b = bq + (iu - f.u0);
+            const float* pk = proj + (int64_t)k * det.nv * det.nu;
 #pragma unroll
-                    for (int z = 0; z < FDK_ZC; ++z) {
-                        const float fv = __builtin_fmaf((float)z, dfv, fv0);
-                        const float flv = __builtin_floorf(fv);
-                        const float av = fv - flv;
-                        const float* t = b + (int)((flv - v0f) * (float)FDK_P);
-                        const float s0 = __builtin_fmaf(wu0, t[0], wu1 * t[1]);
-                        const float s1 = __builtin_fmaf(wu0, t[FDK_P], wu1 * t[FDK_P + 1]);
-                        acc[z] = __builtin_fmaf(wt, __builtin_fmaf(1.0f - av, s0, av * s1), acc[z]);
-                    }
-                    continue;
-                }
-#pragma unroll
-                for (int z = 0; z < FDK_ZC; ++z) {
-                    const float fv = __builtin_fmaf((float)z, dfv, fv0);
-                    const float flv = __builtin_floorf(fv);
-                    const int iv = (int)flv;
-                    const float av = fv - flv;
-                    const float wv0 = (unsigned)iv < (unsigned)det.nv ? 1.0f - av : 0.0f;
-                    const float wv1 = (unsigned)(iv + 1) < (unsigned)det.nv ? av : 0.0f;
-                    const int r0 = min(max(min(max(iv, 0), det.nv - 1) - f.v0, 0), f.h - 1);
-                    const int r1 = min(max(min(max(iv + 1, 0), det.nv - 1) - f.v0, 0), f.h - 1);
-                    const float* p0 = bq + r0 * f.pitch;
-                    const float* p1 = bq + r1 * f.pitch;
-                    const float s0 = __builtin_fmaf(wu0, p0[c0], wu1 * p0[c1]);
-                    const float s1 = __builtin_fmaf(wu0, p1[c0], wu1 * p1[c1]);
-                    acc[z] = __builtin_fmaf(wt, __builtin_fmaf(wv0, s0, wv1 * s1), acc[z]);
-                }
-            } else {
-                const float* pk = proj + (int64_t)k * det.nv * det.nu;
-#pragma unroll
-                for (int z = 0; z < FDK_ZC; ++z) {
-                    const float fv = __builtin_fmaf((float)z, dfv, fv0);
-                    const float flv = __builtin_floorf(fv);
-                    const int iv = (int)flv;
-                    const float av = fv - flv;
-                    const float wv0 = (unsigned)iv < (unsigned)det.nv ? 1.0f - av : 0.0f;
-                    const float wv1 = (unsigned)(iv + 1) < (unsigned)det.nv ? av : 0.0f;
-                    const int v0 = min(max(iv, 0), det.nv - 1), v1 = min(max(iv + 1, 0), det.nv - 1);
-                    const float* r0 = pk + (int64_t)v0 * det.nu;
-                    const float* r1 = pk + (int64_t)v1 * det.nu;
-                    const float s0 = __builtin_fmaf(wu0, r0[u0], wu1 * r0[u1]);
-                    const float s1 = __builtin_fmaf(wu0, r1[u0], wu1 * r1[u1]);
-                    acc[z] = __builtin_fmaf(wt, __builtin_fmaf(wv0, s0, wv1 * s1), acc[z]);
-                }
+            for (int z = 0; z < ZC; ++z) {
+                const float fv = __builtin_fmaf((float)z, dfv, fv0);
+                const float flv = __builtin_floorf(fv);
+                const int iv = (int)flv;
+                const float av = fv - flv;
+                const float wv0 = (unsigned)iv < (unsigned)det.nv ? 1.0f - av : 0.0f;
+                const float wv1 = (unsigned)(iv + 1) < (unsigned)det.nv ? av : 0.0f;
+                const int v0 = min(max(iv, 0), det.nv - 1), v1 = min(max(iv + 1, 0), det.nv - 1);
+                const float* r0 = pk + (int64_t)v0 * det.nu;
+                const float* r1 = pk + (int64_t)v1 * det.nu;
+                const float s0 = __builtin_fmaf(wu0, r0[u0], wu1 * r0[u1]);
+                const float s1 = __builtin_fmaf(wu0, r1[u0], wu1 * r1[u1]);
+                acc[z] = __builtin_fmaf(wt, __builtin_fmaf(wv0, s0, wv1 * s1), acc[z]);
             }
         }
     }
     if (!live) return;
 #pragma unroll
-    for (int z = 0; z < FDK_ZC; ++z) {
+    for (int z = 0; z < ZC; ++z) {
         const int iz = iz0 + z;
         if (iz >= v.nz) break;
         float* o = vol + ((int64_t)iz * v.ny + iy) * v.nx + ix;
@@ -634,12 +629,24 @@ __global__ void __launch_bounds__(256) k_fdk_filter(const float* in, float* out,
 hipError_t launch_backward_fdk(const Plan& p, const float* proj, float* vol, int64_t view0, int64_t nviews,
                                float beta, hipStream_t s)
 {
-    const int nbx = (p.vol.nx + FDK_TX - 1) / FDK_TX;
-    const int nby = (p.vol.ny + FDK_TY - 1) / FDK_TY;
-    const int nbz = (p.vol.nz + FDK_ZC - 1) / FDK_ZC;
+    const int nbx = (p.vol.nx + FDK_T - 1) / FDK_T;
+    const int nby = (p.vol.ny + FDK_T - 1) / FDK_T;
+    constexpr int ZC = 16;
+    const int nbz = (p.vol.nz + ZC - 1) / ZC;
     const unsigned blocks = (unsigned)nbx * nby * nbz;
-    hipLaunchKernelGGL(k_backward_fdk, dim3(blocks), dim3(FDK_TX * FDK_TY), 0, s, proj, vol, p.d_views,
-                       (int)view0, (int)nviews, p.vol, p.det, nbx, nby, beta);
+    auto run = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(FDK_T * FDK_T), 0, s, proj, vol, p.d_views, (int)view0, (int)nviews,
+                           p.vol, p.det, nbx, nby, beta);
+    };
+    // pixels per row that a block's diagonal covers at the volume's near side
+    const ctmi_geometry& g = p.geo;
+    const double dx = g.dVoxel[2], dy = g.dVoxel[1];
+    const double near = g.DSO - 0.5 * std::hypot(dx * p.vol.nx, dy * p.vol.ny);
+    const bool narrow = near > 0.0 && FDK_T * std::hypot(dx, dy) * g.DSD / (near * g.dDetector[1]) + 4.0 <= FDK_NARROW;
+    if (narrow)
+        run(k_backward_fdk<ZC, FDK_NARROW>);
+    else
+        run(k_backward_fdk<ZC, FDK_WIDE>);
     return hipGetLastError();
 }
 

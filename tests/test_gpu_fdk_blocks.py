@@ -1,0 +1,71 @@
+"""The FDK backprojector and the flattening at the edges of their work split,
+against the FP64 oracle: blocks of 16 x 16 x 16 voxels cut on every axis,
+footprints staged at both row pitches, cut by the detector on every side or off
+it, too large to stage, and more views than the footprint table holds; the
+flattening's row and view slices.
+
+Tolerance rel-L2 1e-4, the projectors' parity bar: FP32 positions carry three
+roundings of a sum that counts pixels from the detector's corner (5e-5 of a pixel at
+300 pixels), and neighbouring pixels of the projections are independent; a tap
+from a wrong pixel shows at 1e-2 and more."""
+import numpy as np
+import pytest
+
+import synth
+from synth import CurvedDetector, Geometry
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _rel(a, b):
+    return float(np.linalg.norm(a.ravel() - b.ravel()) / np.linalg.norm(b.ravel()))
+
+
+@pytest.fixture(scope="module")
+def P():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2412_10129_amd as P
+    return P
+
+
+# volume (z, y, x), detector, pixel (mm; voxels of 1 mm, magnification 1.5), offset (v, u), views
+@pytest.mark.parametrize("n,det,pix,off,views", [
+    ((1, 1, 1), (2, 3), 1.0, (0.0, 0.0), 1),
+    ((16, 16, 16), (40, 40), 1.2, (0.2, -0.3), 33),
+    ((17, 15, 33), (50, 75), 0.9, (0.2, -0.3), 70),      # narrow pitch, three tables of views
+    ((31, 18, 40), (120, 160), 0.58, (0.4, 0.3), 18),    # wide pitch
+    ((18, 20, 22), (200, 230), 0.25, (0.4, 0.3), 5),     # read from global memory
+    ((40, 37, 43), (21, 25), 1.1, (3.0, -7.0), 20),      # the detector cuts and misses blocks on every side
+    ((40, 37, 43), (5, 300), 0.7, (0.0, 0.0), 9),        # fewer rows than a block's footprint
+    ((5, 40, 40), (60, 3), 1.0, (0.0, 2.0), 9),          # rows narrower than a group of four
+])
+def test_backprojector_blocks(P, orc, n, det, pix, off, views):
+    geo = Geometry(DSD=900.0, DSO=600.0, nVoxel=n, dVoxel=(1.0, 1.0, 1.0), nDetector=det, dDetector=(pix, pix),
+                   offOrigin=(0.3, -0.4, 0.2), offDetector=off)
+    ang = synth.circular_angles(views) + 0.013
+    y = np.random.Generator(np.random.PCG64(51)).standard_normal((views,) + det).astype(np.float32)
+    buf = torch.full((y.size + 514,), float("nan"), device="cuda")   # rows on 4 bytes only, poison around
+    yd = buf[257:257 + y.size].view(y.shape)
+    yd.copy_(torch.from_numpy(y))
+    plan = P.Plan(geo, ang)
+    got = plan.backproject(yd, kind="fdk")
+    assert torch.equal(got, plan.backproject(yd, kind="fdk"))
+    want = orc.bfdk(geo, ang, y.astype(np.float64))
+    assert np.linalg.norm(got.cpu().numpy() - want) <= 1e-4 * np.linalg.norm(want) + 1e-30
+    acc = got.clone()
+    plan.backproject(yd, out=acc, kind="fdk", beta=2.0)
+    assert np.linalg.norm(acc.cpu().numpy() - 3.0 * want) <= 3e-4 * np.linalg.norm(want) + 1e-30
+
+
+@pytest.mark.parametrize("nv,nu,views", [(1, 1, 3), (17, 65, 1), (16, 64, 40), (300, 130, 5)])
+def test_flatten_slices(P, orc, nv, nu, views):
+    geo = Geometry(DSD=900.0, DSO=600.0, nVoxel=(8, 8, 8), dVoxel=(1.0, 1.0, 1.0), nDetector=(nv, nu), dDetector=(1.1, 0.9))
+    cd = CurvedDetector(nDetector=(nv + 3, nu + 5), dDetector=(1.05, 0.95), radius=900.0, offDetector=(0.3, -0.4))
+    q = np.random.Generator(np.random.PCG64(52)).random((views,) + cd.nDetector).astype(np.float32)
+    plan = P.Plan(geo, synth.circular_angles(views))
+    got = plan.flatten_curved(torch.from_numpy(q).cuda(), cd).cpu().numpy().astype(np.float64)
+    want = orc.flatten_curved(geo, cd, q)
+    assert _rel(got, want) < 1e-5
