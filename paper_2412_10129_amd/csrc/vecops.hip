@@ -211,18 +211,25 @@ __global__ void __launch_bounds__(256) k_sart_update(float* __restrict__ x, cons
 // u (all three backward neighbours present) is s_u = sqrt(sum_a w_a d_a^2 +
 // eps), d_a = x_u - x_{u - e_a}, w_a = exp(-(d_a / delta)^2) (1 for plain
 // TV); q_a(u) = w_a d_a / s_u (0 when s_u = 0).  The gradient with the
-// weights lagged is g_v = sum_a q_a(v) - sum_a q_a(v + e_a).  One thread per
-// voxel reads its 13-point neighbourhood (neighbouring threads share it
-// through the caches) and forms the four terms it needs.
+// weights lagged is g_v = sum_a q_a(v) - sum_a q_a(v + e_a).
+//
+// A wave owns TVX voxels along x (its lanes, with one more on either side) by
+// TVY rows and marches up z on its own: the neighbours along x come from the
+// next lanes (DPP), those along y and z from the thread's registers, so there
+// is no LDS and no barrier, and the terms formed twice are the lanes' and rows'
+// ends (64 / 62 and 9 / 8).  The next plane's rows are loaded a step ahead.  VALU
+// bounds it (three exponentials, a correctly rounded root and a division per
+// term): 512^3, adaptive weights, 400 us as 64 x 8 tiles staged in LDS, with 2.3
+// rounds of terms per tile and step between barriers; 322 us so (1.07 GB).
 struct TvTerm {
     float qz, qy, qx;
 };
 
-__device__ __forceinline__ TvTerm tv_term(float c, float bz, float by, float bx, float nid2, float eps)
+template <bool ADAPTIVE>
+__device__ __forceinline__ TvTerm tv_term(float dz, float dy, float dx, float nid2, float eps)
 {
-    const float dz = c - bz, dy = c - by, dx = c - bx;
     float wz = 1.0f, wy = 1.0f, wx = 1.0f;
-    if (nid2 != 0.0f) {   // nid2 = -1 / delta^2
+    if (ADAPTIVE) {   // nid2 = -1 / delta^2
         wz = __expf(dz * dz * nid2);
         wy = __expf(dy * dy * nid2);
         wx = __expf(dx * dx * nid2);
@@ -233,109 +240,80 @@ __device__ __forceinline__ TvTerm tv_term(float c, float bz, float by, float bx,
     return TvTerm{az * r, ay * r, ax * r};
 }
 
-// Tiled form: a workgroup owns a 64 x 8 (x, y) column of the volume over
-// TZ consecutive planes and marches up z.  Each step stages plane z + 1 (with
-// a one-voxel lower halo in x and y) in LDS, forms the terms of plane z + 1
-// once for the tile and its upper halo, and finishes plane z's gradient from
-// the terms of planes z and z + 1.  The plane after is loaded into registers
-// while the step runs.
-constexpr int TVX = 64, TVY = 8, TVZ = 64;
-constexpr int TXH = TVX + 2, TYH = TVY + 2;          // staged plane with lower and upper halo
-constexpr int TQX = TVX + 1, TQY = TVY + 1;          // terms: tile plus upper halo
-constexpr int TVL = (TXH * TYH + 255) / 256;         // staged cells per thread
-
-__global__ void __launch_bounds__(256) k_awtv_grad(const float* __restrict__ x, float* __restrict__ g, int nz, int ny,
-                                                   int nx, float nid2, float eps)
+__device__ __forceinline__ float lane_below(float v)   // of lane - 1 (0 for lane 0)
 {
-    __shared__ float pl[2][TXH * TYH];   // planes z and z + 1 (x from x0 - 1, y from y0 - 1)
-    __shared__ float q[2][3][TQX * TQY]; // terms (z, y, x components) of planes z and z + 1
-    const int tid = threadIdx.x;
-    const int x0 = blockIdx.x * TVX, y0 = blockIdx.y * TVY, z0 = blockIdx.z * TVZ;
-    const int z1 = min(z0 + TVZ, nz);
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float lane_above(float v)   // of lane + 1 (0 for lane 63)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xf, 0xf, false));
+}
+
+constexpr int TVX = 62, TVY = 8;
+
+template <bool ADAPTIVE>
+__global__ void __launch_bounds__(256, 6) k_awtv_grad(const float* __restrict__ x, float* __restrict__ g, int nz, int ny,
+                                                   int nx, int tz, int nbx, int nby, float nid2, float eps)
+{
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // layers of tz planes from the top down (what is written last, the low planes, is
+    // what a pass over g reads first); in a layer each XCD takes a contiguous
+    // run (tiles side by side along x share cache lines)
+    const int per = (nbx * nby + 7) / 8, layers = (nz + tz - 1) / tz;
+    const int layer = (int)(blockIdx.x / (8 * per)), r = (int)(blockIdx.x % (8 * per));
+    const int b = r % 8 * per + r / 8;
+    if (b >= nbx * nby) return;
+    const int by = b / nbx, bx = b - by * nbx;
+    const int X = bx * TVX + lane - 1;
+    const int y0 = (by * 4 + wave) * TVY;
+    const int z0 = (layers - 1 - layer) * tz, z1 = min(z0 + tz, nz);
+    if (y0 >= ny) return;
     const int64_t sz = (int64_t)nx * ny;
-    // staged cells of this thread: c -> (x0 - 1 + c % TXH, y0 - 1 + c / TXH)
-    int64_t off[TVL];
-    bool in[TVL];
+    const bool in = X >= 0 && X < nx;                       // this lane's column is in the volume
+    const bool term_x = X >= 1 && X < nx;                   // and has a term
+    const bool out_x = in && lane >= 1 && lane <= TVX;      // and is this wave's
+    // rows y0 - 1 ... y0 + TVY of a plane (0 outside the volume)
+    auto load = [&](int Z, float (&r)[TVY + 2]) {
+        const float* pz = x + (int64_t)Z * sz;
 #pragma unroll
-    for (int m = 0; m < TVL; ++m) {
-        const int c = tid + 256 * m;
-        const int X = x0 - 1 + c % TXH, Y = y0 - 1 + c / TXH;
-        in[m] = c < TXH * TYH && X >= 0 && X < nx && Y >= 0 && Y < ny;
-        off[m] = in[m] ? (int64_t)Y * nx + X : 0;
-    }
-    auto fetch = [&](int Z, float (&r)[TVL]) {
-#pragma unroll
-        for (int m = 0; m < TVL; ++m) r[m] = (in[m] && Z >= 0 && Z < nz) ? x[(int64_t)Z * sz + off[m]] : 0.0f;
-    };
-    auto stage = [&](float* dst, const float (&r)[TVL]) {
-#pragma unroll
-        for (int m = 0; m < TVL; ++m) {
-            const int c = tid + 256 * m;
-            if (c < TXH * TYH) dst[c] = r[m];
+        for (int j = 0; j < TVY + 2; ++j) {
+            const int Y = y0 - 1 + j;
+            r[j] = 0.0f;
+            if (Z >= 0 && Z < nz && Y >= 0 && Y < ny && in) r[j] = pz[(int64_t)Y * nx + X];
         }
     };
-    // terms of plane Z from its staged plane cur and the plane below, prev
-    auto terms = [&](int Z, const float* cur, const float* prev, int slot) {
-        for (int c = tid; c < TQX * TQY; c += 256) {
-            const int i = c % TQX, j = c / TQX;
-            const int X = x0 + i, Y = y0 + j;
-            float qz = 0.0f, qy = 0.0f, qx = 0.0f;
-            if (X >= 1 && Y >= 1 && Z >= 1 && X < nx && Y < ny && Z < nz) {
-                const int k = (j + 1) * TXH + (i + 1);
-                const TvTerm t = tv_term(cur[k], prev[k], cur[k - TXH], cur[k - 1], nid2, eps);
-                qz = t.qz;
-                qy = t.qy;
-                qx = t.qx;
-            }
-            q[slot][0][c] = qz;
-            q[slot][1][c] = qy;
-            q[slot][2][c] = qx;
-        }
-    };
-    int cp = 0, cq = 0;   // LDS slots holding plane z and its terms
-    {
-        float r[TVL];
-        fetch(z0 - 1, r);
-        stage(pl[1], r);
-        fetch(z0, r);
-        stage(pl[0], r);
-    }
-    __syncthreads();
-    terms(z0, pl[0], pl[1], 0);
-    // planes z + 1 ... z + 4 in flight in registers (global-load latency is
-    // longer than one step)
-    float ra[TVL], rb[TVL], rc[TVL], rd[TVL];
-    fetch(z0 + 1, ra);
-    fetch(z0 + 2, rb);
-    fetch(z0 + 3, rc);
-    fetch(z0 + 4, rd);
-    auto step = [&](int z, float (&r)[TVL]) {
-        // stage plane z + 1 over the slot of plane z - 1, then refill the
-        // registers with plane z + 5
-        stage(pl[cp ^ 1], r);
-        __syncthreads();
-        fetch(z + 5, r);
-        terms(z + 1, pl[cp ^ 1], pl[cp], cq ^ 1);
-        __syncthreads();
+    float prev[TVY + 2], cur[TVY + 2], next[TVY + 2];
+    float own[TVY], upy[TVY], upx[TVY];   // the plane below: a voxel's own terms, its upper neighbours' in y and x
+    load(z0 - 1, prev);
+    load(z0, cur);
+    for (int z = z0; z <= z1; ++z) {   // terms of plane z, gradient of plane z - 1
+        if (z < z1) load(z + 1, next);
+        TvTerm t[TVY + 1];
 #pragma unroll
-        for (int o = tid; o < TVX * TVY; o += 256) {
-            const int tx = o % TVX, ty = o / TVX;
-            const int X = x0 + tx, Y = y0 + ty;
-            if (X < nx && Y < ny) {
-                const int k = ty * TQX + tx;
-                const float gv = q[cq][0][k] + q[cq][1][k] + q[cq][2][k] - q[cq ^ 1][0][k] - q[cq][1][k + TQX] -
-                                 q[cq][2][k + 1];
-                g[(int64_t)z * sz + (int64_t)Y * nx + X] = gv;
-            }
+        for (int j = 0; j <= TVY; ++j) {
+            const int Y = y0 + j;
+            t[j] = TvTerm{0.0f, 0.0f, 0.0f};
+            const float c = cur[j + 1], cx = lane_below(c);
+            if (z >= 1 && z < nz && Y >= 1 && Y < ny && term_x)
+                t[j] = tv_term<ADAPTIVE>(c - prev[j + 1], c - cur[j], c - cx, nid2, eps);
         }
-        cp ^= 1;
-        cq ^= 1;
-    };
-    for (int z = z0; z < z1; z += 4) {
-        step(z, ra);
-        if (z + 1 < z1) step(z + 1, rb);
-        if (z + 2 < z1) step(z + 2, rc);
-        if (z + 3 < z1) step(z + 3, rd);
+        if (z > z0) {
+            float* gz = g + (int64_t)(z - 1) * sz;
+#pragma unroll
+            for (int j = 0; j < TVY; ++j)
+                if (y0 + j < ny && out_x) gz[(int64_t)(y0 + j) * nx + X] = own[j] - t[j].qz - upy[j] - upx[j];
+        }
+#pragma unroll
+        for (int j = 0; j < TVY; ++j) {
+            own[j] = t[j].qz + t[j].qy + t[j].qx;
+            upy[j] = t[j + 1].qy;
+            upx[j] = lane_above(t[j].qx);
+        }
+#pragma unroll
+        for (int j = 0; j < TVY + 2; ++j) {
+            prev[j] = cur[j];
+            cur[j] = next[j];
+        }
     }
 }
 
@@ -473,10 +451,18 @@ hipError_t launch_sart_update(float* x, const float* v, const float* bp, int64_t
 
 hipError_t launch_awtv_grad(const float* x, float* g, int nz, int ny, int nx, float delta, float eps, hipStream_t s)
 {
-    // -1 / delta^2, or 0 for plain TV (delta <= 0 or infinite)
-    const float nid2 = (delta > 0.0f && delta < CTMI_INF) ? -1.0f / (delta * delta) : 0.0f;
-    const dim3 grid((unsigned)((nx + TVX - 1) / TVX), (unsigned)((ny + TVY - 1) / TVY), (unsigned)((nz + TVZ - 1) / TVZ));
-    hipLaunchKernelGGL(k_awtv_grad, grid, dim3(256), 0, s, x, g, nz, ny, nx, nid2, eps);
+    // planes per wave: 8 (each march forms one plane of terms more than it writes, but
+    // long ones keep waves in planes far apart in memory: 512^3 at 32 planes 329 us, at 16
+    // 321, at 8 322 with the next pass 8 us faster), or 4 where that leaves the 256 CUs
+    // short of waves
+    const int nbx = (nx + TVX - 1) / TVX, nby = (ny + 4 * TVY - 1) / (4 * TVY);
+    const int tz = (int64_t)nbx * nby * 4 * ((nz + 7) / 8) < 4096 ? 4 : 8;
+    const dim3 grid((unsigned)((nbx * nby + 7) / 8 * 8 * ((nz + tz - 1) / tz)));
+    if (delta > 0.0f && delta < CTMI_INF)
+        hipLaunchKernelGGL(k_awtv_grad<true>, grid, dim3(256), 0, s, x, g, nz, ny, nx, tz, nbx, nby,
+                           -1.0f / (delta * delta), eps);
+    else   // plain TV
+        hipLaunchKernelGGL(k_awtv_grad<false>, grid, dim3(256), 0, s, x, g, nz, ny, nx, tz, nbx, nby, 0.0f, eps);
     return hipGetLastError();
 }
 
