@@ -68,6 +68,34 @@ __device__ __forceinline__ bf16x8 as_bf16x8(uint4 q)
     return r;
 }
 
+// Voxel v of an [n][d][h][w] grid of nvox voxels.  Below 2^31 in 32 bits: three
+// 64-bit divisions are several hundred instructions, most of what the kernels
+// with little work per voxel did.
+struct Vox {
+    int x, y, z, n;
+};
+__device__ __forceinline__ Vox vox_of(int64_t v, int64_t nvox, int d, int h, int w)
+{
+    Vox q;
+    if (nvox < (int64_t)1 << 31) {
+        unsigned r = (unsigned)v;
+        q.x = (int)(r % (unsigned)w);
+        r /= (unsigned)w;
+        q.y = (int)(r % (unsigned)h);
+        r /= (unsigned)h;
+        q.z = (int)(r % (unsigned)d);
+        q.n = (int)(r / (unsigned)d);
+    } else {
+        q.x = (int)(v % w);
+        v /= w;
+        q.y = (int)(v % h);
+        v /= h;
+        q.z = (int)(v % d);
+        q.n = (int)(v / d);
+    }
+    return q;
+}
+
 // ------------------------------------------------------------------ conv3
 constexpr int CX = 16, CY = 8, CZ = 2;               // output tile (x fastest)
 constexpr int HX = CX + 2, HY = CY + 2, HZ = CZ + 2;  // halo brick
@@ -740,14 +768,11 @@ __global__ void k_pool2(const u16* __restrict__ in, int ldi, int n, int d, int h
     const int64_t total = (int64_t)n * d * h * w * groups;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= total) return;
-    const int cg = (int)(i % groups);
-    int64_t v = i / groups;
-    const int x = (int)(v % w);
-    v /= w;
-    const int y = (int)(v % h);
-    v /= h;
-    const int z = (int)(v % d);
-    const int nb = (int)(v / d);
+    const bool small = total < (int64_t)1 << 31;
+    const int64_t v = small ? (int64_t)((unsigned)i / (unsigned)groups) : i / groups;
+    const int cg = (int)(i - v * groups);
+    const Vox q = vox_of(v, total / groups, d, h, w);
+    const int x = q.x, y = q.y, z = q.z, nb = q.n;
     float s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     for (int k = 0; k < 8; ++k) {
         const int zz = 2 * z + (k >> 2), yy = 2 * y + ((k >> 1) & 1), xx = 2 * x + (k & 1);
@@ -773,14 +798,11 @@ __global__ void k_skip_grad(const u16* __restrict__ e, int lde, const u16* __res
     const int64_t total = (int64_t)n * d * h * w * groups;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= total) return;
-    const int cg = (int)(i % groups);
-    int64_t v = i / groups;
-    const int x = (int)(v % w);
-    v /= w;
-    const int y = (int)(v % h);
-    v /= h;
-    const int z = (int)(v % d);
-    const int nb = (int)(v / d);
+    const bool small = total < (int64_t)1 << 31;
+    const int64_t v = small ? (int64_t)((unsigned)i / (unsigned)groups) : i / groups;
+    const int cg = (int)(i - v * groups);
+    const Vox q = vox_of(v, total / groups, d, h, w);
+    const int x = q.x, y = q.y, z = q.z, nb = q.n;
     const size_t fv = (((size_t)nb * d + z) * h + y) * w + x;
     const size_t pv = (((size_t)nb * (d / 2) + z / 2) * (h / 2) + y / 2) * (w / 2) + x / 2;
     float fe[8], fp[8], fc[8];
@@ -855,16 +877,13 @@ __global__ __launch_bounds__(256) void k_up2_mfma(const u16* __restrict__ x, int
     const int64_t v = v0 + li;
     const bool vok = v < nvox;
     const u16* xr = x + (vok ? v : v0) * ldx + 8 * g;
-    int64_t r = vok ? v : v0;
-    const int cx = (int)(r % w);
-    r /= w;
-    const int cy = (int)(r % h);
-    r /= h;
-    const int cz = (int)(r % d);
-    const int nb = (int)(r / d);
+    const Vox p = vox_of(vok ? v : v0, nvox, d, h, w);
+    const int cx = p.x, cy = p.y, cz = p.z, nb = p.n;
     const int D = 2 * d, H = 2 * h, W = 2 * w;
+    // this workgroup's output channels and sub-positions
+    const int cb = (int)blockIdx.y * 16 * NT, ns = 8 / (int)gridDim.z;
     // sub-positions one at a time (the input row stays in L1 between them)
-    for (int s = 0; s < 8; ++s) {
+    for (int s = (int)blockIdx.z * ns; s < ((int)blockIdx.z + 1) * ns; ++s) {
         f32x4 acc[NT];
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -873,7 +892,7 @@ __global__ __launch_bounds__(256) void k_up2_mfma(const u16* __restrict__ x, int
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
                 const uint4 wf =
-                    *reinterpret_cast<const uint4*>(wt + ((size_t)(nt * 16 + li) * 8 + s) * cin + kc + 8 * g);
+                    *reinterpret_cast<const uint4*>(wt + ((size_t)(cb + nt * 16 + li) * 8 + s) * cin + kc + 8 * g);
                 acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wf), xb, acc[nt], 0, 0, 0);
             }
         }
@@ -893,7 +912,7 @@ __global__ __launch_bounds__(256) void k_up2_mfma(const u16* __restrict__ x, int
         const size_t fv = (((size_t)nb * D + Z) * H + Y) * W + X;
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
-            const int co = nt * 16 + 4 * g;
+            const int co = cb + nt * 16 + 4 * g;
             float o[4] = {acc[nt][0], acc[nt][1], acc[nt][2], acc[nt][3]};
             if (bias) {
 #pragma unroll
@@ -960,18 +979,16 @@ __global__ void k_up2_dgrad(const u16* __restrict__ gr, int ldg, int cout, const
 // workgroup stages each 32-wide k chunk of W' transposed in LDS ([ci][32],
 // one 16-byte A fragment per lane and ci tile).  Lane (li, g) ends with
 // ci = 16 nt + 4 g .. + 3 of voxel v0 + li.
-#ifndef CTMI_UP2_DGRAD_MFMA
-#define CTMI_UP2_DGRAD_MFMA 1
-#endif
 constexpr int UPD_VG = 2;   // 16-voxel groups per wave
 template <int NT>
 __global__ __launch_bounds__(256) void k_up2_dgrad_mfma(const u16* __restrict__ gr, int ldg, int cout,
-                                                        const u16* __restrict__ wt, const u16* __restrict__ below,
-                                                        int ldb, int n, int d, int h, int w, u16* __restrict__ out,
-                                                        int ldo)
+                                                        const u16* __restrict__ wt, int cin,
+                                                        const u16* __restrict__ below, int ldb, int n, int d, int h,
+                                                        int w, u16* __restrict__ out, int ldo)
 {
-    constexpr int CIN = 16 * NT, WS = 40;   // LDS row stride (u16): 32 k + 8 pad
+    constexpr int CIN = 16 * NT, WS = 40;   // this workgroup's channels; LDS row stride (u16): 32 k + 8 pad
     __shared__ __attribute__((aligned(16))) u16 wl[CIN * WS];
+    const int cb = (int)blockIdx.y * CIN;
     const int lane = threadIdx.x & 63, g = lane >> 4, li = lane & 15;
     const int64_t nvox = (int64_t)n * d * h * w;
     const int64_t vw = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * (16 * UPD_VG);   // the wave's first voxel
@@ -982,14 +999,8 @@ __global__ __launch_bounds__(256) void k_up2_dgrad_mfma(const u16* __restrict__ 
     for (int q = 0; q < UPD_VG; ++q) {
         const int64_t v = vw + 16 * q + li;
         vok[q] = v < nvox;
-        int64_t r = vok[q] ? v : 0;
-        const int cx = (int)(r % w);
-        r /= w;
-        const int cy = (int)(r % h);
-        r /= h;
-        const int cz = (int)(r % d);
-        const int nb = (int)(r / d);
-        fb[q] = (((int64_t)nb * D2 + 2 * cz) * H2 + 2 * cy) * W2 + 2 * cx;
+        const Vox p = vox_of(vok[q] ? v : 0, nvox, d, h, w);
+        fb[q] = (((int64_t)p.n * D2 + 2 * p.z) * H2 + 2 * p.y) * W2 + 2 * p.x;
     }
     f32x4 acc[UPD_VG][NT];
 #pragma unroll
@@ -1002,7 +1013,7 @@ __global__ __launch_bounds__(256) void k_up2_dgrad_mfma(const u16* __restrict__ 
         for (int i = threadIdx.x; i < CIN * 32; i += 256) {
             const int ci = i % CIN, kk = i / CIN;   // consecutive threads read consecutive ci
             const int k = kc + kk, s = k / cout, co = k - s * cout;
-            wl[ci * WS + kk] = wt[((size_t)co * 8 + s) * CIN + ci];
+            wl[ci * WS + kk] = wt[((size_t)co * 8 + s) * cin + cb + ci];
         }
         __syncthreads();
         const int k = kc + 8 * g, s = k / cout, co0 = k - s * cout;
@@ -1033,7 +1044,7 @@ __global__ __launch_bounds__(256) void k_up2_dgrad_mfma(const u16* __restrict__ 
         const int64_t v = vw + 16 * q + li;
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
-            const int ci = nt * 16 + 4 * g;
+            const int ci = cb + nt * 16 + 4 * g;
             float o[4] = {acc[q][nt][0], acc[q][nt][1], acc[q][nt][2], acc[q][nt][3]};
             if (below) {
                 const uint2 m = *reinterpret_cast<const uint2*>(below + v * ldb + ci);
@@ -1092,15 +1103,9 @@ __global__ __launch_bounds__(256) void k_up2_wgrad_mfma(const u16* __restrict__ 
         const int64_t v = (split + j * nsplit) * 64 + lane;
         g0 = g1 = x0 = x1 = make_uint4(0, 0, 0, 0);
         if (j < mine && v < nvox) {
-            int64_t r = v;
-            const int cx = (int)(r % w);
-            r /= w;
-            const int cy = (int)(r % h);
-            r /= h;
-            const int cz = (int)(r % d);
-            const int nb = (int)(r / d);
-            const int64_t fv = (((int64_t)nb * D2 + 2 * cz + (s >> 2)) * H2 + 2 * cy + ((s >> 1) & 1)) * W2 + 2 * cx +
-                               (s & 1);
+            const Vox p = vox_of(v, nvox, d, h, w);
+            const int64_t fv =
+                (((int64_t)p.n * D2 + 2 * p.z + (s >> 2)) * H2 + 2 * p.y + ((s >> 1) & 1)) * W2 + 2 * p.x + (s & 1);
             const u16* gp = gr + fv * ldg + cot * 16;
             const u16* xp = x + v * ldx + cit * 16;
             g0 = *reinterpret_cast<const uint4*>(gp);
@@ -1381,14 +1386,20 @@ hipError_t launch_unet_up2(const uint16_t* x, int ldx, int cin, const uint16_t* 
 {
     const int64_t nvox = (int64_t)n * d * h * w;
     if (cin % 32 == 0 && (cout == 16 || cout == 32 || cout == 64)) {
-        // one wave per 16 coarse voxels, four waves per workgroup
+        // one wave per 16 coarse voxels, four waves per workgroup, all output
+        // channels and sub-positions (the input is then read once), or, where
+        // that leaves most of the 256 CUs idle, 16 channels and one
+        // sub-position (four crops of 8^3, 128 -> 64 channels: 32 us in 32
+        // workgroups, 13 us in 1024)
         const unsigned blocks = (unsigned)((nvox + 63) / 64);
-        if (cout == 16)
-            k_up2_mfma<1><<<blocks, 256, 0, s>>>(x, ldx, cin, wt, bias, n, d, h, w, out, ldo);
-        else if (cout == 32)
+        if (cout == 16 || blocks < 256) {
+            const dim3 grid(blocks, cout / 16, blocks < 256 ? 8 : 1);
+            k_up2_mfma<1><<<grid, 256, 0, s>>>(x, ldx, cin, wt, bias, n, d, h, w, out, ldo);
+        } else if (cout == 32) {
             k_up2_mfma<2><<<blocks, 256, 0, s>>>(x, ldx, cin, wt, bias, n, d, h, w, out, ldo);
-        else
+        } else {
             k_up2_mfma<4><<<blocks, 256, 0, s>>>(x, ldx, cin, wt, bias, n, d, h, w, out, ldo);
+        }
         return hipGetLastError();
     }
     const int64_t total = nvox * 8 * (cout / 8);
@@ -1401,11 +1412,18 @@ hipError_t launch_unet_up2_dgrad(const uint16_t* g, int ldg, int cout, const uin
                                  hipStream_t s)
 {
     const int64_t nvox = (int64_t)n * d * h * w;
-    if (CTMI_UP2_DGRAD_MFMA && cout % 16 == 0 && (cin == 32 || cin == 64 || cin == 128)) {
+    if (cout % 16 == 0 && (cin == 32 || cin == 64 || cin == 128)) {
+        // all input channels per workgroup, or 16 where the voxels alone leave
+        // most of the 256 CUs idle (four crops of 8^3, 128 channels: 44 us in 16
+        // workgroups, 21 us in 128)
         const unsigned blocks = (unsigned)((nvox + 4 * 16 * UPD_VG - 1) / (4 * 16 * UPD_VG));
-        if (cin == 32) k_up2_dgrad_mfma<2><<<blocks, 256, 0, s>>>(g, ldg, cout, wt, below, ldb, n, d, h, w, out, ldo);
-        else if (cin == 64) k_up2_dgrad_mfma<4><<<blocks, 256, 0, s>>>(g, ldg, cout, wt, below, ldb, n, d, h, w, out, ldo);
-        else k_up2_dgrad_mfma<8><<<blocks, 256, 0, s>>>(g, ldg, cout, wt, below, ldb, n, d, h, w, out, ldo);
+        const int nt = blocks < 256 ? 1 : cin / 16;
+        const dim3 grid(blocks, cin / (16 * nt));
+        auto run = [&](auto kernel) { kernel<<<grid, 256, 0, s>>>(g, ldg, cout, wt, cin, below, ldb, n, d, h, w, out, ldo); };
+        if (nt == 1) run(k_up2_dgrad_mfma<1>);
+        else if (nt == 2) run(k_up2_dgrad_mfma<2>);
+        else if (nt == 4) run(k_up2_dgrad_mfma<4>);
+        else run(k_up2_dgrad_mfma<8>);
         return hipGetLastError();
     }
     const int64_t total = nvox * (cin / 8);

@@ -155,3 +155,25 @@ def test_head_loss_sums(P, nv):  # noqa: F811
     assert abs(s[17] / nv - loss) < 1e-6 * loss
     assert _rel(s[:16], g @ act) < 1e-5 and abs(s[16] - g.sum()) < 1e-5 * np.abs(g).sum()
     assert _rel(dhead.cpu().numpy(), s[:17]) < 1e-6
+
+
+# the up-convolution at both sides of its channel split (fewer than 256 workgroups of
+# 64 voxels, or not), forward and data gradient, against the oracle
+@pytest.mark.parametrize("n,d,h,w,cin,cout", [(1, 1, 1, 1, 32, 16), (2, 5, 7, 9, 128, 64), (1, 26, 25, 26, 64, 32),
+                                              (1, 33, 32, 33, 32, 16), (1, 33, 32, 33, 64, 64), (1, 33, 32, 33, 128, 16)])
+def test_up2_split_edges(P, n, d, h, w, cin, cout):  # noqa: F811
+    L = _lib()
+    lib = L.lib()
+    x = synth.bf16_values((n, d, h, w, cin), 31)
+    wt = synth.bf16_values((cout, 8, cin), 32, -0.3, 0.3)
+    b = synth.bf16_values((cout,), 33, -0.5, 0.5)
+    out = torch.full((n, 2 * d, 2 * h, 2 * w, cout), float("nan"), dtype=torch.bfloat16, device="cuda")
+    tx, tw, tb = _bf(x), _bf(wt), torch.from_numpy(b).cuda()
+    L.check(lib.ctmi_upsample2(n, d, h, w, _p(tx), cin, cin, _p(tw), _p(tb), cout, _p(out), cout, _s()))
+    _bf16_close(_np(out), U.up2(x, wt, b))
+    gr = synth.bf16_values((n, 2 * d, 2 * h, 2 * w, cout), 34)
+    below = synth.bf16_values((n, d, h, w, cin), 35)
+    dx = torch.full((n, d, h, w, cin), float("nan"), dtype=torch.bfloat16, device="cuda")
+    tg, tbel = _bf(gr), _bf(below)
+    L.check(lib.ctmi_upsample2_dgrad(n, d, h, w, _p(tg), cout, cout, _p(tw), cin, _p(tbel), cin, _p(dx), cin, _s()))
+    _bf16_close(_np(dx), U.up2_dgrad(gr, wt) * (below > 0))
