@@ -874,54 +874,65 @@ __global__ __launch_bounds__(256) void k_up2_mfma(const u16* __restrict__ x, int
     const int64_t nvox = (int64_t)n * d * h * w;
     const int64_t v0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 16;
     if (v0 >= nvox) return;   // uniform over the wave
-    const int64_t v = v0 + li;
-    const bool vok = v < nvox;
-    const u16* xr = x + (vok ? v : v0) * ldx + 8 * g;
-    const Vox p = vox_of(vok ? v : v0, nvox, d, h, w);
-    const int cx = p.x, cy = p.y, cz = p.z, nb = p.n;
+    const bool vok = v0 + li < nvox;
+    const u16* xr = x + (vok ? v0 + li : v0) * ldx + 8 * g;
+    // The fine voxels that this lane writes: sub-position odd (li / 8) along x of
+    // coarse voxels v0 + li % 8 and 8 further
+    const int odd = li >> 3;
+    const int64_t va = v0 + (li & 7), vb = va + 8;
+    const bool aok = va < nvox, bok = vb < nvox;
+    const Vox pa = vox_of(aok ? va : v0, nvox, d, h, w), pb = vox_of(bok ? vb : v0, nvox, d, h, w);
     const int D = 2 * d, H = 2 * h, W = 2 * w;
+    const size_t fa = (((size_t)pa.n * D + 2 * pa.z) * H + 2 * pa.y) * W + 2 * pa.x + odd;
+    const size_t fb = (((size_t)pb.n * D + 2 * pb.z) * H + 2 * pb.y) * W + 2 * pb.x + odd;
     // this workgroup's output channels and sub-positions
-    const int cb = (int)blockIdx.y * 16 * NT, ns = 8 / (int)gridDim.z;
-    // sub-positions one at a time (the input row stays in L1 between them)
-    for (int s = (int)blockIdx.z * ns; s < ((int)blockIdx.z + 1) * ns; ++s) {
-        f32x4 acc[NT];
+    const int cb = (int)blockIdx.y * 16 * NT, ns = 4 / (int)gridDim.z;
+    // two sub-positions along x at a time (the input row stays in L1 between them)
+    for (int sp = (int)blockIdx.z * ns; sp < ((int)blockIdx.z + 1) * ns; ++sp) {
+        f32x4 acc[2][NT];
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int q = 0; q < 2 * NT; ++q) acc[q / NT][q % NT] = f32x4{0.f, 0.f, 0.f, 0.f};
         for (int kc = 0; kc < cin; kc += 32) {
             const bf16x8 xb = as_bf16x8(vok ? *reinterpret_cast<const uint4*>(xr + kc) : make_uint4(0, 0, 0, 0));
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                const uint4 wf =
-                    *reinterpret_cast<const uint4*>(wt + ((size_t)(cb + nt * 16 + li) * 8 + s) * cin + kc + 8 * g);
-                acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wf), xb, acc[nt], 0, 0, 0);
+            for (int q = 0; q < 2 * NT; ++q) {
+                const uint4 wf = *reinterpret_cast<const uint4*>(
+                    wt + ((size_t)(cb + q % NT * 16 + li) * 8 + 2 * sp + q / NT) * cin + kc + 8 * g);
+                acc[q / NT][q % NT] =
+                    __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wf), xb, acc[q / NT][q % NT], 0, 0, 0);
             }
         }
         // The accumulators are read right after the last MFMA; the compiler
         // left too few wait states there (the first two of each four read
         // stale values), so 24 explicit ones are placed between the MFMAs
         // that define them and the reads, pinned by in/out operands.
-        if constexpr (NT == 1)
-            asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" : "+a"(acc[0]));
-        else if constexpr (NT == 2)
-            asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" : "+a"(acc[0]), "+a"(acc[1]));
-        else
-            asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7"
-                         : "+a"(acc[0]), "+a"(acc[1]), "+a"(acc[2]), "+a"(acc[3]));
-        if (!vok) continue;
-        const int Z = 2 * cz + (s >> 2), Y = 2 * cy + ((s >> 1) & 1), X = 2 * cx + (s & 1);
-        const size_t fv = (((size_t)nb * D + Z) * H + Y) * W + X;
+#pragma unroll
+        for (int q = 0; q < 2 * NT; ++q)
+            asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" : "+a"(acc[q / NT][q % NT]));
+        const size_t so = ((size_t)(sp >> 1) * H + (sp & 1)) * W;
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
             const int co = cb + nt * 16 + 4 * g;
-            float o[4] = {acc[nt][0], acc[nt][1], acc[nt][2], acc[nt][3]};
-            if (bias) {
+            uint2 o[2];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) o[e] += bias[co + e];
+            for (int q = 0; q < 2; ++q) {
+                float f[4] = {acc[q][nt][0], acc[q][nt][1], acc[q][nt][2], acc[q][nt][3]};
+                if (bias) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) f[e] += bias[co + e];
+                }
+                o[q].x = (uint32_t)f2bf(f[0]) | ((uint32_t)f2bf(f[1]) << 16);
+                o[q].y = (uint32_t)f2bf(f[2]) | ((uint32_t)f2bf(f[3]) << 16);
             }
-            uint2 q;
-            q.x = (uint32_t)f2bf(o[0]) | ((uint32_t)f2bf(o[1]) << 16);
-            q.y = (uint32_t)f2bf(o[2]) | ((uint32_t)f2bf(o[3]) << 16);
-            *reinterpret_cast<uint2*>(out + fv * ldo + co) = q;
+            // Each store covers both sub-positions of eight voxels (rows without
+            // gaps) instead of one of sixteen: lanes li and li ^ 8 exchange
+            // what the other one writes.
+            const uint2 send = odd ? o[0] : o[1];
+            uint2 recv;
+            recv.x = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)send.x, 0x128, 0xf, 0xf, false);   // row_ror:8
+            recv.y = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)send.y, 0x128, 0xf, 0xf, false);
+            if (aok) *reinterpret_cast<uint2*>(out + (fa + so) * ldo + co) = odd ? recv : o[0];
+            if (bok) *reinterpret_cast<uint2*>(out + (fb + so) * ldo + co) = odd ? o[1] : recv;
         }
     }
 }
@@ -1388,17 +1399,15 @@ hipError_t launch_unet_up2(const uint16_t* x, int ldx, int cin, const uint16_t* 
     if (cin % 32 == 0 && (cout == 16 || cout == 32 || cout == 64)) {
         // one wave per 16 coarse voxels, four waves per workgroup, all output
         // channels and sub-positions (the input is then read once), or, where
-        // that leaves most of the 256 CUs idle, 16 channels and one
-        // sub-position (four crops of 8^3, 128 -> 64 channels: 32 us in 32
-        // workgroups, 13 us in 1024)
+        // that leaves most of the 256 CUs idle, 16 channels and two
+        // sub-positions (four crops of 8^3, 128 -> 64 channels: 32 us in 32
+        // workgroups, 13 us in 512)
         const unsigned blocks = (unsigned)((nvox + 63) / 64);
         if (cout == 16 || blocks < 256) {
-            const dim3 grid(blocks, cout / 16, blocks < 256 ? 8 : 1);
+            const dim3 grid(blocks, cout / 16, blocks < 256 ? 4 : 1);
             k_up2_mfma<1><<<grid, 256, 0, s>>>(x, ldx, cin, wt, bias, n, d, h, w, out, ldo);
-        } else if (cout == 32) {
-            k_up2_mfma<2><<<blocks, 256, 0, s>>>(x, ldx, cin, wt, bias, n, d, h, w, out, ldo);
-        } else {
-            k_up2_mfma<4><<<blocks, 256, 0, s>>>(x, ldx, cin, wt, bias, n, d, h, w, out, ldo);
+        } else {   // (64 channels in two halves: 47 us against 66 at once, 32^3 coarse voxels)
+            k_up2_mfma<2><<<dim3(blocks, cout / 32), 256, 0, s>>>(x, ldx, cin, wt, bias, n, d, h, w, out, ldo);
         }
         return hipGetLastError();
     }
