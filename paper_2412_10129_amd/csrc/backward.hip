@@ -423,7 +423,6 @@ k_backward_siddon(const float* __restrict__ proj, float* __restrict__ vol, const
     const int x1 = min(x0 + BX, v.nx), y1 = min(y0 + BY, v.ny), z1 = min(z0 + BZ, v.nz);
     const float lo[3] = {x0 - 0.5f, y0 - 0.5f, z0 - 0.5f};   // cell box in voxel-centre coordinates
     const float hi[3] = {x1 - 0.5f, y1 - 0.5f, z1 - 0.5f};
-    char* const accb = reinterpret_cast<char*>(acc);
 
     for (int k = 0; k < nviews; k += GV) {
         int exs[2] = {0, 0};
