@@ -190,7 +190,7 @@ __device__ __forceinline__ int round_int(float q)
 template <int GV>
 struct GroupLds {
     int u0[GV], v0[GV], w[GV], h[GV];
-    int ku[GV], kv[GV], rk[GV], hp[GV], pre[GV + 1];
+    int ku[GV], kv[GV], rk[GV], hp[GV], wide[GV], pre[GV + 1];
     float rcol[GV], rrow[GV];   // reciprocals of ku kv hp (pixels per column group) and hp
     float most[GV], f[GV];      // rays on one cell times the most each adds per unit y; the latter
     float red[2][16];           // per wave: largest |y|, sum of |y|
@@ -205,32 +205,41 @@ struct GroupLds {
 // length.  A bank model of the atomics (16 lanes per step, 64 banks) gives 44
 // clocks per 64 samples at 1.5 pixels per voxel, 69 for plain column order, 68
 // for row order, with 79 % of the lanes at work (76 % for groups of 2 ku).
-template <int GV>
+// Where a column's rows end within 16 lanes, a step of the interpolated adjoint's
+// atomics takes in the next column too, whose rays share its cells: there a group
+// is 2 ku columns in the order 0, ku, 1, ku + 1, ... (`wide`; 245x112x112 x 46
+// views 2.21 -> 2.06 ms, 201x84x178 x 46 0.80 -> 0.73, 512^3 x 120 102.0 -> 100.0).
+// Not for three row classes and more, whose ku columns fill a wave already
+// (117x203x181 x 37: 2.73 -> 2.76 ms), nor for Siddon, whose walks leave a cell
+// at every step (259x78x51 x 46: 612 -> 635 us).
+template <bool SIDDON, int GV>
 __device__ __forceinline__ void pixel_order(GroupLds<GV>& G, int g, float pu, float pv)
 {
     const int w = G.w[g], h = G.h[g];
     const int ku = min(max((int)__builtin_ceilf(fminf(pu, 16.0f) - 0.1f), 1), 8);
     const int kv = min(max((int)__builtin_ceilf(fminf(pv, 16.0f) - 0.1f), 1), 8);
-    const int hp = (h + kv - 1) / kv, per = ku * kv * hp;
+    const int hp = (h + kv - 1) / kv, wide = !SIDDON && kv <= 2 && hp <= 16 ? 2 : 1, per = wide * ku * kv * hp;
     G.ku[g] = ku;
+    G.wide[g] = wide;
     G.kv[g] = kv;
-    G.rk[g] = (65536 + ku - 1) / ku;   // ceil(2^16 / ku): i ku / 2^16 floors to i div ku for i < 64
+    G.rk[g] = (65536 + wide * ku - 1) / (wide * ku);   // ceil(2^16 / n): i / n for i < 128, n <= 16
     G.hp[g] = hp;
     G.rcol[g] = 1.0f / (float)per;
     G.rrow[g] = 1.0f / (float)hp;
-    G.pre[g + 1] = (((w + ku - 1) / ku) * per + 63) / 64;
+    G.pre[g + 1] = (((w + wide * ku - 1) / (wide * ku)) * per + 63) / 64;
 }
 
 // Pixel p of view g's order; false when the index falls on padding.  The
 // quotients come from FP32 reciprocals: floor((i + 1/2) r), r = fl(1/n), is
 // i div n for every i < 2^22.  (A footprint of more pixels than that, of a
 // voxel that covers thousands, is corrected by an exact remainder step.)
-template <int GV>
+template <bool SIDDON, int GV>
 __device__ __forceinline__ bool group_pixel(const GroupLds<GV>& G, int g, int p, int& iu, int& iv)
 {
     // the view's layout is the same in every lane: scalar registers
     const int ku = __builtin_amdgcn_readfirstlane(G.ku[g]), kv = __builtin_amdgcn_readfirstlane(G.kv[g]);
-    const int hp = __builtin_amdgcn_readfirstlane(G.hp[g]), per = ku * kv * hp;
+    const int wide = SIDDON ? 1 : __builtin_amdgcn_readfirstlane(G.wide[g]);
+    const int hp = __builtin_amdgcn_readfirstlane(G.hp[g]), per = wide * ku * kv * hp;
     int cg = (int)(((float)p + 0.5f) * G.rcol[g]);
     if (G.pre[g + 1] - G.pre[g] > (1 << 16)) {
         const int rem = p - cg * per;
@@ -240,7 +249,8 @@ __device__ __forceinline__ bool group_pixel(const GroupLds<GV>& G, int g, int p,
     const int ab = (int)(((float)r + 0.5f) * G.rrow[g]);
     r -= ab * hp;
     const int a = (ab * G.rk[g]) >> 16;
-    const int du = cg * ku + ab - a * ku, dv = a + kv * r;
+    const int b = ab - a * wide * ku;
+    const int du = cg * wide * ku + (wide == 2 ? (b >> 1) + (b & 1) * ku : b), dv = a + kv * r;
     iu = G.u0[g] + du;
     iv = G.v0[g] + dv;
     return du < G.w[g] && dv < G.h[g];
@@ -299,7 +309,7 @@ __device__ __forceinline__ int group_scale(GroupLds<GV>& G, const ViewGeo* __res
                 }
                 G.f[g] = one;
                 G.most[g] = cu * cv * one;
-                pixel_order(G, g, f.su, f.sv);
+                pixel_order<SIDDON>(G, g, f.su, f.sv);
             }
         }
     }
@@ -435,7 +445,7 @@ k_backward_siddon(const float* __restrict__ proj, float* __restrict__ vol, const
         for (int bt = wave; bt < nbat; bt += NW) {
             while (bt >= __builtin_amdgcn_readfirstlane(G.pre[gv + 1])) ++gv;   // the batch's view (uniform)
             int iu, iv;
-            const bool in = group_pixel(G, gv, 64 * (bt - __builtin_amdgcn_readfirstlane(G.pre[gv])) + lane, iu, iv);
+            const bool in = group_pixel<true>(G, gv, 64 * (bt - __builtin_amdgcn_readfirstlane(G.pre[gv])) + lane, iu, iv);
             float y = 0.0f;
             if (in) y = finite_or_zero(proj[((int64_t)(k + gv) * det.nv + iv) * det.nu + iu]);
             if (y == 0.0f || (fabsf(y) > cut) != (cls != 0)) continue;
@@ -687,7 +697,7 @@ k_backward_interp(const float* __restrict__ proj, float* __restrict__ vol, const
         for (int bt = wave; bt < nbat; bt += NW) {
             while (bt >= __builtin_amdgcn_readfirstlane(G.pre[gv + 1])) ++gv;   // the batch's view (uniform)
             int iu, iv;
-            const bool in = group_pixel(G, gv, 64 * (bt - __builtin_amdgcn_readfirstlane(G.pre[gv])) + lane, iu, iv);
+            const bool in = group_pixel<false>(G, gv, 64 * (bt - __builtin_amdgcn_readfirstlane(G.pre[gv])) + lane, iu, iv);
             float y = 0.0f;
             if (in) y = finite_or_zero(proj[((int64_t)(k + gv) * det.nv + iv) * det.nu + iu]);
             InterpRay r;
@@ -912,7 +922,11 @@ int64_t adjoint_bricks(const Plan& p)
 size_t interp_adjoint_ws_bytes(const Plan& p) { return sizeof(float) * (size_t)adjoint_bricks(p) * CTMI_HALO_SLOTS; }
 
 // Views per call up to which the interpolated adjoint keeps a fixed-point unit
-// per round of rays (backward_few.hip); ordered-subset blocks lie below.
+// per round of rays (backward_few.hip); ordered-subset blocks lie below.  The
+// bricks above are faster there too (18 views of 512x512 on 256^3, an OS-SART
+// block: 5.27 ms against 6.46), but SART and EM results then move by up to 2e-4 in
+// blocks of 5 to 20 views, and 3 of 18 runs at 21 to 32 views still moved single
+// voxels by 8e-4 and more.
 constexpr int64_t FEW_VIEWS = 32;
 
 template <int BZ>
@@ -944,13 +958,15 @@ hipError_t launch_bricks(const Plan& p, const float* proj, float* vol, int64_t v
 }
 
 // Brick height and waves per brick, by the number of 16x16x8 bricks.  From
-// 2048 on, bricks of 16 planes with 8 waves (24 waves per CU in three
+// 1280 on, bricks of 16 planes with 8 waves (24 waves per CU in three
 // workgroups) fill the GPU's 256 CUs: fewer rays are cut short by a brick's
 // upper and lower face, so a wave's lanes run more alike, and the footprint,
 // scale and flush of a group are shared by twice the voxels (interpolated, 512^3
 // x 120 views: 114 -> 104 ms against bricks of 8 planes with 4 waves; Siddon,
 // 256^3 x 90 views: 9.6 -> 8.5 ms).  Below that the bricks of 8 planes keep more
-// CUs at work (128^3 x 12 views, Siddon: 205 us against 215), and below 512 a
+// CUs at work (128^3 x 12 views, Siddon: 205 us against 215; 1 127 bricks, Siddon,
+// 46 views: 555 against 580, where 1 352 gain: 480 -> 463 us, interpolated 1 120 ->
+// 907, and 1 519: 636 -> 537 and 2 738 -> 2 209), and below 512 a
 // brick takes 16 waves; the Siddon adjoint, which has no shells whose size the
 // workspace fixes, then also halves the brick (64^3 x 64 views, forward and
 // adjoint: 199 -> 177 us).  A volume of up to 8 planes has one layer of bricks
@@ -960,7 +976,7 @@ hipError_t launch_adjoint(const Plan& p, const float* proj, float* vol, int64_t 
                           float* shell, hipStream_t s)
 {
     const int64_t bricks = adjoint_bricks(p);
-    if (p.vol.nz > 8 && bricks >= 2048)
+    if (p.vol.nz > 8 && bricks >= 1280)
         return launch_bricks<SIDDON, 16, 8, 8, 6>(p, proj, vol, view0, nviews, beta, shell, s);
     if (bricks >= 512) return launch_bricks<SIDDON, 8, 8, 8, 6>(p, proj, vol, view0, nviews, beta, shell, s);
     return launch_bricks<SIDDON, SIDDON ? 4 : 8, 16, 16, 4>(p, proj, vol, view0, nviews, beta, shell, s);

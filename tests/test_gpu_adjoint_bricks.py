@@ -80,3 +80,20 @@ def test_values_far_above_the_rest_keep_the_others_exact(P, orc, kind, views):
     assert 0 < reached.sum() < reached.size // 2
     assert _rel(got[reached], want[reached]) < 1e-4
     assert _rel(got[~reached], want[~reached]) < 1e-4
+
+
+@pytest.mark.parametrize("kind", ["siddon", "interp"])
+@pytest.mark.parametrize("n", [(148, 120, 122), (156, 120, 122)])    # 1216 and 1280 bricks of 8 planes
+@pytest.mark.parametrize("det,pix", [((45, 61), (1.5, 0.9)), ((40, 52), (1.2, 1.2)), ((60, 50), (0.6, 1.0))])
+def test_adjoint_wide_column_groups(P, orc, n, det, pix, kind):
+    """Short columns (one and two row classes: groups of twice the columns per
+    voxel) and three row classes (single groups), on both sides of the brick
+    height's rule.  Tolerance: the parity bar above."""
+    geo = Geometry(DSD=600.0, DSO=400.0, nVoxel=n, dVoxel=(1.0, 1.0, 1.0), nDetector=det, dDetector=pix,
+                   offOrigin=(0.4, -0.3, 0.6), offDetector=(0.3, -0.2))
+    ang = synth.circular_angles(33) + 0.013
+    rng = np.random.Generator(np.random.PCG64(7 * det[0] + n[0]))
+    y = rng.standard_normal((33,) + det).astype(np.float32)
+    got = P.Plan(geo, ang).backproject(torch.from_numpy(y).cuda(), kind=kind)
+    want = orc.backward(geo, ang, y.astype(np.float64), kind)
+    assert _rel(got.cpu().numpy().astype(np.float64), want) < 1e-4
