@@ -157,8 +157,11 @@ k_backward_fdk(const float* __restrict__ proj, float* __restrict__ vol, const Vi
 
     if (tid < min(2 * FDK_TAB, nviews)) fb[tid] = fdk_box(tab[view0 + tid], lo, hi, det, W_MAX);
     __syncthreads();
-    FdkBox next = get(0);
-    fetch(0, next);
+    FdkBox next = {0, 0, 0, 0, FDK_NONE};
+    if (nviews > 0) {   // (a call without views only scales the volume: fb holds nothing, and proj may be null)
+        next = get(0);
+        fetch(0, next);
+    }
     for (int k = 0; k < nviews; ++k) {
         const FdkBox f = next;
         float* bq = box[k & 1];

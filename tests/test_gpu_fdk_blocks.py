@@ -69,3 +69,18 @@ def test_flatten_slices(P, orc, nv, nu, views):
     got = plan.flatten_curved(torch.from_numpy(q).cuda(), cd).cpu().numpy().astype(np.float64)
     want = orc.flatten_curved(geo, cd, q)
     assert _rel(got, want) < 1e-5
+
+
+@pytest.mark.parametrize("kind", ["fdk", "siddon", "interp"])
+@pytest.mark.parametrize("beta", [0.0, 2.0])
+def test_call_without_views(P, kind, beta):
+    """A range of no views scales the volume by beta and reads no projection
+    (none is given), also right after a call whose footprints are still in LDS."""
+    geo = Geometry(DSD=900.0, DSO=600.0, nVoxel=(17, 35, 33), dVoxel=(1.0, 1.0, 1.0), nDetector=(50, 75),
+                   dDetector=(0.9, 0.9))
+    plan = P.Plan(geo, synth.circular_angles(20))
+    y = torch.from_numpy(np.random.Generator(np.random.PCG64(53)).random((20, 50, 75)).astype(np.float32)).cuda()
+    vol = plan.backproject(y, kind=kind)
+    want = beta * vol
+    plan.backproject(torch.empty((0, 50, 75), device="cuda"), out=vol, kind=kind, beta=beta, view0=20, nviews=0)
+    assert torch.equal(vol, want)
