@@ -231,8 +231,8 @@ __device__ __forceinline__ void pixel_order(GroupLds<GV>& G, int g, float pu, fl
 
 // Pixel p of view g's order; false when the index falls on padding.  The
 // quotients come from FP32 reciprocals: floor((i + 1/2) r), r = fl(1/n), is
-// i div n for every i < 2^22.  (A footprint of more pixels than that, of a
-// voxel that covers thousands, is corrected by an exact remainder step.)
+// i div n for every i < 2^22.  (In a footprint of more pixels than that, of a
+// voxel that covers thousands, both are corrected by an exact remainder step.)
 template <bool SIDDON, int GV>
 __device__ __forceinline__ bool group_pixel(const GroupLds<GV>& G, int g, int p, int& iu, int& iv)
 {
@@ -240,13 +240,18 @@ __device__ __forceinline__ bool group_pixel(const GroupLds<GV>& G, int g, int p,
     const int ku = __builtin_amdgcn_readfirstlane(G.ku[g]), kv = __builtin_amdgcn_readfirstlane(G.kv[g]);
     const int wide = SIDDON ? 1 : __builtin_amdgcn_readfirstlane(G.wide[g]);
     const int hp = __builtin_amdgcn_readfirstlane(G.hp[g]), per = wide * ku * kv * hp;
+    const bool large = G.pre[g + 1] - G.pre[g] > (1 << 16);
     int cg = (int)(((float)p + 0.5f) * G.rcol[g]);
-    if (G.pre[g + 1] - G.pre[g] > (1 << 16)) {
+    if (large) {
         const int rem = p - cg * per;
         cg += rem >= per ? 1 : (rem < 0 ? -1 : 0);
     }
     int r = p - cg * per;
-    const int ab = (int)(((float)r + 0.5f) * G.rrow[g]);
+    int ab = (int)(((float)r + 0.5f) * G.rrow[g]);
+    if (large) {
+        const int rem = r - ab * hp;
+        ab += rem >= hp ? 1 : (rem < 0 ? -1 : 0);
+    }
     r -= ab * hp;
     const int a = (ab * G.rk[g]) >> 16;
     const int b = ab - a * wide * ku;
