@@ -355,17 +355,17 @@ __device__ __forceinline__ int group_scale(GroupLds<GV>& G, const ViewGeo* __res
         ys += G.red[1][i];
     }
     float F = 0.0f, N = 0.0f;
-    int npx = 0;
+    float npx = 0.0f;   // (a view holds < 2^28 pixels; a group may hold more than an int32)
 #pragma unroll
     for (int g = 0; g < GV; ++g) {
         F = fmaxf(F, G.f[g]);
         N += G.most[g];
-        npx += G.w[g] * G.h[g];
+        npx += (float)(G.w[g] * G.h[g]);
     }
     if (!(ym > 0.0f)) return 0;
     ex[0] = ex[1] = fixed_exp(N, ym);
     if (ys <= 0x1.fffffep127f) ex[0] = ex[1] = max(ex[0], fixed_exp(F, ys));
-    cut = ys / (float)npx * 8.0f;
+    cut = ys / npx * 8.0f;
     if (cut < ym && cut > 0.0f) ex[0] = max(ex[0], fixed_exp(N, cut));
     else cut = CTMI_INF;
     return __builtin_amdgcn_readfirstlane(G.pre[GV]);
