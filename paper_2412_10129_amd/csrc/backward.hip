@@ -489,8 +489,9 @@ k_backward_siddon(const float* __restrict__ proj, float* __restrict__ vol, const
                 float anb = __builtin_fmaf(qb, B.inv, B.c), anc = __builtin_fmaf(qc, C.inv, C.c);
                 // The cell's LDS address is kept in FP32 as a multiple of 2^-149 (a
                 // denormal has its integer as bits; exact), so that a crossing
-                // moves it by a fused multiply-add with the axis' step.  Empty
-                // second and third segments are added too (VALU bounds the walk,
+                // moves it by a fused multiply-add with the axis' step.  No
+                // crossing lies before acur (ordered_cell), so the segments
+                // need no lower bound.  Empty second and third ones are added too (VALU bounds the walk,
                 // and a test costs more than the LDS atomic of a zero): 256^3 x 90
                 // views on 512^2 8.25 ms with integer offsets and tests, 7.98 with
                 // the tests, 7.68 so.

@@ -307,19 +307,23 @@ __device__ __forceinline__ int entry_cell(float S, float d, float a, int step, i
     return i;
 }
 
-// Cell at parameter a along one axis in the walks' crossing order: the cell
-// entered at a (on a plane, the one the ray moves into), moved back by one
-// when the FP32 crossing parameter of the plane through which the ray enters
-// that cell lies beyond a, then clamped to [lo, hi - 1].  For a ray (nearly)
-// parallel to an axis's planes whose FP32 position rounds onto one of them,
-// the position and the crossing parameters disagree; the walks step by the
-// crossing parameters, so their start cells must follow them too (the
-// forward walk and each adjoint brick then split the ray at the same plane).
+// Cell at parameter a along one axis in the walks' crossing order, clamped to
+// [lo, hi - 1]: the plane nearest to the FP32 position at a lies behind the ray
+// when its FP32 crossing parameter is at or before a, and ahead of it otherwise.
+// For a ray (nearly) parallel to an axis's planes whose position rounds onto or
+// past one of them, the position and the crossing parameters disagree (by a
+// fraction of a cell: half a unit in the last place of S inv is 2^-24 S cells);
+// the walks step by the crossing parameters, so their start cells must follow
+// them too: the forward walk and each adjoint brick then split the ray at the
+// same plane, no crossing lies before a walk's start, and the forward's box test
+// sees the cell that the walk reaches.
 __device__ __forceinline__ int ordered_cell(const SiddonAxis& ax, float S, float d, float a, int lo, int hi)
 {
-    const float x = __builtin_fmaf(a, d, S);
-    int i = ax.step < 0 ? (int)__builtin_ceilf(x) - 1 : (int)__builtin_floorf(x);
-    if (ax.step != 0 && plane_alpha(ax, (float)(i + (ax.step < 0))) > a) i -= ax.step;
+    const float x = __builtin_fmaf(a, d, S), r = __builtin_rintf(x);
+    const bool ahead = __builtin_fmaf(r, ax.inv, ax.c) > a;
+    // (a parallel ray crosses no plane: the cell that holds x)
+    const bool below = ax.step == 0 ? x < r : ahead == (ax.step > 0);
+    int i = (int)r - (below ? 1 : 0);
     i = i < lo ? lo : i;
     i = i > hi - 1 ? hi - 1 : i;
     return i;

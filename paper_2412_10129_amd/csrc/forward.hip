@@ -739,8 +739,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CTMI_F
         }
         const int n = idle ? 0 : k1 - k0 + 1, kf = dir > 0 ? k0 : k1;   // layers, and the first in the direction of travel
         if (inbox && !wave_steep) {
-            // The three-cell form, 27 VALU per layer.  o is the LDS address of the
-            // ray's cell in FP32 (lds_at); plane numbers and steps are exact too.
+            // The three-cell form, 26 VALU per layer.  o is the LDS address of the
+            // ray's cell in FP32 (lds_at); plane numbers and steps are exact too.  No
+            // crossing lies before acur (ordered_cell), so no length is negative.
             const float DB = __int_as_float(4 * st_b), DC = __int_as_float(4 * st_c);
             const float DA = dir > 0 ? __int_as_float(4 * st_a) : -__int_as_float(4 * st_a);
             const float fdir = (float)dir, sb = (float)B.step, sc = (float)C.step;
