@@ -887,7 +887,19 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CTMI_F
     InterpRay r;
     const bool has = interp_ray(tab64[view0 + view], active ? iu : 0, active ? iv : 0, v, ds, 1.0f / ds, r) && active;
     int k = has ? r.k0 : 0;
-    const int k1 = has ? r.k1 : -1;
+    int k1 = has ? r.k1 : -1;
+    if (ds > fminf(v.hx, fminf(v.hy, v.hz))) {
+        // the samples one step beyond the support lie further out than the
+        // boxes' margin of one voxel: they add nothing, so the range ends here
+        auto outside = [&](int j) {
+            float p[3];
+            interp_pos(r, j, p);
+            return p[0] < -2.0f || p[1] < -2.0f || p[2] < -2.0f || p[0] >= (float)(v.nx + 1) ||
+                   p[1] >= (float)(v.ny + 1) || p[2] >= (float)(v.nz + 1);
+        };
+        while (k <= k1 && outside(k)) ++k;
+        while (k <= k1 && outside(k1)) --k1;
+    }
     // sample k sits at base + (k - kc) st; along the dominant axis the slab
     // boundary plane P is reached at (k - kc) = (P - base_a) / st_a
     const float sa = a == 0 ? r.st[0] : (a == 1 ? r.st[1] : r.st[2]);

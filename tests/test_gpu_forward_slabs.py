@@ -74,3 +74,17 @@ def test_rays_along_z(P, orc, n, pix, kind):
     k = np.arange(6)
     views = synth.views(geo, np.stack([0.3 + k, 1.3 + 0.02 * k, 0.1 * k], axis=1))
     _check(P, orc, geo, views, kind, 43)
+
+
+@pytest.mark.parametrize("accuracy", [0.9, 1.0, 1.5, 2.0, 3.7])
+@pytest.mark.parametrize("h", [(1.0, 1.0, 1.0), (2.5, 1.0, 1.2)])
+def test_steps_of_a_voxel_and_more(P, orc, accuracy, h):
+    """Interpolation steps up to several voxels: the samples one step beyond the
+    volume at either end of a ray lie outside every staged box and add nothing."""
+    geo = Geometry(DSD=900.0, DSO=600.0, nVoxel=(30, 37, 43), dVoxel=h, nDetector=(61, 66), dDetector=(1.1, 0.9),
+                   offOrigin=(0.3, -0.4, 0.2), offDetector=(0.2, -0.3), accuracy=accuracy)
+    ang = np.array([0.0, 0.013, 0.4, 0.78, 1.2, np.pi / 2, 2.36, 3.2, 4.4, 5.5])
+    _check(P, orc, geo, ang, "interp", 47)
+    y = np.random.Generator(np.random.PCG64(48)).random((len(ang),) + geo.nDetector).astype(np.float32)
+    got = P.Plan(geo, ang).backproject(torch.from_numpy(y).cuda(), kind="interp")
+    assert _rel(got.cpu().numpy().astype(np.float64), orc.backward(geo, ang, y.astype(np.float64), "interp")) < 1e-4
