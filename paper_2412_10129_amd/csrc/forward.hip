@@ -1005,14 +1005,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CTMI_F
             next = slab_of(si + 1);
             if (next.flags & BOX_SOME) fetch_box<PF>(pf, vol, v, next);
         }
-        // byte offsets over the whole grid and its margins stay exact FP32 integers
-        const bool exact = (int64_t)b.wz * (v.nz + 4) + (int64_t)b.w * (v.ny + 4) + v.nx + 4 < 1 << 22;
-        if (fits && !clipped && mono && exact) {
+        if (fits && !clipped && mono) {
             // fast path: every sample of the slab has its 2x2x2 corners in the box.
             // The LDS address is formed in FP32 as a multiple of 2^-149 (see
-            // lds_read): the box's origin is the first product's addend.
+            // lds_at).
             const float SX = __int_as_float(4), SY = __int_as_float(4 * b.w), SZ = __int_as_float(4 * b.wz);
-            const float C0 = (float)((int)lds_address(box) - 4 * (b.o[0] + b.w * b.o[1] + b.wz * b.o[2])) * 0x1p-149f;
             const unsigned o01 = 4 * (unsigned)b.w, o10 = 4 * (unsigned)b.wz, o11 = o10 + o01;
             // samples k..kl by their offset j = k - kc from the ray's anchor, an
             // exact FP32 integer (interp_pos's position, without an int->float
@@ -1020,19 +1017,31 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CTMI_F
             // offsets are below its sample count, far below 2^24, so the FP32
             // counter steps exactly and the loop ends.
             const float jl = (float)(kl - r.kc);
-            for (float j = (float)(k - r.kc); k <= kl && j <= jl; j += 1.0f) {
-                float p[3];
+            auto samples = [&](float ox, float oy, float oz, float C) {
+                for (float j = (float)(k - r.kc); k <= kl && j <= jl; j += 1.0f) {
+                    float p[3];
 #pragma unroll
-                for (int i = 0; i < 3; ++i) p[i] = __builtin_fmaf(j, r.st[i], r.base[i]);
-                const float fx = __builtin_floorf(p[0]), fy = __builtin_floorf(p[1]), fz = __builtin_floorf(p[2]);
-                const unsigned off =
-                    __float_as_uint(__builtin_fmaf(fz, SZ, __builtin_fmaf(fy, SY, __builtin_fmaf(fx, SX, C0))));
-                const lds_float *r0 = lds_at(off), *r1 = lds_at(off + o01), *r2 = lds_at(off + o10), *r3 = lds_at(off + o11);
-                const float ax = p[0] - fx, ay = p[1] - fy, az = p[2] - fz;
-                const float c00 = lerp1(ax, r0[0], r0[1]), c01 = lerp1(ax, r1[0], r1[1]);
-                const float c10 = lerp1(ax, r2[0], r2[1]), c11 = lerp1(ax, r3[0], r3[1]);
-                acc += lerp1(az, lerp1(ay, c00, c01), lerp1(ay, c10, c11));
-            }
+                    for (int i = 0; i < 3; ++i) p[i] = __builtin_fmaf(j, r.st[i], r.base[i]);
+                    const float fx = __builtin_floorf(p[0]), fy = __builtin_floorf(p[1]), fz = __builtin_floorf(p[2]);
+                    const unsigned off = __float_as_uint(
+                        __builtin_fmaf(fz - oz, SZ, __builtin_fmaf(fy - oy, SY, __builtin_fmaf(fx - ox, SX, C))));
+                    const lds_float *r0 = lds_at(off), *r1 = lds_at(off + o01), *r2 = lds_at(off + o10),
+                                    *r3 = lds_at(off + o11);
+                    const float ax = p[0] - fx, ay = p[1] - fy, az = p[2] - fz;
+                    const float c00 = lerp1(ax, r0[0], r0[1]), c01 = lerp1(ax, r1[0], r1[1]);
+                    const float c10 = lerp1(ax, r2[0], r2[1]), c11 = lerp1(ax, r3[0], r3[1]);
+                    acc += lerp1(az, lerp1(ay, c00, c01), lerp1(ay, c10, c11));
+                }
+            };
+            const int at = (int)lds_address(box);
+            // The box's origin is the first product's addend where byte offsets
+            // over the whole grid and its margins stay exact FP32 integers;
+            // elsewhere (some thousand planes with wide boxes) it is taken off
+            // each coordinate, three instructions per sample more.
+            if ((int64_t)b.wz * (v.nz + 4) + (int64_t)b.w * (v.ny + 4) + v.nx + 4 < 1 << 22)
+                samples(0.0f, 0.0f, 0.0f, (float)(at - 4 * (b.o[0] + b.w * b.o[1] + b.wz * b.o[2])) * 0x1p-149f);
+            else
+                samples((float)b.o[0], (float)b.o[1], (float)b.o[2], (float)at * 0x1p-149f);
             k = max(k, kl + 1);
         } else {
             for (; k <= kl; ++k) {

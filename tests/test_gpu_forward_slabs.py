@@ -88,3 +88,14 @@ def test_steps_of_a_voxel_and_more(P, orc, accuracy, h):
     y = np.random.Generator(np.random.PCG64(48)).random((len(ang),) + geo.nDetector).astype(np.float32)
     got = P.Plan(geo, ang).backproject(torch.from_numpy(y).cuda(), kind="interp")
     assert _rel(got.cpu().numpy().astype(np.float64), orc.backward(geo, ang, y.astype(np.float64), "interp")) < 1e-4
+
+
+@pytest.mark.parametrize("nz", [2400, 3600])
+@pytest.mark.parametrize("kind", ["siddon", "interp"])
+def test_tall_grids_under_wide_boxes(P, orc, nz, kind):
+    """Planes of 1600 words and more in the boxes: byte offsets over the whole grid
+    are exact FP32 integers up to about 2600 planes, and box-relative above.  The
+    rays cross the highest planes, where inexact offsets would show."""
+    geo = Geometry(DSD=5000.0, DSO=2500.0, nVoxel=(nz, 60, 90), dVoxel=(1.0, 1.0, 1.0), nDetector=(40, 30),
+                   dDetector=(0.6, 10.0), offDetector=(0.9 * nz, 0.3))
+    _check(P, orc, geo, np.array([0.0, 0.05, 0.7, 1.2, np.pi / 2, 3.2, 4.6]), kind, 49)
