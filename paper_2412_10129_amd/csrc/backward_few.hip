@@ -110,7 +110,7 @@ __device__ __forceinline__ int fixed_exp(float cmax, float m)
     return 30 - ec - em + (a * b < 0.5f ? 1 : 0);
 }
 
-// |y| for finite y, 0 for NaN and infinities (those rays are handled by
+// y for finite y, 0 for NaN and infinities (those rays are handled by
 // k_nonfinite after the accumulation)
 __device__ __forceinline__ float finite_or_zero(float y)
 {
