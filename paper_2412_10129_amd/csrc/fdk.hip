@@ -195,7 +195,8 @@ k_backward_fdk(const float* __restrict__ proj, float* __restrict__ vol, const Vi
             const int C = (int)(unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)bq +
                           4 * (iu - f.u0 - f.v0 * P);
             const float Cf = (float)C * 0x1p-149f, Pf = __int_as_float(4 * P);
-            const float wu0 = 1.0f - au;
+            // (weights, not s0 + av (s1 - s0): an infinite pixel stays an infinity)
+            const float wu0 = wt * (1.0f - au), wu1 = wt * au;
 #pragma unroll
             for (int z = 0; z < ZC; ++z) {
                 const float fv = __builtin_fmaf((float)z, dfv, fv0);
@@ -203,13 +204,13 @@ k_backward_fdk(const float* __restrict__ proj, float* __restrict__ vol, const Vi
                 const float av = fv - flv;
                 const auto* t = (const __attribute__((address_space(3))) float*)(uintptr_t)__float_as_uint(
                     __builtin_fmaf(flv, Pf, Cf));
-                const float s0 = __builtin_fmaf(wu0, t[0], au * t[1]);
-                const float s1 = __builtin_fmaf(wu0, t[P], au * t[P + 1]);
-                acc[z] = __builtin_fmaf(wt, __builtin_fmaf(av, s1 - s0, s0), acc[z]);
+                const float s0 = __builtin_fmaf(wu0, t[0], wu1 * t[1]);
+                const float s1 = __builtin_fmaf(wu0, t[P], wu1 * t[P + 1]);
+                acc[z] = __builtin_fmaf(av, s1, __builtin_fmaf(1.0f - av, s0, acc[z]));
             }
         } else {
-            const float wu0 = (unsigned)iu < (unsigned)det.nu ? 1.0f - au : 0.0f;
-            const float wu1 = (unsigned)(iu + 1) < (unsigned)det.nu ? au : 0.0f;
+            const float wu0 = (unsigned)iu < (unsigned)det.nu ? wt * (1.0f - au) : 0.0f;
+            const float wu1 = (unsigned)(iu + 1) < (unsigned)det.nu ? wt * au : 0.0f;
             if (wu0 == 0.0f && wu1 == 0.0f) continue;
             const int u0 = min(max(iu, 0), det.nu - 1), u1 = min(max(iu + 1, 0), det.nu - 1);
             const float* pk = proj + (int64_t)k * det.nv * det.nu;
@@ -226,7 +227,7 @@ k_backward_fdk(const float* __restrict__ proj, float* __restrict__ vol, const Vi
                 const float* r1 = pk + (int64_t)v1 * det.nu;
                 const float s0 = __builtin_fmaf(wu0, r0[u0], wu1 * r0[u1]);
                 const float s1 = __builtin_fmaf(wu0, r1[u0], wu1 * r1[u1]);
-                acc[z] = __builtin_fmaf(wt, __builtin_fmaf(wv0, s0, wv1 * s1), acc[z]);
+                acc[z] = __builtin_fmaf(wv1, s1, __builtin_fmaf(wv0, s0, acc[z]));
             }
         }
     }

@@ -84,3 +84,25 @@ def test_call_without_views(P, kind, beta):
     want = beta * vol
     plan.backproject(torch.empty((0, 50, 75), device="cuda"), out=vol, kind=kind, beta=beta, view0=20, nviews=0)
     assert torch.equal(vol, want)
+
+
+@pytest.mark.parametrize("n,det,pix", [((17, 35, 33), (50, 75), 0.9), ((18, 20, 22), (200, 230), 0.25)])
+def test_infinite_pixel_stays_an_infinity(P, orc, n, det, pix):
+    """Staged and read from global memory: voxels that the pixels reach with some
+    weight hold their infinity, the sum's other voxels are finite, none is NaN.
+    (A FP32 position may lie 1e-4 of a pixel to the other side of the tap's edge:
+    weights from 0 to 1e-3 are left open.)"""
+    geo = Geometry(DSD=900.0, DSO=600.0, nVoxel=n, dVoxel=(1.0, 1.0, 1.0), nDetector=det, dDetector=(pix, pix),
+                   offOrigin=(0.3, -0.4, 0.2), offDetector=(0.2, -0.3))
+    ang = synth.circular_angles(7) + 0.013
+    y = np.random.Generator(np.random.PCG64(54)).standard_normal((7,) + det).astype(np.float32)
+    mark = np.zeros(y.shape)
+    for k, v, u in ((1, det[0] // 2, det[1] // 2), (4, det[0] // 2 + 1, det[1] // 2 - 3)):
+        y[k, v:v + 4, u:u + 4] = np.inf
+        mark[k, v:v + 4, u:u + 4] = 1.0
+    w = orc.bfdk(geo, ang, mark)
+    got = P.Plan(geo, ang).backproject(torch.from_numpy(y).cuda(), kind="fdk").cpu().numpy()
+    assert (w > 1e-3).sum() > 20
+    assert not np.isnan(got).any()
+    assert np.isposinf(got[w > 1e-3]).all()
+    assert np.isfinite(got[w == 0.0]).mean() > 0.99 and np.isfinite(got).any()
