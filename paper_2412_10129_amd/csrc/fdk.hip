@@ -9,7 +9,7 @@ namespace ctmi {
 namespace {
 
 // ------------------------------------------------------------ backprojector
-// A workgroup owns 16 x 16 voxel columns of ZC voxels, one column per thread;
+// A workgroup owns 16 x 16 voxel columns of ZC (16 or 8) voxels, one column per thread;
 // every view of the call is accumulated in registers, so each output voxel is
 // written once.  On a circular orbit W and fu do not depend on z, so per view a
 // thread computes one reciprocal and then walks its ZC voxels along v.
@@ -19,14 +19,15 @@ namespace {
 // zero outside the detector, so that the taps need neither clamps nor zero
 // weights: rows of four pixels per thread, the next view's loaded into
 // registers while this one is summed, one barrier per view.  A footprint wider
-// than the row pitch (or 64 pixels) or higher than FDK_H rows, or a block with a
-// corner not in front of the source, reads its view from global memory instead.
+// than the row pitch P (or four pixels per staging thread) or higher than H rows, or a
+// block with a corner not in front of the source, reads its view from global memory
+// instead; launch_backward_fdk chooses ZC, P and H so that few do.
 //
 // A read takes 32 lanes (8 x 4 columns: a wave is 8 x 8 columns) from 32 banks; row
 // pitches of 16 modulo 32 keep neighbours that share a column but not a row apart
 // (a model of the reads gives 1.02 clocks per 32 lanes; 16 x 2 columns 1.3, 32 x 1
-// 1.85; a pitch of 68 with 16 x 2 columns measured 19.6 ms against 18.2).  The narrow
-// pitch leaves LDS for eight workgroups per CU.  The tap's LDS address is formed in
+// 1.85; a pitch of 68 with 16 x 2 columns measured 19.6 ms against 18.2).  A pitch of
+// 48 with 48 rows leaves LDS for eight workgroups per CU.  The tap's LDS address is formed in
 // FP32 as a multiple of 2^-149 (a denormal has its integer as bits): one fused
 // multiply-add per voxel.
 //
@@ -35,9 +36,6 @@ namespace {
 // columns staged pixel by pixel between barriers, with clamped taps at the edges.
 // ZC 8: 20.5 ms, 32: 17.5 (with five waves per SIMD; small volumes want the smaller).
 constexpr int FDK_T = 16;                       // voxel columns per side
-constexpr int FDK_H = 48;                       // most staged rows
-constexpr int FDK_M = FDK_H / 16;               // staging passes of 16 rows
-constexpr int FDK_NARROW = 48, FDK_WIDE = 80;   // LDS row pitches
 constexpr int FDK_TAB = 16;                     // views whose footprints are formed together
 
 typedef float fdk_quad __attribute__((ext_vector_type(4), aligned(4)));
@@ -52,7 +50,7 @@ struct FdkBox {
 };
 
 __device__ __forceinline__ FdkBox fdk_box(const ViewGeo& g, const float lo[3], const float hi[3], const DetDims& det,
-                                          int width)
+                                          int width, int height, int pass)
 {
     float umin = CTMI_INF, umax = -CTMI_INF, vmin = CTMI_INF, vmax = -CTMI_INF, wmin = CTMI_INF;
 #pragma unroll
@@ -79,26 +77,27 @@ __device__ __forceinline__ FdkBox fdk_box(const ViewGeo& g, const float lo[3], c
     // a voxel of the block projects inside the corners' bounding box, so its
     // taps floor(u), floor(u) + 1 lie in [floor(umin) - 1, floor(umax) + 2] (a pixel
     // to spare for rounding), and the same for v
-    if (umax - umin > (float)width || vmax - vmin > (float)FDK_H) return f;
+    if (umax - umin > (float)width || vmax - vmin > (float)height) return f;
     f.u0 = (int)__builtin_floorf(umin) - 1;
     f.v0 = (int)__builtin_floorf(vmin) - 1;
     f.w = (int)__builtin_floorf(umax) + 3 - f.u0;
     f.h = (int)__builtin_floorf(vmax) + 3 - f.v0;
-    if (f.w > width || f.h > FDK_H) return f;
-    // (loads come in whole quads and passes of 16 rows)
-    const bool inside = f.u0 >= 0 && f.v0 >= 0 && f.u0 + ((f.w + 3) & ~3) <= det.nu && f.v0 + ((f.h + 15) & ~15) <= det.nv;
+    if (f.w > width || f.h > height) return f;
+    // (loads come in whole quads and passes of several rows)
+    const bool inside = f.u0 >= 0 && f.v0 >= 0 && f.u0 + ((f.w + 3) & ~3) <= det.nu && f.v0 + (f.h + pass - 1) / pass * pass <= det.nv;
     f.how = inside ? FDK_INSIDE : FDK_EDGE;
     return f;
 }
 
-template <int ZC, int P>
-__global__ void __launch_bounds__(FDK_T* FDK_T) __attribute__((amdgpu_waves_per_eu(P == FDK_NARROW ? 7 : 5, 8)))
+template <int ZC, int P, int H, int WPE>
+__global__ void __launch_bounds__(FDK_T* FDK_T) __attribute__((amdgpu_waves_per_eu(WPE, 8)))
 k_backward_fdk(const float* __restrict__ proj, float* __restrict__ vol, const ViewGeo* __restrict__ tab, int view0,
                int nviews, VolDims v, DetDims det, int nbx, int nby, float beta)
 {
-    __shared__ __attribute__((aligned(16))) float box[2][FDK_H * P];
+    __shared__ __attribute__((aligned(16))) float box[2][H * P];
     __shared__ FdkBox fb[2 * FDK_TAB];   // ring: views k and on, a half formed at a time
-    constexpr int W_MAX = P < 64 ? P : 64;   // 16 threads stage a row
+    // threads that stage a row, rows and passes of a footprint, its widest row
+    constexpr int TPR = P <= 80 ? 16 : 32, RP = FDK_T * FDK_T / TPR, M = H / RP, W_MAX = P < 4 * TPR ? P : 4 * TPR;
     const int b = (int)blockIdx.x;
     const int bx = b % nbx, by = (b / nbx) % nby, bz = b / (nbx * nby);
     const int tid = (int)threadIdx.x;
@@ -125,24 +124,24 @@ k_backward_fdk(const float* __restrict__ proj, float* __restrict__ vol, const Vi
         f.how = __builtin_amdgcn_readfirstlane(m.how);
         return f;
     };
-    const int sr = tid >> 4, sc = (tid & 15) * 4;   // this thread's row (+ 16 m) and first column of a footprint
+    const int sr = tid / TPR, sc = tid % TPR * 4;   // this thread's row (+ RP m) and first column of a footprint
     const unsigned soff = (unsigned)sr * (unsigned)det.nu + (unsigned)sc;
-    fdk_quad pf[FDK_M];
+    fdk_quad pf[M];
     auto fetch = [&](int k, const FdkBox& f) {
         if (f.how < FDK_EDGE || sc >= f.w) return;
         const float* pk = proj + (int64_t)k * det.nv * det.nu;
         if (f.how == FDK_INSIDE) {
             const float* pq = pk + ((int64_t)f.v0 * det.nu + f.u0);
 #pragma unroll
-            for (int m = 0; m < FDK_M; ++m)
-                if (16 * m < f.h) pf[m] = *reinterpret_cast<const fdk_quad*>(pq + (int64_t)(16 * m) * det.nu + soff);
+            for (int m = 0; m < M; ++m)
+                if (RP * m < f.h) pf[m] = *reinterpret_cast<const fdk_quad*>(pq + (int64_t)(RP * m) * det.nu + soff);
             return;
         }
 #pragma unroll
-        for (int m = 0; m < FDK_M; ++m) {
-            const int u = f.u0 + sc, vv = f.v0 + sr + 16 * m;
+        for (int m = 0; m < M; ++m) {
+            const int u = f.u0 + sc, vv = f.v0 + sr + RP * m;
             pf[m] = fdk_quad{0.0f, 0.0f, 0.0f, 0.0f};
-            if (16 * m < f.h && (unsigned)vv < (unsigned)det.nv) {
+            if (RP * m < f.h && (unsigned)vv < (unsigned)det.nv) {
                 const float* row = pk + (int64_t)vv * det.nu;
                 if (u >= 0 && u + 3 < det.nu) {
                     pf[m] = *reinterpret_cast<const fdk_quad*>(row + u);
@@ -155,7 +154,7 @@ k_backward_fdk(const float* __restrict__ proj, float* __restrict__ vol, const Vi
         }
     };
 
-    if (tid < min(2 * FDK_TAB, nviews)) fb[tid] = fdk_box(tab[view0 + tid], lo, hi, det, W_MAX);
+    if (tid < min(2 * FDK_TAB, nviews)) fb[tid] = fdk_box(tab[view0 + tid], lo, hi, det, W_MAX, H, RP);
     __syncthreads();
     FdkBox next = {0, 0, 0, 0, FDK_NONE};
     if (nviews > 0) {   // (a call without views only scales the volume: fb holds nothing, and proj may be null)
@@ -167,11 +166,11 @@ k_backward_fdk(const float* __restrict__ proj, float* __restrict__ vol, const Vi
         float* bq = box[k & 1];
         // (the half that held the last FDK_TAB views; read again FDK_TAB - 1 barriers from here)
         if (k > 0 && (k & (FDK_TAB - 1)) == 0 && tid < min(FDK_TAB, nviews - k - FDK_TAB))
-            fb[(k + FDK_TAB + tid) & (2 * FDK_TAB - 1)] = fdk_box(tab[view0 + k + FDK_TAB + tid], lo, hi, det, W_MAX);
+            fb[(k + FDK_TAB + tid) & (2 * FDK_TAB - 1)] = fdk_box(tab[view0 + k + FDK_TAB + tid], lo, hi, det, W_MAX, H, RP);
         if (f.how >= FDK_EDGE && sc < f.w) {
 #pragma unroll
-            for (int m = 0; m < FDK_M; ++m)
-                if (16 * m < f.h) *reinterpret_cast<fdk_quad16*>(&bq[(sr + 16 * m) * P + sc]) = pf[m];
+            for (int m = 0; m < M; ++m)
+                if (RP * m < f.h) *reinterpret_cast<fdk_quad16*>(&bq[(sr + RP * m) * P + sc]) = pf[m];
         }
         __syncthreads();   // (also: the other buffer's reads are done)
         if (k + 1 < nviews) {
@@ -630,28 +629,41 @@ __global__ void __launch_bounds__(256) k_fdk_filter(const float* in, float* out,
 
 }  // namespace
 
+// Planes per block, row pitch and rows of the staged footprint, by the pixels that a
+// block covers: across it at the volume's near side (w), and the rows of 16 or 8
+// planes at its centre, with the shift of the detector's last row over the
+// block's depth (h).  The lines lie where neighbours measured equal, or where one
+// starts to read views from global memory (which costs two to three times the
+// staged kernel).  90 views on 256 x 256 voxels of 0.5 mm (us; z-heights of
+// 0.85 / 0.9 / 1.75 mm on pixels of 0.512): 16 planes 475 / 645 / 968, 8 planes 504 / 485 / 349,
+// 8 planes and 96 rows 683 / 634 / 413; 128 planes of 512 x 512 x 2 mm, 120 views: 7.7, 4.6
+// and 3.1 ms.  Pixels of 0.45 / 0.4 / 0.3 / 0.27: pitch 48 308 / 351 / 1009 / 1154, pitch 80
+// 371 / 390 / 403 / 1018, pitch 144 with 8 planes 496 / 531 / 554 / 579; pixels of 0.6 x 0.27 and 0.24:
+// pitch 80 570 and 1114, pitch 144 with 16 planes 421 and 423.  (Blocks of 32 x 8 columns with up
+// to 2560 pixels of any shape, as before: 1060 / 1051 / 840; 7.8 ms; 692 / 774 / 1366 / 1427; 832 and 953.)
 hipError_t launch_backward_fdk(const Plan& p, const float* proj, float* vol, int64_t view0, int64_t nviews,
                                float beta, hipStream_t s)
 {
     const int nbx = (p.vol.nx + FDK_T - 1) / FDK_T;
     const int nby = (p.vol.ny + FDK_T - 1) / FDK_T;
-    constexpr int ZC = 16;
-    const int nbz = (p.vol.nz + ZC - 1) / ZC;
-    const unsigned blocks = (unsigned)nbx * nby * nbz;
-    auto run = [&](auto kernel) {
+    auto run = [&](auto kernel, int planes) {
+        const unsigned blocks = (unsigned)nbx * nby * ((p.vol.nz + planes - 1) / planes);
         hipLaunchKernelGGL(kernel, dim3(blocks), dim3(FDK_T * FDK_T), 0, s, proj, vol, p.d_views, (int)view0, (int)nviews,
                            p.vol, p.det, nbx, nby, beta);
+        return hipGetLastError();
     };
-    // pixels per row that a block's diagonal covers at the volume's near side
     const ctmi_geometry& g = p.geo;
-    const double dx = g.dVoxel[2], dy = g.dVoxel[1];
+    const double dx = g.dVoxel[2], dy = g.dVoxel[1], diag = FDK_T * std::hypot(dx, dy);
     const double near = g.DSO - 0.5 * std::hypot(dx * p.vol.nx, dy * p.vol.ny);
-    const bool narrow = near > 0.0 && FDK_T * std::hypot(dx, dy) * g.DSD / (near * g.dDetector[1]) + 4.0 <= FDK_NARROW;
-    if (narrow)
-        run(k_backward_fdk<ZC, FDK_NARROW>);
-    else
-        run(k_backward_fdk<ZC, FDK_WIDE>);
-    return hipGetLastError();
+    const double w = near > 0.0 ? diag * g.DSD / (near * g.dDetector[1]) + 4.0 : 1e30;
+    const double plane = g.dVoxel[0] * g.DSD / (g.DSO * g.dDetector[0]), shift = 0.5 * p.det.nv * diag / g.DSO + 4.0;
+    const double h16 = 16.0 * plane + shift, h8 = 8.0 * plane + shift;
+    if (h8 <= 50.0) {
+        if (w <= 48.0) return h16 <= 48.0 ? run(k_backward_fdk<16, 48, 48, 7>, 16) : run(k_backward_fdk<8, 48, 48, 7>, 8);
+        if (w <= 70.0) return h16 <= 48.0 ? run(k_backward_fdk<16, 80, 48, 5>, 16) : run(k_backward_fdk<8, 80, 48, 5>, 8);
+        return h16 <= 34.0 ? run(k_backward_fdk<16, 144, 32, 4>, 16) : run(k_backward_fdk<8, 144, 32, 4>, 8);
+    }
+    return run(k_backward_fdk<8, 48, 96, 4>, 8);
 }
 
 hipError_t launch_fdk_filter(const Plan& p, int wang, const float* proj, float* out, int64_t view0, int64_t nviews,

@@ -106,3 +106,30 @@ def test_infinite_pixel_stays_an_infinity(P, orc, n, det, pix):
     assert not np.isnan(got).any()
     assert np.isposinf(got[w > 1e-3]).all()
     assert np.isfinite(got[w == 0.0]).mean() > 0.99 and np.isfinite(got).any()
+
+
+# volume, voxel (z, y, x), detector, pixel (v, u), offset (v, u), views; magnification 1.5
+@pytest.mark.parametrize("n,dvox,det,pix,off,views", [
+    ((21, 18, 35), (1.0, 1.0, 1.0), (70, 64), (0.5, 0.9), (0.2, -0.3), 18),     # 8 planes, 48 rows
+    ((8, 33, 17), (2.0, 1.0, 1.0), (50, 70), (0.9, 1.1), (1.3, 0.4), 35),       # thick slices, one layer
+    ((19, 20, 31), (1.0, 1.0, 1.0), (161, 50), (0.2, 0.9), (0.2, -0.3), 17),    # 96 rows
+    ((9, 16, 16), (3.0, 1.0, 1.0), (90, 31), (0.31, 1.0), (-2.0, 5.0), 33),     # 96 rows, cut on two sides
+    ((25, 35, 18), (1.0, 1.0, 1.0), (90, 95), (0.45, 0.58), (0.2, -0.3), 16),   # 80 columns, 8 planes
+    ((33, 31, 18), (1.0, 1.0, 1.0), (52, 170), (1.0, 0.3), (0.2, -0.3), 19),    # 128 columns, 32 rows
+    ((15, 18, 33), (1.0, 1.0, 1.0), (60, 181), (0.5, 0.3), (-1.0, 6.0), 18),    # 128 columns, 8 planes
+    ((15, 35, 33), (1.0, 1.0, 1.0), (60, 260), (0.5, 0.22), (0.2, -0.3), 9),    # some views wider than that
+    ((40, 18, 33), (1.0, 1.0, 1.0), (500, 60), (0.12, 0.9), (0.2, -0.3), 7),    # some blocks higher than 96 rows
+    ((20, 18, 33), (1.0, 1.0, 1.0), (9, 181), (0.45, 0.3), (0.0, 0.0), 9),      # fewer rows than a pass
+])
+def test_backprojector_shapes_of_footprints(P, orc, n, dvox, det, pix, off, views):
+    geo = Geometry(DSD=900.0, DSO=600.0, nVoxel=n, dVoxel=dvox, nDetector=det, dDetector=pix,
+                   offOrigin=(0.3, -0.4, 0.2), offDetector=off)
+    ang = synth.circular_angles(views) + 0.013
+    y = np.random.Generator(np.random.PCG64(55)).standard_normal((views,) + det).astype(np.float32)
+    buf = torch.full((y.size + 514,), float("nan"), device="cuda")   # rows on 4 bytes only, poison around
+    yd = buf[257:257 + y.size].view(y.shape)
+    yd.copy_(torch.from_numpy(y))
+    plan = P.Plan(geo, ang)
+    got = plan.backproject(yd, kind="fdk")
+    assert torch.equal(got, plan.backproject(yd, kind="fdk"))
+    assert _rel(got.cpu().numpy().astype(np.float64), orc.bfdk(geo, ang, y.astype(np.float64))) < 1e-4
