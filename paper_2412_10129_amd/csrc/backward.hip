@@ -212,17 +212,18 @@ struct GroupLds {
 // Not for three row classes and more, whose ku columns fill a wave already
 // (117x203x181 x 37: 2.73 -> 2.76 ms), nor for Siddon, whose walks leave a cell
 // at every step (259x78x51 x 46: 612 -> 635 us).
+constexpr float KMAX = 32.0f;   // most columns and row classes (of 8, rays meet in cells beyond: 96^3 on 8 pixels per voxel 35.1 -> 26.4 ms)
 template <bool SIDDON, int GV>
 __device__ __forceinline__ void pixel_order(GroupLds<GV>& G, int g, float pu, float pv)
 {
     const int w = G.w[g], h = G.h[g];
-    const int ku = min(max((int)__builtin_ceilf(fminf(pu, 16.0f) - 0.1f), 1), 8);
-    const int kv = min(max((int)__builtin_ceilf(fminf(pv, 16.0f) - 0.1f), 1), 8);
+    const int ku = max((int)__builtin_ceilf(fminf(pu, KMAX) - 0.1f), 1);
+    const int kv = max((int)__builtin_ceilf(fminf(pv, KMAX) - 0.1f), 1);
     const int hp = (h + kv - 1) / kv, wide = !SIDDON && kv <= 2 && hp <= 16 ? 2 : 1, per = wide * ku * kv * hp;
     G.ku[g] = ku;
     G.wide[g] = wide;
     G.kv[g] = kv;
-    G.rk[g] = (65536 + wide * ku - 1) / (wide * ku);   // ceil(2^16 / n): i / n for i < 128, n <= 16
+    G.rk[g] = (65536 + wide * ku - 1) / (wide * ku);   // ceil(2^16 / n): i / n for i (n - 1) < 2^16 (i < 1024, n <= 32)
     G.hp[g] = hp;
     G.rcol[g] = 1.0f / (float)per;
     G.rrow[g] = 1.0f / (float)hp;

@@ -97,3 +97,22 @@ def test_adjoint_wide_column_groups(P, orc, n, det, pix, kind):
     got = P.Plan(geo, ang).backproject(torch.from_numpy(y).cuda(), kind=kind)
     want = orc.backward(geo, ang, y.astype(np.float64), kind)
     assert _rel(got.cpu().numpy().astype(np.float64), want) < 1e-4
+
+
+@pytest.mark.parametrize("kind,views", [("siddon", 8), ("siddon", 9), ("siddon", 35), ("interp", 35)])
+@pytest.mark.parametrize("n,det,pix", [
+    (FEW, (210, 330), (0.17, 0.22))])   # row classes beyond 8
+def test_adjoint_of_sparse_and_of_dense_footprints(P, orc, n, det, pix, kind, views):
+    """More than eight pixels per voxel.  Tolerance: the parity bar above."""
+    geo = Geometry(DSD=600.0, DSO=400.0, nVoxel=n, dVoxel=(1.0, 1.0, 1.0), nDetector=det, dDetector=pix,
+                   offOrigin=(0.4, -0.3, 0.6), offDetector=(0.3, -0.2))
+    ang = synth.circular_angles(views) + 0.013
+    rng = np.random.Generator(np.random.PCG64(5 * det[0] + views))
+    y = rng.standard_normal((views,) + det).astype(np.float32)
+    y[rng.random(y.shape) < 0.2] = 0.0
+    y[views // 2] = 0.0
+    plan = P.Plan(geo, ang)
+    got = plan.backproject(torch.from_numpy(y).cuda(), kind=kind)
+    assert torch.equal(got, plan.backproject(torch.from_numpy(y).cuda(), kind=kind))
+    want = orc.backward(geo, ang, y.astype(np.float64), kind)
+    assert _rel(got.cpu().numpy().astype(np.float64), want) < 1e-4
