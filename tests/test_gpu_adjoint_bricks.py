@@ -101,9 +101,9 @@ def test_adjoint_wide_column_groups(P, orc, n, det, pix, kind):
 
 @pytest.mark.parametrize("kind,views", [("siddon", 8), ("siddon", 9), ("siddon", 35), ("interp", 35)])
 @pytest.mark.parametrize("n,det,pix", [
-    (FEW, (210, 330), (0.17, 0.22))])   # row classes beyond 8
+    (FEW, (210, 330), (0.17, 0.22)), (SOME, (14, 130), (8.0, 1.1)), (MANY, (38, 70), (11.0, 2.1))])   # row classes beyond 8; short columns
 def test_adjoint_of_sparse_and_of_dense_footprints(P, orc, n, det, pix, kind, views):
-    """More than eight pixels per voxel.  Tolerance: the parity bar above."""
+    """Column groups of 4 ku, and more than eight pixels per voxel.  Tolerance: the parity bar above."""
     geo = Geometry(DSD=600.0, DSO=400.0, nVoxel=n, dVoxel=(1.0, 1.0, 1.0), nDetector=det, dDetector=pix,
                    offOrigin=(0.4, -0.3, 0.6), offDetector=(0.3, -0.2))
     ang = synth.circular_angles(views) + 0.013
