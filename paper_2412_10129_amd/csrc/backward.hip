@@ -216,7 +216,7 @@ struct GroupLds {
 // 1, ...), so that a step's columns are a voxel apart again: 128^3 x 36 views on pixels of
 // 4 x 0.5 voxels 607 -> 500 us, 3 x 0.7 487 -> 452.
 constexpr float KMAX = 32.0f;   // most columns and row classes (of 8, rays meet in cells beyond: 96^3 on 8 pixels per voxel 35.1 -> 26.4 ms)
-template <bool SIDDON, int GV>
+template <bool SIDDON, bool PACK, int GV>
 __device__ __forceinline__ void pixel_order(GroupLds<GV>& G, int g, float pu, float pv)
 {
     const int w = G.w[g], h = G.h[g];
@@ -231,21 +231,36 @@ __device__ __forceinline__ void pixel_order(GroupLds<GV>& G, int g, float pu, fl
     G.hp[g] = hp;
     G.rcol[g] = 1.0f / (float)per;
     G.rrow[g] = 1.0f / (float)hp;
-    G.pre[g + 1] = (((w + wide * ku - 1) / (wide * ku)) * per + 63) / 64;
+    const int n = (w + wide * ku - 1) / (wide * ku) * per;
+    G.pre[g + 1] = PACK ? n : (n + 63) / 64;
 }
 
-// Pixel p of view g's order; false when the index falls on padding.  The
-// quotients come from FP32 reciprocals: floor((i + 1/2) r), r = fl(1/n), is
-// i div n for every i < 2^22.  (In a footprint of more pixels than that, of a
-// voxel that covers thousands, both are corrected by an exact remainder step.)
-template <bool SIDDON, int GV>
-__device__ __forceinline__ bool group_pixel(const GroupLds<GV>& G, int g, int p, int& iu, int& iv)
+// Lane `lane` of batch bt: its view g of the group and its pixel; false when it falls on
+// padding.  Batches come in order (g starts at 0 and is kept by the caller); with
+// PACK a batch runs over the views' ends.  The quotients come from FP32 reciprocals:
+// floor((i + 1/2) r), r = fl(1/n), is i div n for every i < 2^22.  (In a footprint of
+// more pixels than that, of a voxel that covers thousands, both are corrected by an
+// exact remainder step.)
+template <bool SIDDON, bool PACK, int GV>
+__device__ __forceinline__ bool group_pixel(const GroupLds<GV>& G, int bt, int lane, int& g, int& iu, int& iv)
 {
-    // the view's layout is the same in every lane: scalar registers
-    const int ku = __builtin_amdgcn_readfirstlane(G.ku[g]), kv = __builtin_amdgcn_readfirstlane(G.kv[g]);
-    const int wide = SIDDON ? 1 : __builtin_amdgcn_readfirstlane(G.wide[g]);
-    const int hp = __builtin_amdgcn_readfirstlane(G.hp[g]), per = wide * ku * kv * hp;
-    const bool large = G.pre[g + 1] - G.pre[g] > (1 << 16);
+    // without PACK the view and its layout are the same in every lane: scalar registers
+    auto get = [&](int v) { return PACK ? v : __builtin_amdgcn_readfirstlane(v); };
+    int p = 64 * bt + lane;
+    bool in = true;
+    if (PACK) {
+        in = p < G.pre[GV];
+        g = 0;
+#pragma unroll
+        for (int st = GV / 2; st > 0; st >>= 1) g += p >= G.pre[g + st] ? st : 0;
+        p -= G.pre[g];
+    } else {
+        while (bt >= get(G.pre[g + 1])) ++g;
+        p -= 64 * get(G.pre[g]);
+    }
+    const int ku = get(G.ku[g]), kv = get(G.kv[g]), wide = SIDDON ? 1 : get(G.wide[g]), hp = get(G.hp[g]);
+    const int per = wide * ku * kv * hp;
+    const bool large = G.pre[g + 1] - G.pre[g] > (PACK ? 1 << 22 : 1 << 16);
     int cg = (int)(((float)p + 0.5f) * G.rcol[g]);
     if (large) {
         const int rem = p - cg * per;
@@ -264,7 +279,7 @@ __device__ __forceinline__ bool group_pixel(const GroupLds<GV>& G, int g, int p,
     const int du = cg * wide * ku + (b >> lw) + (b & (wide - 1)) * ku, dv = a + kv * r;
     iu = G.u0[g] + du;
     iv = G.v0[g] + dv;
-    return du < G.w[g] && dv < G.h[g];
+    return in && du < G.w[g] && dv < G.h[g];
 }
 
 // Prepares the group of views [k, k + n): footprints of the box [lo, hi],
@@ -292,7 +307,7 @@ __device__ __forceinline__ bool group_pixel(const GroupLds<GV>& G, int g, int p,
 // has no more than some thousand rays (N below 2^12 F), that second bound is
 // scaled to 2^31 less 1 %: 2.1e7 units are then left for the roundings of its
 // terms, half a unit each.
-template <bool SIDDON, int NW, int GV>
+template <bool SIDDON, bool PACK, int NW, int GV>
 __device__ __forceinline__ int group_scale(GroupLds<GV>& G, const ViewGeo* __restrict__ tab,
                                            const float* __restrict__ proj, int view0, int k, int n, const float lo[3],
                                            const float hi[3], const DetDims& det, const VolDims& v, float ds,
@@ -323,7 +338,7 @@ __device__ __forceinline__ int group_scale(GroupLds<GV>& G, const ViewGeo* __res
                 }
                 G.f[g] = one;
                 G.most[g] = cu * cv * one;
-                pixel_order<SIDDON>(G, g, f.su, f.sv);
+                pixel_order<SIDDON, PACK>(G, g, f.su, f.sv);
             }
         }
     }
@@ -379,7 +394,8 @@ __device__ __forceinline__ int group_scale(GroupLds<GV>& G, const ViewGeo* __res
     cut = ys / npx * 8.0f;
     if (cut < ym && cut > 0.0f) ex[0] = max(ex[0], fixed_exp(N, cut) + bit);
     else cut = CTMI_INF;
-    return __builtin_amdgcn_readfirstlane(G.pre[GV]);
+    const int last = __builtin_amdgcn_readfirstlane(G.pre[GV]);
+    return PACK ? (last + 63) / 64 : last;
 }
 
 template <int BZ, int T>
@@ -429,7 +445,7 @@ __device__ __forceinline__ void add_at(float o, float q)
                            __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-template <int BZ, int NW, int GV, int WPE>
+template <int BZ, int NW, int GV, int WPE, bool PACK>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE, 8)))
 k_backward_siddon(const float* __restrict__ proj, float* __restrict__ vol, const ViewGeo* __restrict__ tab,
                   const ViewGeo64* __restrict__ tab64, int view0, int nviews, VolDims v, DetDims det, BrickMap m,
@@ -453,15 +469,14 @@ k_backward_siddon(const float* __restrict__ proj, float* __restrict__ vol, const
     for (int k = 0; k < nviews; k += GV) {
         int exs[2] = {0, 0};
         float cut = CTMI_INF;
-        const int nbat = group_scale<true, NW, GV>(G, tab, proj, view0, k, min(GV, nviews - k), lo, hi, det, v, 0.0f,
+        const int nbat = group_scale<true, PACK, NW, GV>(G, tab, proj, view0, k, min(GV, nviews - k), lo, hi, det, v, 0.0f,
                                                    cmax, exs, cut);
         for (int cls = 0; cls < (cut < CTMI_INF ? 2 : 1); ++cls) {
         const int ex = exs[cls];
         int gv = 0;
         for (int bt = wave; bt < nbat; bt += NW) {
-            while (bt >= __builtin_amdgcn_readfirstlane(G.pre[gv + 1])) ++gv;   // the batch's view (uniform)
             int iu, iv;
-            const bool in = group_pixel<true>(G, gv, 64 * (bt - __builtin_amdgcn_readfirstlane(G.pre[gv])) + lane, iu, iv);
+            const bool in = group_pixel<true, PACK>(G, bt, lane, gv, iu, iv);
             float y = 0.0f;
             if (in) y = finite_or_zero(proj[((int64_t)(k + gv) * det.nv + iv) * det.nu + iu]);
             if (y == 0.0f || (fabsf(y) > cut) != (cls != 0)) continue;
@@ -670,7 +685,7 @@ __device__ __forceinline__ void box_samples(const InterpRay& r, const float lo[3
     }
 }
 
-template <int BZ, int NW, int GV, int WPE>
+template <int BZ, int NW, int GV, int WPE, bool PACK>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE, 8)))
 k_backward_interp(const float* __restrict__ proj, float* __restrict__ vol, const ViewGeo* __restrict__ tab,
                   const ViewGeo64* __restrict__ tab64, int view0, int nviews, VolDims v, DetDims det, BrickMap m,
@@ -706,15 +721,14 @@ k_backward_interp(const float* __restrict__ proj, float* __restrict__ vol, const
     for (int k = 0; k < nviews; k += GV) {
         int exs[2] = {0, 0};
         float cut = CTMI_INF;
-        const int nbat = group_scale<false, NW, GV>(G, tab, proj, view0, k, min(GV, nviews - k), lo, hi, det, v, ds,
+        const int nbat = group_scale<false, PACK, NW, GV>(G, tab, proj, view0, k, min(GV, nviews - k), lo, hi, det, v, ds,
                                                     cmax, exs, cut);
         for (int cls = 0; cls < (cut < CTMI_INF ? 2 : 1); ++cls) {
         const int ex = exs[cls];
         int gv = 0;
         for (int bt = wave; bt < nbat; bt += NW) {
-            while (bt >= __builtin_amdgcn_readfirstlane(G.pre[gv + 1])) ++gv;   // the batch's view (uniform)
             int iu, iv;
-            const bool in = group_pixel<false>(G, gv, 64 * (bt - __builtin_amdgcn_readfirstlane(G.pre[gv])) + lane, iu, iv);
+            const bool in = group_pixel<false, PACK>(G, bt, lane, gv, iu, iv);
             float y = 0.0f;
             if (in) y = finite_or_zero(proj[((int64_t)(k + gv) * det.nv + iv) * det.nu + iu]);
             InterpRay r;
@@ -961,18 +975,18 @@ hipError_t launch_halo_add(const Plan& p, float* vol, const float* shell, hipStr
     return hipGetLastError();
 }
 
-template <bool SIDDON, int BZ, int NW, int GV, int WPE>
+template <bool SIDDON, int BZ, int NW, int GV, int WPE, bool PACK = false>
 hipError_t launch_bricks(const Plan& p, const float* proj, float* vol, int64_t view0, int64_t nviews, float beta,
                          float* shell, hipStream_t s)
 {
     const BrickMap m = brick_map(p, BZ);
     const dim3 grid((unsigned)m.nbx * m.nby * m.nbz), block(64 * NW);
     if constexpr (SIDDON) {
-        hipLaunchKernelGGL((k_backward_siddon<BZ, NW, GV, WPE>), grid, block, 0, s, proj, vol, p.d_views, p.d_views64,
+        hipLaunchKernelGGL((k_backward_siddon<BZ, NW, GV, WPE, PACK>), grid, block, 0, s, proj, vol, p.d_views, p.d_views64,
                            (int)view0, (int)nviews, p.vol, p.det, m, beta, p.round_siddon);
         return hipGetLastError();
     } else {
-        hipLaunchKernelGGL((k_backward_interp<BZ, NW, GV, WPE>), grid, block, 0, s, proj, vol, p.d_views, p.d_views64,
+        hipLaunchKernelGGL((k_backward_interp<BZ, NW, GV, WPE, PACK>), grid, block, 0, s, proj, vol, p.d_views, p.d_views64,
                            (int)view0, (int)nviews, p.vol, p.det, m, beta, p.ds, p.round_interp, shell);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -994,14 +1008,52 @@ hipError_t launch_bricks(const Plan& p, const float* proj, float* vol, int64_t v
 // workspace fixes, then also halves the brick (64^3 x 64 views, forward and
 // adjoint: 199 -> 177 us).  A volume of up to 8 planes has one layer of bricks
 // either way, and its workspace holds the shells of bricks of 8.
+//
+// Where a brick of 8 planes has few rays in a view (pixels of about two voxels and
+// more, detectors of a row or two), batches of 64 lanes run over the views' ends, in
+// groups of 16 or 32 views: a batch per view leaves most of its lanes idle.  Footprints of
+// 160 pixels gain 5 to 10 % so (more gain nothing), those of 30 a third to a half: 64 views
+// on pixels of 5 voxels, Siddon, 256^3 644 -> 477 us, 128^3 182 -> 94, interpolated 1058 -> 807
+// and 276 -> 131 (at 128^3 with four waves per brick, since every brick has its few
+// rays; on a detector of one row with eight).  Up to 8 views there is one group
+// either way, and the 16-plane bricks' is the faster one without.
+struct AdjointForm {
+    bool tall, mid;    // bricks of 16 planes; of 8 planes with 8 waves
+    bool sparse;       // few rays per brick and view
+    bool whole;        // the detector is larger than a brick's footprint
+};
+static AdjointForm adjoint_form(const Plan& p)
+{
+    const int64_t bricks = adjoint_bricks(p);
+    const float w = 22.6f / p.pix[0] + 1.0f, h = 8.8f / p.pix[1] + 1.0f;   // a brick's footprint at the volume's centre
+    const float nu = (float)p.det.nu, nv = (float)p.det.nv;
+    AdjointForm f;
+    f.tall = p.vol.nz > 8 && bricks >= 1280;
+    f.mid = !f.tall && bricks >= 512;
+    // (fewer than 2^26 pixels: a group's padded footprints are counted in an int32)
+    f.sparse = fminf(w, nu) * fminf(h, nv) <= 160.0f && nu * nv < 0x1p26f;
+    f.whole = w <= nu && h <= nv;
+    return f;
+}
+
 template <bool SIDDON>
 hipError_t launch_adjoint(const Plan& p, const float* proj, float* vol, int64_t view0, int64_t nviews, float beta,
                           float* shell, hipStream_t s)
 {
-    const int64_t bricks = adjoint_bricks(p);
-    if (p.vol.nz > 8 && bricks >= 1280)
+    const AdjointForm f = adjoint_form(p);
+    if (f.tall) {
+        if (f.sparse && nviews > 8)
+            return launch_bricks<SIDDON, 16, 8, 16, 6, true>(p, proj, vol, view0, nviews, beta, shell, s);
         return launch_bricks<SIDDON, 16, 8, 8, 6>(p, proj, vol, view0, nviews, beta, shell, s);
-    if (bricks >= 512) return launch_bricks<SIDDON, 8, 8, 8, 6>(p, proj, vol, view0, nviews, beta, shell, s);
+    }
+    if (f.mid) {
+        constexpr int GV = SIDDON ? 16 : 32, WPE = SIDDON ? 6 : 4;
+        if (f.sparse && f.whole)
+            return launch_bricks<SIDDON, 8, 4, GV, WPE, true>(p, proj, vol, view0, nviews, beta, shell, s);
+        if (f.sparse) return launch_bricks<SIDDON, 8, 8, GV, WPE, true>(p, proj, vol, view0, nviews, beta, shell, s);
+        return launch_bricks<SIDDON, 8, 8, 8, 6>(p, proj, vol, view0, nviews, beta, shell, s);
+    }
+    if (f.sparse) return launch_bricks<SIDDON, SIDDON ? 4 : 8, 16, 16, 4, true>(p, proj, vol, view0, nviews, beta, shell, s);
     return launch_bricks<SIDDON, SIDDON ? 4 : 8, 16, 16, 4>(p, proj, vol, view0, nviews, beta, shell, s);
 }
 

@@ -330,9 +330,11 @@ int bitrev(int x, int bits)
 
 // Cells of one plane that a 16 x 16 pixel tile of rays at 45 degrees and the
 // slab around it cover, by the pixels' footprint at the volume's centre (largest
-// over the views): sizes the forward kernels' LDS boxes.
-float tile_area(const ctmi::VolDims& v, const ctmi::DetDims& d, const std::vector<ViewGeo>& t)
+// over the views): sizes the forward kernels' LDS boxes.  pix: voxels per pixel there
+// along u and v (smallest over the views).
+float tile_area(const ctmi::VolDims& v, const ctmi::DetDims& d, const std::vector<ViewGeo>& t, float pix[2])
 {
+    pix[0] = pix[1] = HUGE_VALF;
     const double C[3] = {0.5 * v.nx, 0.5 * v.ny, 0.5 * v.nz};
     double most = 0.0;
     for (const ViewGeo& g : t) {
@@ -345,6 +347,8 @@ float tile_area(const ctmi::VolDims& v, const ctmi::DetDims& d, const std::vecto
             v2 += (double)g.DV[i] * g.DV[i];
         }
         const double m = rr > 0.0 ? std::fmin(std::fmax(cr / rr, 0.0), 1.0) : 1.0;
+        pix[0] = std::fmin(pix[0], (float)(m * std::sqrt(u2)));
+        pix[1] = std::fmin(pix[1], (float)(m * std::sqrt(v2)));
         most = std::fmax(most, (22.6 * m * std::sqrt(u2) + 14.0) * (16.0 * m * std::sqrt(v2) + 4.0));
     }
     return (float)most;
@@ -490,7 +494,7 @@ static int create_plan(const ctmi_geometry* geo, const double* angles, const ctm
         view_table_general(geo, views, nviews, t.data(), t64.data());
     else
         view_table(geo, angles, nviews, t.data(), t64.data());
-    p->tile_area = tile_area(p->vol, p->det, t);
+    p->tile_area = tile_area(p->vol, p->det, t, p->pix);
     std::vector<float> Hbr, tw;
     ramp_tables(geo, L, logL, Hbr, tw);
 

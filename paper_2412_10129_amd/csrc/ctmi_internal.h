@@ -89,6 +89,7 @@ struct Plan {
     float entry_siddon;   // largest single adjoint term factor, Siddon (one chord, mm)
     float round_interp;   // most one ray adds to one adjoint cell per unit y: K ds (mm)
     float round_siddon;   // the same for Siddon: one chord (mm)
+    float pix[2];         // voxels per pixel at the volume's centre along u and v (smallest over views)
     float tile_area;      // cells (largest over views) of a plane under a 16 x 16 pixel tile of oblique rays
 };
 

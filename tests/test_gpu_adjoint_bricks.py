@@ -99,11 +99,17 @@ def test_adjoint_wide_column_groups(P, orc, n, det, pix, kind):
     assert _rel(got.cpu().numpy().astype(np.float64), want) < 1e-4
 
 
+TALL = (160, 120, 122)   # 1280 bricks of 8 planes
+
+
 @pytest.mark.parametrize("kind,views", [("siddon", 8), ("siddon", 9), ("siddon", 35), ("interp", 35)])
 @pytest.mark.parametrize("n,det,pix", [
+    (FEW, (10, 14), (7.0, 7.0)), (FEW, (3, 40), (4.0, 1.1)), (SOME, (18, 25), (6.0, 6.0)), (SOME, (1, 130), (1.2, 1.0)),
+    (SOME, (66, 2), (2.4, 1.0)), (TALL, (40, 30), (7.0, 5.0)), (TALL, (70, 45), (4.0, 3.6)),      # few rays per brick
     (FEW, (210, 330), (0.17, 0.22)), (SOME, (14, 130), (8.0, 1.1)), (MANY, (38, 70), (11.0, 2.1))])   # row classes beyond 8; short columns
 def test_adjoint_of_sparse_and_of_dense_footprints(P, orc, n, det, pix, kind, views):
-    """Column groups of 4 ku, and more than eight pixels per voxel.  Tolerance: the parity bar above."""
+    """Batches over the views' ends (few rays per brick and view), column groups of 4 ku,
+    and more than eight pixels per voxel.  Tolerance: the parity bar above."""
     geo = Geometry(DSD=600.0, DSO=400.0, nVoxel=n, dVoxel=(1.0, 1.0, 1.0), nDetector=det, dDetector=pix,
                    offOrigin=(0.4, -0.3, 0.6), offDetector=(0.3, -0.2))
     ang = synth.circular_angles(views) + 0.013
