@@ -458,10 +458,10 @@ hipError_t launch_awtv_grad(const float* x, float* g, int nz, int ny, int nx, fl
     const int nbx = (nx + TVX - 1) / TVX, nby = (ny + 4 * TVY - 1) / (4 * TVY);
     const int tz = (int64_t)nbx * nby * 4 * ((nz + 7) / 8) < 4096 ? 4 : 8;
     const dim3 grid((unsigned)((nbx * nby + 7) / 8 * 8 * ((nz + tz - 1) / tz)));
-    if (delta > 0.0f && delta < CTMI_INF)
-        hipLaunchKernelGGL(k_awtv_grad<true>, grid, dim3(256), 0, s, x, g, nz, ny, nx, tz, nbx, nby,
-                           -1.0f / (delta * delta), eps);
-    else   // plain TV
+    const float nid2 = delta > 0.0f ? -1.0f / (delta * delta) : 0.0f;
+    if (nid2 != 0.0f)
+        hipLaunchKernelGGL(k_awtv_grad<true>, grid, dim3(256), 0, s, x, g, nz, ny, nx, tz, nbx, nby, nid2, eps);
+    else   // plain TV (also a delta whose square is infinite: every weight is 1)
         hipLaunchKernelGGL(k_awtv_grad<false>, grid, dim3(256), 0, s, x, g, nz, ny, nx, tz, nbx, nby, 0.0f, eps);
     return hipGetLastError();
 }

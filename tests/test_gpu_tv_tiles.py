@@ -34,3 +34,11 @@ def test_awtv_grad_tiles(P, orc, delta, shape):
         assert torch.equal(got, ops.awtv_grad(xd, delta=delta, eps=1e-8))
     want = orc.awtv_grad(x.astype(np.float64), delta, 1e-8)
     assert np.linalg.norm(got.cpu().numpy() - want) < 1e-5 * np.linalg.norm(want)
+
+
+def test_delta_with_an_infinite_square_is_plain_tv(P):
+    """delta^2 overflows, so that every weight is 1, also where a difference's square does."""
+    from paper_2412_10129_amd import ops
+    rng = np.random.Generator(np.random.PCG64(62))
+    x = torch.from_numpy((rng.random((5, 9, 70)) * 5e19).astype(np.float32)).cuda()
+    assert torch.equal(ops.awtv_grad(x, delta=1e20), ops.awtv_grad(x, delta=float("inf")))
