@@ -629,6 +629,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CTMI_F
         klo = max((int)__builtin_floorf(fminf(p0, p1)) - 1, 0);
         khi = min((int)__builtin_floorf(fmaxf(p0, p1)) + 1, na - 1);
     }
+    const int kmin = klo, kmax = khi;   // this ray's own (its layers only: a length of 0 in any other times a NaN would count)
     // the three-cell form needs every ray of the wave below 0.99 along b and c
     bool steep = lay && (fabsf(Db) > 0.99f * fabsf(Da) || fabsf(Dc) > 0.99f * fabsf(Da));
 #pragma unroll
@@ -737,7 +738,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CTMI_F
                 roff = inbox ? 4 * ((ib - ob) * st_b + (ic - oc) * st_c) : 0;
             }
         }
-        const int n = idle ? 0 : k1 - k0 + 1, kf = dir > 0 ? k0 : k1;   // layers, and the first in the direction of travel
+        // layers, and the first in the direction of travel
+        const int l0 = max(c0, kmin), l1 = min(c1 - 1, kmax), n = idle ? 0 : l1 - l0 + 1, kf = dir > 0 ? l0 : l1;
         if (inbox && !wave_steep) {
             // The three-cell form, 26 VALU per layer.  o is the LDS address of the
             // ray's cell in FP32 (lds_at); plane numbers and steps are exact too.  No

@@ -99,3 +99,21 @@ def test_tall_grids_under_wide_boxes(P, orc, nz, kind):
     geo = Geometry(DSD=5000.0, DSO=2500.0, nVoxel=(nz, 60, 90), dVoxel=(1.0, 1.0, 1.0), nDetector=(40, 30),
                    dDetector=(0.6, 10.0), offDetector=(0.9 * nz, 0.3))
     _check(P, orc, geo, np.array([0.0, 0.05, 0.7, 1.2, np.pi / 2, 3.2, 4.6]), kind, 49)
+
+
+@pytest.mark.parametrize("n,det,pix", [((40, 45, 50), (60, 70), 1.1), ((20, 30, 25), (120, 130), 0.4)])
+def test_siddon_rays_beside_a_nan_stay_finite(P, orc, n, det, pix):
+    """Voxels of NaN on the volume's faces: every ray through one is NaN, and none is that
+    stays a voxel away from all of them (a ray's walk goes on for the wave's
+    other rays after it has left the volume, with lengths of 0)."""
+    geo = Geometry(DSD=900.0, DSO=600.0, nVoxel=n, dVoxel=(1.0, 1.0, 1.0), nDetector=det, dDetector=(pix, pix))
+    ang = synth.circular_angles(9) + 0.013
+    x = np.random.Generator(np.random.PCG64(81)).random(n).astype(np.float32)
+    hit, near = np.zeros(n), np.zeros(n)
+    for z, y, u in ((n[0] // 3, n[1] // 4, n[2] // 3), (n[0] - 1, 0, n[2] - 1), (0, n[1] // 2, 0), (n[0] // 2, n[1] - 1, n[2] // 2)):
+        x[z, y, u] = np.nan
+        hit[z, y, u] = 1.0
+        near[max(z - 1, 0):z + 2, max(y - 1, 0):y + 2, max(u - 1, 0):u + 2] = 1.0
+    got = np.isnan(P.Plan(geo, ang).forward(torch.from_numpy(x).cuda(), kind="siddon").cpu().numpy())
+    assert got[orc.forward(geo, ang, hit, "siddon") > 1e-3].all()
+    assert not got[orc.forward(geo, ang, near, "siddon") == 0.0].any()
