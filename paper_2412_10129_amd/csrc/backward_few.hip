@@ -18,7 +18,7 @@
 // different lengths keep every lane busy.  32-bit cells hold the round's exact
 // integer sum and are flushed after every round, in a fixed order, so the
 // result is bit-reproducible.
-#include "ctmi_internal.h"
+#include "adjoint_bricks.h"
 
 namespace ctmi {
 
@@ -27,34 +27,12 @@ namespace {
 #ifndef CTMI_BWD_INT_SAMPLES
 #define CTMI_BWD_INT_SAMPLES 6
 #endif
-constexpr int BX = CTMI_BWD_BX, BY = CTMI_BWD_BY, BZ = CTMI_BWD_BZ;   // brick (voxels)
+constexpr int BZ = CTMI_BWD_BZ;                   // planes per brick
 constexpr int NB = BX * BY * BZ;
 constexpr int OWN = NB / 256;                     // voxels owned per thread
 
-struct BrickMap {
-    int nbx, nby, nbz;
-};
-
-__device__ __forceinline__ void brick_origin(const BrickMap& m, int b, int& bx, int& by, int& bz)
-{
-    bx = b % m.nbx;
-    const int r = b / m.nbx;
-    by = r % m.nby;
-    bz = r / m.nby;
-}
-
-// Pixel range whose rays may cross the voxel-centre-coordinate box
-// [lo, hi] (per axis x, y, z): the pixel centres inside the bounding box of
-// the 8 projected corners (the box's silhouette is their convex hull, so a
-// ray through a centre outside it misses the box), widened by FOOT_EPS pixel
-// against the FP32 rounding of the projection (about 1e-4 pixel; a ray that
-// close to the box lies within 0.01 pixel of it, some 100 FP32 position
-// rounding units, so a sample the FP32 walk might still place in the box is
-// never left out), clamped to the detector.  Returns false if empty.
-#ifndef CTMI_BWD_FOOT_EPS
-#define CTMI_BWD_FOOT_EPS 0.01f
-#endif
-constexpr float FOOT_EPS = CTMI_BWD_FOOT_EPS;
+// Pixel range whose rays may cross the voxel-centre-coordinate box [lo, hi] (per
+// axis x, y, z).  Returns false if empty.
 __device__ __forceinline__ bool footprint(const ViewGeo& g, const float lo[3], const float hi[3],
                                           const DetDims& det, int& u0, int& u1, int& v0, int& v1)
 {
@@ -73,48 +51,8 @@ __device__ __forceinline__ bool footprint(const ViewGeo& g, const float lo[3], c
         vmin = fminf(vmin, V * rw);
         vmax = fmaxf(vmax, V * rw);
     }
-    // clamp in float first: the corners may project far outside the detector
-    umin = fminf(fmaxf(umin, -2.0f), (float)det.nu + 1.0f);
-    vmin = fminf(fmaxf(vmin, -2.0f), (float)det.nv + 1.0f);
-    umax = fminf(fmaxf(umax, -2.0f), (float)det.nu + 1.0f);
-    vmax = fminf(fmaxf(vmax, -2.0f), (float)det.nv + 1.0f);
-    u0 = max((int)__builtin_ceilf(umin - FOOT_EPS), 0);
-    v0 = max((int)__builtin_ceilf(vmin - FOOT_EPS), 0);
-    u1 = min((int)__builtin_floorf(umax + FOOT_EPS), det.nu - 1);
-    v1 = min((int)__builtin_floorf(vmax + FOOT_EPS), det.nv - 1);
+    foot_pixels(umin, umax, vmin, vmax, det, u0, u1, v0, v1);
     return u0 <= u1 && v0 <= v1;
-}
-
-// Ray-table slots hold footprint pixels in bit-reversed order: slots that sit
-// next to each other (whose items run on neighbouring lanes) then hold pixels
-// far apart on the detector.  The rays of adjacent pixels cross the same cells
-// at the same steps, and LDS atomics of one instruction from several lanes to
-// one address serialise (about 3x the cost of distinct addresses when 4 lanes
-// share one).
-// Fixed-point scale for one round: the
-// exponent e of the largest power of two (up to exact powers of two) with
-// 2^e cmax m <= 2^30, where cmax bounds a single contribution's matrix
-// factor (K samples of ds) and m > 0 is the round's sum of |y| (finite
-// values only).  Formed from
-// the operands' exponents, so neither a product nor a quotient can
-// overflow or underflow: with cmax = a 2^ec and m = b 2^em (a, b in
-// [1/2, 1)), 2^(30 - ec - em) cmax m = 2^30 a b < 2^30, and one more
-// power of two fits when a b < 1/2.  Contributions are scaled by 2^e and
-// the integer sums by 2^-e with ldexp (exact), so the fixed point works at
-// every magnitude of y that FP32 holds.
-__device__ __forceinline__ int fixed_exp(float cmax, float m)
-{
-    int ec, em;
-    const float a = __builtin_frexpf(cmax, &ec);
-    const float b = __builtin_frexpf(m, &em);
-    return 30 - ec - em + (a * b < 0.5f ? 1 : 0);
-}
-
-// y for finite y, 0 for NaN and infinities (those rays are handled by
-// k_nonfinite after the accumulation)
-__device__ __forceinline__ float finite_or_zero(float y)
-{
-    return __builtin_fabsf(y) <= 0x1.fffffep127f ? y : 0.0f;
 }
 
 // Views are processed in groups of GV, the ray-setup rounds running over the
@@ -196,27 +134,6 @@ __device__ __forceinline__ void flush_view(Acc* acc, int px, int py, int pad, in
     }
 }
 
-__device__ __forceinline__ void store_owned(float* __restrict__ vol, const float own[OWN], const VolDims& v, int x0,
-                                            int y0, int z0, float beta)
-{
-#pragma unroll
-    for (int m = 0; m < OWN; ++m) {
-        const int i = threadIdx.x + 256 * m;
-        const int gx = x0 + i % BX, gy = y0 + (i / BX) % BY, gz = z0 + i / (BX * BY);
-        if (gx >= v.nx || gy >= v.ny || gz >= v.nz) continue;
-        float* o = vol + ((int64_t)gz * v.ny + gy) * v.nx + gx;
-        *o = beta == 0.0f ? own[m] : __builtin_fmaf(beta, *o, own[m]);
-    }
-}
-
-// floor(q + 1/2) as an int32 in one instruction (rintf costs a round and a
-// convert); it differs from round-half-even only on exact ties
-__device__ __forceinline__ int round_int(float q)
-{
-    int r;
-    asm("v_cvt_rpi_i32_f32 %0, %1" : "=v"(r) : "v"(q));
-    return r;
-}
 __device__ __forceinline__ void acc_add(int* a, float q) { atomicAdd(a, round_int(q)); }
 
 constexpr int HX = BX + 2, HY = BY + 2, HZ = BZ + 2;   // interpolated accumulator: brick plus a one-voxel halo
@@ -229,30 +146,8 @@ constexpr int INT_SAMPLES = CTMI_BWD_INT_SAMPLES;  // samples per interpolated i
 // faces (x = BX with y, z in [0, BY] x [0, BZ]; y = BY with x < BX; z = BZ
 // with x < BX, y < BY), written to the plan's halo buffer and added to the
 // neighbouring bricks' voxels by k_halo_add in a fixed order.
-constexpr int HSX = (BY + 1) * (BZ + 1), HSY = BX * (BZ + 1), HSZ = BX * BY;
-constexpr int HALO_SLOTS = HSX + HSY + HSZ;
+constexpr int HALO_SLOTS = Shell<BZ>::N;
 constexpr int NH = (HALO_SLOTS + 255) / 256;   // shell cells per thread
-static_assert(HALO_SLOTS == CTMI_HALO_SLOTS, "halo buffer size");
-
-__device__ __forceinline__ void halo_slot(int h, int& lx, int& ly, int& lz)
-{
-    if (h < HSX) {
-        lx = BX;
-        ly = h % (BY + 1);
-        lz = h / (BY + 1);
-    } else if (h < HSX + HSY) {
-        h -= HSX;
-        lx = h % BX;
-        ly = BY;
-        lz = h / BX;
-    } else {
-        h -= HSX + HSY;
-        lx = h % BX;
-        ly = h / BX;
-        lz = BZ;
-    }
-}
-
 // shell cells -> per-thread FP32 registers, clearing them (accumulator
 // origin at the brick corner minus one voxel)
 template <typename Acc>
@@ -263,7 +158,7 @@ __device__ __forceinline__ void flush_shell(Acc* acc, int e, float hown[NH])
         const int h = threadIdx.x + 256 * m;
         if (h < HALO_SLOTS) {
             int lx, ly, lz;
-            halo_slot(h, lx, ly, lz);
+            Shell<BZ>::cell(h, lx, ly, lz);
             Acc* c = acc + ((lz + 1) * HY + (ly + 1)) * HX + (lx + 1);
             const Acc a = *c;
             *c = 0;
@@ -284,6 +179,12 @@ constexpr int RPT = 2, RAYS = 256 * RPT;
 constexpr int IMAPCAP = CTMI_BWD_IMAPCAP;
 static_assert(RAYS == 512, "slot permutation is a 9-bit reversal");
 
+// Ray-table slots hold footprint pixels in bit-reversed order: slots that sit
+// next to each other (whose items run on neighbouring lanes) then hold pixels
+// far apart on the detector.  The rays of adjacent pixels cross the same cells
+// at the same steps, and LDS atomics of one instruction from several lanes to
+// one address serialise (about 3x the cost of distinct addresses when 4 lanes
+// share one).
 __device__ __forceinline__ int slot_pixel(int s)
 {
     return (int)(__builtin_bitreverse32((unsigned)s) >> 23);
@@ -561,7 +462,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CTMI_B
             flush_view(acc, HX, HY, 1, ex, own);
         }
     }
-    store_owned(vol, own, v, x0, y0, z0, beta);
+    store_owned<BZ, 256>(vol, own, v, x0, y0, z0, beta);
     float* out = shell + (size_t)blockIdx.x * HALO_SLOTS;
 #pragma unroll
     for (int m2 = 0; m2 < NH; ++m2) {
@@ -575,10 +476,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CTMI_B
 hipError_t launch_backward_interp_few_bricks(const Plan& p, const float* proj, float* vol, int64_t view0,
                                              int64_t nviews, float beta, float* shell, hipStream_t s)
 {
-    BrickMap m;
-    m.nbx = (p.vol.nx + BX - 1) / BX;
-    m.nby = (p.vol.ny + BY - 1) / BY;
-    m.nbz = (p.vol.nz + BZ - 1) / BZ;
+    const BrickMap m = brick_map(p, BZ);
     const unsigned blocks = (unsigned)m.nbx * m.nby * m.nbz;
     hipLaunchKernelGGL(k_backward_interp_few, dim3(blocks), dim3(256), 0, s, proj, vol, p.d_views, p.d_views64,
                        (int)view0, (int)nviews, p.vol, p.det, m, beta, p.ds, p.round_interp, shell);
