@@ -45,9 +45,10 @@ PEAK_VALU_TLI = 256 * 4 * 16 * 2.4e9 / 1e12
 #     1 accumulate                                                     = 24
 #   interpolated A^T, per sample: 3 advance, 6 fract, 15 to form the 8
 #     tent weights, 8 FMA scatters                                     = 32
-#   FDK backprojection, per voxel-view update: 3 incremental numerators,
-#     1 rcp, 2 mul, 2 weight, 4 floor/fract, 3 lerps x 2               = 18
-INSTR = {"siddon_fwd": 6, "siddon_bwd": 6, "interp_fwd": 24, "interp_bwd": 32, "fdk_bp": 18}
+#   FDK backprojection, per voxel-view update (the reciprocal, column and
+#     weight are shared by a voxel column): 1 advance, 2 floor/fract, 1 tap
+#     address, 2 row interpolations x 2, 1 between the rows into the sum = 9
+INSTR = {"siddon_fwd": 6, "siddon_bwd": 6, "interp_fwd": 24, "interp_bwd": 32, "fdk_bp": 9}
 
 # source file of each timed kernel (the HBM traffic recorded for a kernel in
 # profiles/traffic.json is used only while that file is unchanged)

@@ -468,7 +468,6 @@ static int create_plan(const ctmi_geometry* geo, const double* angles, const ctm
         double hdiag2 = 0.0;
         for (int a = 0; a < 3; ++a) hdiag2 += geo->dVoxel[a] * geo->dVoxel[a];
         const double hdiag = std::sqrt(hdiag2);
-        p->entry_siddon = (float)(hdiag * 1.0001);
         // one ray crosses a cell once, and items end on cell boundaries, so a
         // ray adds at most one chord to one cell
         p->round_siddon = (float)(hdiag * 1.0001);

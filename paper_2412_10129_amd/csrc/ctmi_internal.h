@@ -86,7 +86,6 @@ struct Plan {
     VolDims vol;
     DetDims det;
     float ds;             // interpolated-projector step, mm
-    float entry_siddon;   // largest single adjoint term factor, Siddon (one chord, mm)
     float round_interp;   // most one ray adds to one adjoint cell per unit y: K ds (mm)
     float round_siddon;   // the same for Siddon: one chord (mm)
     float pix[2];         // voxels per pixel at the volume's centre along u and v (smallest over views)
