@@ -138,7 +138,8 @@ def profile_derived(db_paths, cus=256, xcds=8):
     kernel of the same run (it moves 2^30 bytes each way), L2 hit rate,
     VALU busy (rocprofv3's VALUBusy: SQ_ACTIVE_INST_VALU / CUs / cycles),
     VALU utilisation (active lanes per VALU instruction), VALU
-    wave-instructions per CU-cycle, and LDS bank-conflict cycles per CU-cycle.
+    wave-instructions per CU-cycle, and per CU-cycle the cycles in which LDS
+    works on indexed accesses and those lost to bank conflicts.
     GRBM_GUI_ACTIVE is summed over the XCDs; the per-XCD cycles divide it by
     their count."""
     m = _pmc_means(db_paths)
@@ -148,7 +149,7 @@ def profile_derived(db_paths, cus=256, xcds=8):
     lines = [f"calibration: the 1 GiB stream copy reads FETCH_SIZE {cal.get('FETCH_SIZE', 0):.6g} KiB and "
              f"WRITE_SIZE {cal.get('WRITE_SIZE', 0):.6g} KiB (factors {ff and round(ff, 3)}, {wf and round(wf, 3)})", "",
              "| kernel | HBM read (GB) | HBM write (GB) | L2 hit % | VALU busy % | VALU util % | VALU instr / CU-cycle "
-             "| LDS conflict cycles / CU-cycle |", "|---|---|---|---|---|---|---|---|"]
+             "| LDS busy % | LDS conflict cycles / CU-cycle |", "|---|---|---|---|---|---|---|---|---|"]
     for k in sorted(m):
         d = m[k]
         cyc = d.get("GRBM_GUI_ACTIVE", 0) / xcds
@@ -162,7 +163,8 @@ def profile_derived(db_paths, cus=256, xcds=8):
                 if d.get("SQ_ACTIVE_INST_VALU") else None)
         ipc = d["SQ_INSTS_VALU"] / cus / cyc if cyc and "SQ_INSTS_VALU" in d else None
         ldsc = d["SQ_LDS_BANK_CONFLICT"] / cus / cyc if cyc and "SQ_LDS_BANK_CONFLICT" in d else None
-        lines.append(f"| {k} | {f(rd)} | {f(wr)} | {f(hit)} | {f(busy)} | {f(util)} | {f(ipc)} | {f(ldsc)} |")
+        lds = 100 * d["SQ_LDS_IDX_ACTIVE"] / cus / cyc if cyc and "SQ_LDS_IDX_ACTIVE" in d else None
+        lines.append(f"| {k} | {f(rd)} | {f(wr)} | {f(hit)} | {f(busy)} | {f(util)} | {f(ipc)} | {f(lds)} | {f(ldsc)} |")
     return "\n".join(lines)
 
 

@@ -33,10 +33,10 @@
 // in an LDS table, cut into items and numbered by block scans, with a scale and
 // a flush per round; the interpolated one with eight 32-bit atomics per
 // sample): interpolated, 512^3 x 120 views of 1024 x 768: 152 -> 100 ms (83 -> 55
-// clocks of a CU per 64 samples; LDS at work 84 % of the time, 1.3 vector
-// instructions per clock of the 1 to 1.6 that its mix allows); Siddon, 256^3 x
-// 90 views of 512 x 512: 13.1 -> 7.6 ms (vector instructions 1.15 per clock,
-// LDS at work 21 %).
+// clocks of a CU per 64 samples; at 720 views LDS is at work 78 % of the time, with 1.36
+// vector instructions per clock of the 1 to 1.6 that its mix allows); Siddon, 256^3 x
+// 90 views of 512 x 512: 13.1 -> 7.6 ms (512^3 x 720: 1.31 vector instructions per
+// clock, LDS at work 38 %).
 #include "adjoint_bricks.h"
 
 namespace ctmi {

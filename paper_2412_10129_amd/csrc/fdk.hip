@@ -31,8 +31,8 @@ namespace {
 // FP32 as a multiple of 2^-149 (a denormal has its integer as bits): one fused
 // multiply-add per voxel.
 //
-// LDS reads bound it (77 % of the LDS cycles, 1.2 VALU instructions per CU and
-// clock): 512^3, 360 views on 1024 x 768 33.9 -> 17.7 ms against blocks of 32 x 8
+// LDS reads bound it (74 % of the LDS cycles, 1.15 VALU instructions per CU and
+// clock): 512^3, 360 views on 1024 x 768 33.9 -> 17.6 ms against blocks of 32 x 8
 // columns staged pixel by pixel between barriers, with clamped taps at the edges.
 // ZC 8: 20.5 ms, 32: 17.5 (with five waves per SIMD; small volumes want the smaller).
 constexpr int FDK_T = 16;                       // voxel columns per side
