@@ -185,9 +185,10 @@ __device__ __forceinline__ bool group_pixel(const GroupLds<GV>& G, int bt, int l
 {
     // without PACK the view and its layout are the same in every lane: scalar registers
     auto get = [&](int v) { return PACK ? v : __builtin_amdgcn_readfirstlane(v); };
-    int p = 64 * bt + lane;
+    int p;
     bool in = true;
     if (PACK) {
+        p = 64 * bt + lane;
         in = p < G.pre[GV];
         g = 0;
 #pragma unroll
@@ -195,7 +196,7 @@ __device__ __forceinline__ bool group_pixel(const GroupLds<GV>& G, int bt, int l
         p -= G.pre[g];
     } else {
         while (bt >= get(G.pre[g + 1])) ++g;
-        p -= 64 * get(G.pre[g]);
+        p = 64 * (bt - get(G.pre[g])) + lane;
     }
     const int ku = get(G.ku[g]), kv = get(G.kv[g]), wide = SIDDON ? 1 : get(G.wide[g]), hp = get(G.hp[g]);
     const int per = wide * ku * kv * hp;
